@@ -20,14 +20,12 @@ namespace {
 
 constexpr size_t kAlign = 256;
 constexpr int kMixBlocks = 512;
-constexpr int kQueueBlocks = 2048;
-constexpr int kMaxClasses = 16;
+constexpr int kQueueBlocks = 768;
+constexpr int kMaxClasses = 32;
 // Layout of the ints region: per kernel class the uncertified-queue length,
-// the near-queue length and kXcd item counters of persistent launches; then
-// per instance the count of its ladders outside the radius.
+// the near-queue length; then per instance the count of its ladders outside the radius.
 constexpr int kIntsNear = kMaxClasses;
-constexpr int kIntsClaim = 2 * kMaxClasses;
-constexpr int kIntsInst = kIntsClaim + kMaxClasses * kXcd;
+constexpr int kIntsInst = 2 * kMaxClasses;
 
 size_t align_up(size_t x) { return (x + kAlign - 1) & ~(kAlign - 1); }
 
@@ -79,7 +77,7 @@ int check_inst(const df_inst_t &p, Shape *s) {
 
 // Per-instance workspace regions (byte offsets from the instance base).
 struct Layout {
-    size_t gr, gdm, pdm, gtr, gp32, gtr32, part, norm, gd, chi, w;
+    size_t gr, gdm, pdm, gtr, gp32, gtr32, gsym, gabs, symp, cert, part, norm, gd, chi, w;
     size_t qrep, qlist;               // symmetry tables: int[N] each
     size_t fx, xh, rh, accpart;       // Anderson acceleration (0 when unused)
     size_t total;
@@ -103,6 +101,10 @@ Layout layout_of(const Shape &s, int slots) {
     L.gtr = take(gam);
     L.gp32 = take(gam);              // (gamma, gamma_ij gamma_ji) as 4 floats
     L.gtr32 = take(gam / 2);
+    L.gsym = take(gam);
+    L.gabs = take(gam / 4);
+    L.symp = take((size_t)s.n_om * kPrepChunks * 4 * sizeof(float));
+    L.cert = take((size_t)s.items);
     L.part = take((size_t)s.n_chunks * fld);
     L.norm = take((size_t)kMixBlocks * 2 * sizeof(double));
     L.gd = take(fld);
@@ -256,8 +258,13 @@ int ladder_variant(int n_nu, int prec) {
 
 // Instances that share a kernel build, its padded size and launch shape are
 // fused in one launch.
+// The certified FP64 choices all run the symmetric kernel, built per 16
+// frequencies.
+bool fp64_certified(int v) { return v == LV_GJB || v == LV_GJB_O3 || v == LV_GJB_O4; }
+
 int ladder_class(int n_nu, int prec) {
     const int v = ladder_variant(n_nu, prec);
+    if (fp64_certified(choice_variant(v))) return LV_GJB * 256 + (n_nu + 15) / 16 * 16;
     return v * 256 + variant_padded_size(v, n_nu);
 }
 
@@ -265,7 +272,6 @@ int ladder_class(int n_nu, int prec) {
 struct ClassSlots {
     int *queue, *queue_count;         // uncertified items -> pivoting kernel
     int *near, *near_count;           // refined kernel: items near the instability -> FP64 kernel
-    int *claim;                       // kXcd item counters of a persistent launch
 };
 
 ClassSlots class_slots(void *ws, const Global &g, int cls, size_t queue_off) {
@@ -275,47 +281,16 @@ ClassSlots class_slots(void *ws, const Global &g, int cls, size_t queue_off) {
     c.near = at<int>(ws, g.near) + queue_off;
     c.queue_count = ints + cls;
     c.near_count = ints + kIntsNear + cls;
-    c.claim = ints + kIntsClaim + cls * kXcd;
     return c;
 }
 
-// Work-groups of a persistent launch: p times the resident work-groups of
-// the build on the whole device, at most one per item.
-int persistent_grid(int v, int n_nu, int p, int n_items) {
-    int per_cu = 0;
-    switch (v) {
-        case LV_GJB: per_cu = ladder_gjb_occupancy(n_nu, 0); break;
-        case LV_GJB_O3: per_cu = ladder_gjb_occupancy(n_nu, 3); break;
-        case LV_GJB_O4: per_cu = ladder_gjb_occupancy(n_nu, 4); break;
-        case LV_MIXED: per_cu = ladder_mixed_occupancy(n_nu, 0); break;
-        case LV_MIXED_O3: per_cu = ladder_mixed_occupancy(n_nu, 3); break;
-        case LV_MIXED_O4: per_cu = ladder_mixed_occupancy(n_nu, 4); break;
-        case LV_FP32: per_cu = ladder_fp32_occupancy(n_nu, 0); break;
-        case LV_FP32_O4: per_cu = ladder_fp32_occupancy(n_nu, 4); break;
-        case LV_FP32_O5: per_cu = ladder_fp32_occupancy(n_nu, 5); break;
-        default: break;
-    }
-    static int cus = -1;
-    if (cus < 0) {
-        int dev = 0, n = 0;
-        if (hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-            n = 0;
-        cus = n;
-    }
-    long g = (long)p * (per_cu > 0 ? per_cu : 1) * (cus > 0 ? cus : 1);
-    if (g > n_items) g = n_items;
-    return g < 1 ? 1 : (int)g;
-}
-
 // Launch the ladder for the items in a (single instance, or a fused table)
-// with choice c (variant and launch shape).  The certified kernels queue their
-// uncertified items to the pivoting kernel; the refined kernel first queues
-// its items near the instability to the FP64 certified kernel, which queues
-// its own uncertified ones to the pivoting kernel.  The class's counters must
-// be zero before the call.
+// with choice c.  The FP32 kernel queues its uncertified items, the refined
+// kernel its items near the instability, the screening of the FP64 class its
+// uncertified items and those of vertices that are not symmetric; one launch
+// over the queues follows.  The class's counters must be zero before the call.
 int launch_ladder_variant(int c, LadderArgs a, const ClassSlots &q, hipStream_t st) {
-    const int v = choice_variant(c), p = choice_persist(c);
+    const int v = choice_variant(c);
     switch (v) {
         case LV_VECTOR: HIPCHK(launch_ladder_fp64(a, st)); return DF_OK;
         case LV_MFMA: HIPCHK(launch_ladder_mfma_f64(a, st)); return DF_OK;
@@ -323,13 +298,10 @@ int launch_ladder_variant(int c, LadderArgs a, const ClassSlots &q, hipStream_t 
     }
     a.queue = q.queue;
     a.queue_count = q.queue_count;
-    int grid = a.n_items;
-    if (p > 0) {
-        a.claim = q.claim;
-        grid = persistent_grid(v, a.n_nu, p, a.n_items);
-    }
+    const int grid = a.n_items;
     const bool refined = (v == LV_MIXED || v == LV_MIXED_O3 || v == LV_MIXED_O4);
-    if (refined) {
+    const bool fp64 = fp64_certified(v);
+    if (refined || fp64) {
         a.near_queue = q.near;
         a.near_count = q.near_count;
     }
@@ -340,30 +312,15 @@ int launch_ladder_variant(int c, LadderArgs a, const ClassSlots &q, hipStream_t 
         case LV_MIXED: HIPCHK(launch_ladder_mixed(a, 0, grid, st)); break;
         case LV_MIXED_O3: HIPCHK(launch_ladder_mixed(a, 3, grid, st)); break;
         case LV_MIXED_O4: HIPCHK(launch_ladder_mixed(a, 4, grid, st)); break;
-        case LV_GJB_O3: HIPCHK(launch_ladder_gjb_f64(a, 3, grid, st)); break;
-        case LV_GJB_O4: HIPCHK(launch_ladder_gjb_f64(a, 4, grid, st)); break;
-        default: HIPCHK(launch_ladder_gjb_f64(a, 0, grid, st)); break;
+        default:
+            // FP64: the items are screened (certificate, Gamma^(2)); those of
+            // symmetric vertices run in the symmetric kernel, the rest is queued
+            HIPCHK(launch_ladder_screen(a, st));
+            HIPCHK(launch_ladder_sym(a, st));
+            a.screened = 1;
+            break;
     }
-    const int qblocks = a.n_items < kQueueBlocks ? a.n_items : kQueueBlocks;
-    if (refined) {
-        // the near-instability items: FP64 certified kernel over the near queue
-        LadderArgs b = a;
-        b.claim = nullptr;
-        b.near_queue = nullptr;
-        b.near_count = nullptr;
-        b.in_queue = q.near;
-        b.in_count = q.near_count;
-        HIPCHK(launch_ladder_gjb_f64(b, ladder_gjb_has_occ3(a.n_nu) ? 3 : 0, qblocks, st));
-    }
-    LadderArgs b = a;
-    b.claim = nullptr;
-    b.near_queue = nullptr;
-    b.near_count = nullptr;
-    b.queue = nullptr;
-    b.queue_count = nullptr;
-    b.in_queue = q.queue;
-    b.in_count = q.queue_count;
-    HIPCHK(launch_ladder_fp64_queue(b, qblocks, st));
+    HIPCHK(launch_ladder_rest(a, a.n_items < kQueueBlocks ? a.n_items : kQueueBlocks, st));
     return DF_OK;
 }
 
@@ -396,7 +353,7 @@ int stage_transform_gd(const Shape &s, const double *gd, double *gr, hipStream_t
 }
 
 int stage_bubble(const df_inst_t &p, const Shape &s, const double *gr, double *chi,
-                 hipStream_t st) {
+                 int *zero, int n_zero, hipStream_t st) {
     BubbleArgs a{};
     a.grid = grid_of(s);
     a.n_nu = s.n_nu;
@@ -404,12 +361,17 @@ int stage_bubble(const df_inst_t &p, const Shape &s, const double *gr, double *c
     a.beta = p.beta;
     a.gr = gr;
     a.chi = chi;
+    a.zero = zero;
+    a.n_zero = n_zero;
     HIPCHK(launch_bubble(a, st));
     return DF_OK;
 }
 
-int stage_gamma_prep(const df_inst_t &p, const Shape &s, void *ws, size_t base, const Layout &L,
-                     hipStream_t st) {
+// zero: the call's counters are cleared too (the ladder launches follow on the stream)
+int stage_gamma_prep(const df_inst_t &p, const Plan &P, int i, void *ws, bool zero, hipStream_t st) {
+    const Shape &s = P.shape[i];
+    const Layout &L = P.lay[i];
+    const size_t base = P.base[i];
     GammaPrepArgs a{};
     a.n_nu = s.n_nu;
     a.n_om = s.n_om;
@@ -420,6 +382,13 @@ int stage_gamma_prep(const df_inst_t &p, const Shape &s, void *ws, size_t base, 
     a.gtr = at<double>(ws, base + L.gtr);
     a.gp32 = at<float>(ws, base + L.gp32);
     a.gtr32 = at<float>(ws, base + L.gtr32);
+    a.gsym = at<double>(ws, base + L.gsym);
+    a.gabs = at<float>(ws, base + L.gabs);
+    a.symp = at<float>(ws, base + L.symp);
+    if (zero) {
+        a.zero = at<int>(ws, P.g.ints);
+        a.n_zero = kIntsInst + (int)P.shape.size();
+    }
     HIPCHK(launch_gamma_prep(a, st));
     return DF_OK;
 }
@@ -509,8 +478,10 @@ struct FusedClass {
     int n_nu;                         // any member's n_nu (same padded size)
     int t0, t1;                       // table range
     int items;                        // total items of the class
+    int sblocks;                      // work-groups of its screening launch
     size_t queue_off;                 // first queue slot (ints)
     int full;                         // every member's n_nu equals the padded size
+    int full_sym;                     // every member's n_nu is the class's multiple of 16
 };
 
 struct Fused {
@@ -518,6 +489,43 @@ struct Fused {
     std::vector<FusedClass> cls;
     std::vector<LadderInst> table;    // host copy of the device table
 };
+
+// One entry of the device table: the instance's ladder inputs in the workspace,
+// its outputs, and its position in the launch (items, screening work-groups).
+LadderInst table_entry(const Plan &P, int i, void *ws, bool sym, const double *chi, double *w,
+                       double *logdet, int8_t *status, int *items, int *sblocks) {
+    const Shape &s = P.shape[i];
+    const Layout &L = P.lay[i];
+    const size_t b = P.base[i];
+    LadderInst d{};
+    d.gdm = at<double>(ws, b + L.gdm);
+    d.pdm = at<double>(ws, b + L.pdm);
+    d.gtr = at<double>(ws, b + L.gtr);
+    d.gp32 = at<float>(ws, b + L.gp32);
+    d.gtr32 = at<float>(ws, b + L.gtr32);
+    d.gsym = at<double>(ws, b + L.gsym);
+    d.gabs = at<float>(ws, b + L.gabs);
+    d.symp = at<float>(ws, b + L.symp);
+    d.cert = at<uint8_t>(ws, b + L.cert);
+    d.chi = chi;
+    d.w = w;
+    d.logdet = logdet;
+    d.status = status;
+    d.count = at<int>(ws, P.g.ints) + kIntsInst + i;
+    d.n_nu = s.n_nu;
+    d.n_om = s.n_om;
+    d.N = s.N;
+    d.item0 = *items;
+    d.sblk0 = *sblocks;
+    if (sym) {
+        d.qlist = at<int>(ws, b + L.qlist);
+        d.n_q = s.n_irr;
+        d.im0 = s.im0;
+    }
+    *items += sym ? s.items_sym : s.items;
+    *sblocks += ladder_screen_blocks(s.n_nu, s.n_om - (sym ? s.im0 : 0), sym ? s.n_irr : s.N);
+    return d;
+}
 
 // Group the active instances by ladder class and write the device table.
 // Ordinary (not captured) stream work, synchronised before returning.
@@ -539,38 +547,23 @@ int build_fused(const df_inst_t *inst, const Plan &P, const std::vector<int> &ac
         FusedClass c{};
         c.t0 = (int)F->table.size();
         c.items = 0;
+        c.sblocks = 0;
         c.queue_off = qoff;
         c.full = 1;
+        c.full_sym = 1;
         for (int i : act) {
             if (ladder_class(P.shape[i].n_nu, prec[i]) != key) continue;
             const Shape &s = P.shape[i];
             const Layout &L = P.lay[i];
             const size_t b = P.base[i];
-            LadderInst d{};
-            d.gdm = at<double>(ws, b + L.gdm);
-            d.pdm = at<double>(ws, b + L.pdm);
-            d.gtr = at<double>(ws, b + L.gtr);
-            d.gp32 = at<float>(ws, b + L.gp32);
-            d.gtr32 = at<float>(ws, b + L.gtr32);
-            d.chi = inst[i].chi ? inst[i].chi : at<double>(ws, b + L.chi);
-            d.w = inst[i].w ? inst[i].w : at<double>(ws, b + L.w);
-            d.logdet = inst[i].logdet;
-            d.status = inst[i].status;
-            d.count = at<int>(ws, P.g.ints) + kIntsInst + i;
-            d.n_nu = s.n_nu;
-            d.n_om = s.n_om;
-            d.N = s.N;
-            d.item0 = c.items;
-            if (sym) {
-                d.qlist = at<int>(ws, b + L.qlist);
-                d.n_q = s.n_irr;
-                d.im0 = s.im0;
-            }
-            c.items += sym ? s.items_sym : s.items;
+            F->table.push_back(table_entry(P, i, ws, sym,
+                                           inst[i].chi ? inst[i].chi : at<double>(ws, b + L.chi),
+                                           inst[i].w ? inst[i].w : at<double>(ws, b + L.w),
+                                           inst[i].logdet, inst[i].status, &c.items, &c.sblocks));
             c.n_nu = s.n_nu;
             if (s.n_nu != ladder_gjb_padded_size(s.n_nu)) c.full = 0;
+            if (s.n_nu % 16) c.full_sym = 0;
             c.variant = ladder_variant(s.n_nu, prec[i]);
-            F->table.push_back(d);
             F->active.push_back(i);
         }
         c.t1 = (int)F->table.size();
@@ -596,11 +589,12 @@ int queue_fused_iteration(const df_inst_t *inst, const Plan &P, const Fused &F,
         double *chi = inst[i].chi ? inst[i].chi : at<double>(ws, b + L.chi);
         rc = stage_dual_gf(inst[i], s, inst[i].sigma, gd, gr, st);
         if (rc != DF_OK) return rc;
-        rc = stage_bubble(inst[i], s, gr, chi, st);
+        // (the first bubble also clears the counters of the ladder launches)
+        const bool first = i == F.active[0];
+        rc = stage_bubble(inst[i], s, gr, chi, first ? at<int>(ws, P.g.ints) : nullptr,
+                          first ? kIntsInst + (int)P.shape.size() : 0, st);
         if (rc != DF_OK) return rc;
     }
-    int *ints = at<int>(ws, P.g.ints);
-    HIPCHK(launch_zero_ints(ints, kIntsInst + (int)P.shape.size(), st));
     for (size_t c = 0; c < F.cls.size(); ++c) {
         const FusedClass &k = F.cls[c];
         LadderArgs a{};
@@ -608,8 +602,10 @@ int queue_fused_iteration(const df_inst_t *inst, const Plan &P, const Fused &F,
         a.n_insts = k.t1 - k.t0;
         a.n_nu = k.n_nu;
         a.full = k.full;
+        a.full_sym = k.full_sym;
         a.item0 = 0;
         a.n_items = k.items;
+        a.n_sblk = k.sblocks;
         rc = launch_ladder_variant(k.variant, a, class_slots(ws, P.g, (int)c, k.queue_off), st);
         if (rc != DF_OK) return rc;
     }
@@ -813,7 +809,7 @@ int df_bubble(const df_inst_t *inst, int32_t n_inst, void *ws, size_t ws_bytes, 
         double *gr = at<double>(ws, P.base[i] + P.lay[i].gr);
         rc = stage_transform_gd(s, inst[i].gd, gr, st);
         if (rc != DF_OK) return rc;
-        rc = stage_bubble(inst[i], s, gr, inst[i].chi, st);
+        rc = stage_bubble(inst[i], s, gr, inst[i].chi, nullptr, 0, st);
         if (rc != DF_OK) return rc;
     }
     return DF_OK;
@@ -877,7 +873,7 @@ int df_bubble_noalloc(const df_inst_t *inst, int32_t n_inst, df_stream_t stream)
         (void)check_inst(inst[i], &s);
         rc = stage_transform_gd(s, inst[i].gd, gr, st);
         if (rc != DF_OK) return rc;
-        rc = stage_bubble(inst[i], s, gr, inst[i].chi, st);
+        rc = stage_bubble(inst[i], s, gr, inst[i].chi, nullptr, 0, st);
         if (rc != DF_OK) return rc;
     }
     return DF_OK;
@@ -908,14 +904,13 @@ int df_ladder_solve(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts
         std::vector<int> act(n_inst), pr(n_inst, prec);
         for (int i = 0; i < n_inst; ++i) {
             act[i] = i;
-            rc = stage_gamma_prep(inst[i], P.shape[i], ws, P.base[i], P.lay[i], st);
+            rc = stage_gamma_prep(inst[i], P, i, ws, i == 0, st);
             if (rc == DF_OK && sym) rc = stage_sym_tables(P.shape[i], ws, P.base[i], P.lay[i], st);
             if (rc != DF_OK) return rc;
         }
         Fused F;
         rc = build_fused(inst, P, act, pr, sym, ws, &F, st);
         if (rc != DF_OK) return rc;
-        HIPCHK(launch_zero_ints(ints, kIntsInst + n_inst, st));
         for (size_t c = 0; c < F.cls.size(); ++c) {
             const FusedClass &k = F.cls[c];
             LadderArgs a{};
@@ -923,8 +918,10 @@ int df_ladder_solve(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts
             a.n_insts = k.t1 - k.t0;
             a.n_nu = k.n_nu;
             a.full = k.full;
+            a.full_sym = k.full_sym;
             a.item0 = 0;
             a.n_items = k.items;
+            a.n_sblk = k.sblocks;
             rc = launch_ladder_variant(k.variant, a, class_slots(ws, P.g, (int)c, k.queue_off), st);
             if (rc != DF_OK) return rc;
         }
@@ -941,15 +938,19 @@ int df_ladder_solve(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts
         const Shape &s = P.shape[i];
         const Layout &L = P.lay[i];
         const size_t b = P.base[i];
-        rc = stage_gamma_prep(inst[i], s, ws, b, L, st);
+        rc = stage_gamma_prep(inst[i], P, i, ws, true, st);
         if (rc != DF_OK) return rc;
-        HIPCHK(launch_zero_ints(ints, kIntsInst + n_inst, st));
         LadderArgs a{};
         a.gdm = at<double>(ws, b + L.gdm);
         a.pdm = at<double>(ws, b + L.pdm);
         a.gtr = at<double>(ws, b + L.gtr);
         a.gp32 = at<float>(ws, b + L.gp32);
         a.gtr32 = at<float>(ws, b + L.gtr32);
+        a.gsym = at<double>(ws, b + L.gsym);
+        a.gabs = at<float>(ws, b + L.gabs);
+        a.symp = at<float>(ws, b + L.symp);
+        a.cert = at<uint8_t>(ws, b + L.cert);
+        a.n_sblk = ladder_screen_blocks(s.n_nu, s.n_om - (sym ? s.im0 : 0), sym ? s.n_irr : s.N);
         a.chi = inst[i].chi;
         a.w = inst[i].w;
         a.logdet = inst[i].logdet;
@@ -959,6 +960,7 @@ int df_ladder_solve(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts
         a.n_om = s.n_om;
         a.N = s.N;
         a.full = s.n_nu == ladder_gjb_padded_size(s.n_nu);
+        a.full_sym = s.n_nu % 16 == 0;
         a.item0 = 0;
         a.n_items = s.items;
         if (sym) {
@@ -1033,7 +1035,7 @@ int df_iterate(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts, int
                            ? opts->graph_unroll : 1;
 
     for (int i = 0; i < n_inst; ++i) {
-        rc = stage_gamma_prep(inst[i], P.shape[i], ws, P.base[i], P.lay[i], st);
+        rc = stage_gamma_prep(inst[i], P, i, ws, false, st);
         if (rc != DF_OK) return rc;
         if (opts->symmetry) {
             rc = stage_sym_tables(P.shape[i], ws, P.base[i], P.lay[i], st);
@@ -1271,7 +1273,7 @@ int df_autotune(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts, vo
         if (seen) continue;
         done.push_back(n_nu);
         std::vector<LadderInst> table;
-        int items = 0;
+        int items = 0, sblocks = 0;
         for (int i = i0; i < n_inst && rc == DF_OK; ++i) {
             const Shape &s = P.shape[i];
             if (s.n_nu != n_nu) continue;
@@ -1280,24 +1282,11 @@ int df_autotune(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts, vo
             double *gr = at<double>(ws, b + L.gr);
             double *gd = at<double>(ws, b + L.gd);
             double *chi = at<double>(ws, b + L.chi);
-            rc = stage_gamma_prep(inst[i], s, ws, b, L, st);
+            rc = stage_gamma_prep(inst[i], P, i, ws, false, st);
             if (rc == DF_OK) rc = stage_dual_gf(inst[i], s, inst[i].sigma, gd, gr, st);
-            if (rc == DF_OK) rc = stage_bubble(inst[i], s, gr, chi, st);
-            LadderInst d{};
-            d.gdm = at<double>(ws, b + L.gdm);
-            d.pdm = at<double>(ws, b + L.pdm);
-            d.gtr = at<double>(ws, b + L.gtr);
-            d.gp32 = at<float>(ws, b + L.gp32);
-            d.gtr32 = at<float>(ws, b + L.gtr32);
-            d.chi = chi;
-            d.w = at<double>(ws, b + L.w);
-            d.count = ints + kIntsInst + i;
-            d.n_nu = s.n_nu;
-            d.n_om = s.n_om;
-            d.N = s.N;
-            d.item0 = items;
-            items += s.items;
-            table.push_back(d);
+            if (rc == DF_OK) rc = stage_bubble(inst[i], s, gr, chi, nullptr, 0, st);
+            table.push_back(table_entry(P, i, ws, false, chi, at<double>(ws, b + L.w), nullptr, nullptr,
+                                        &items, &sblocks));
         }
         if (rc != DF_OK) break;
         if (hipMemcpyAsync(at<LadderInst>(ws, P.g.table), table.data(),
@@ -1311,8 +1300,10 @@ int df_autotune(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts, vo
         a.n_insts = (int)table.size();
         a.n_nu = n_nu;
         a.full = n_nu == ladder_gjb_padded_size(n_nu);
+        a.full_sym = n_nu % 16 == 0;
         a.item0 = 0;
         a.n_items = items;
+        a.n_sblk = sblocks;
         for (int prec : precs) {
         // two passes over the candidates, each variant keeping its faster
         // pass: a variant timed right after the slow pivoting kernels (or
@@ -1322,6 +1313,8 @@ int df_autotune(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts, vo
         for (int pass = 0; pass < 2 && rc == DF_OK; ++pass)
         for (int v = 0; v < kChoices && rc == DF_OK; ++v) {
             if (!variant_supports(v, n_nu, prec)) continue;
+            // (the certified FP64 choices run the same kernels: the default stands for them)
+            if (fp64_certified(choice_variant(v)) && v != default_variant(n_nu, prec)) continue;
             constexpr int kReps = 3;
             float ms = 0.f;
             for (int r = 0; r <= kReps && rc == DF_OK; ++r) {   // r = 0: untimed first launch
@@ -1423,11 +1416,11 @@ int df_lattice(const df_inst_t *inst, double mu, double *sigma_lat, double *g_la
     s1.n_om = 1;
     double *gr = at<double>(ws, L.gr);
     rc = stage_transform_gd(s1, f.gd, gr, st);
-    if (rc == DF_OK) rc = stage_bubble(p, s1, gr, at<double>(ws, L.chi0), st);
+    if (rc == DF_OK) rc = stage_bubble(p, s1, gr, at<double>(ws, L.chi0), nullptr, 0, st);
     if (rc == DF_OK) rc = stage_transform_gd(s1, f.fg, gr, st);
-    if (rc == DF_OK) rc = stage_bubble(p, s1, gr, at<double>(ws, L.L), st);
+    if (rc == DF_OK) rc = stage_bubble(p, s1, gr, at<double>(ws, L.L), nullptr, 0, st);
     if (rc == DF_OK) rc = stage_transform_gd(s1, f.gl, gr, st);
-    if (rc == DF_OK) rc = stage_bubble(p, s1, gr, at<double>(ws, L.bub), st);
+    if (rc == DF_OK) rc = stage_bubble(p, s1, gr, at<double>(ws, L.bub), nullptr, 0, st);
     if (rc != DF_OK) return rc;
 
     LatticeChiArgs c{};

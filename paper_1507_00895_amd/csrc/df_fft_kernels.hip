@@ -59,6 +59,12 @@ __global__ __launch_bounds__(NTH) void k_dual_gf(DualGfArgs a) {
         st(a.gr_out, (size_t)n * g.N + r, scale(X[r], invN));
 }
 
+// Clear the counters of the ladder launches that follow on the stream (one
+// work-group of a kernel before them: no launch of its own).
+__device__ __forceinline__ void zero_ints(int *p, int n) {
+    for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0;
+}
+
 // ------------------------------------------------------------------------
 // chi_{m,n}(q) = -T FFT_r[ gr_n(-r) gr_{n+m}(r) ](q); zero when n+m leaves
 // the window.  One block per (n, m).
@@ -72,6 +78,7 @@ __global__ __launch_bounds__(NTH) void k_bubble(BubbleArgs a) {
     const int n = blockIdx.x, im = blockIdx.y;
     const int m = im - (a.n_om - 1) / 2;
     const int n2 = n + m;
+    if (n == 0 && im == 0) zero_ints(a.zero, a.n_zero);
     double *out = a.chi + 2 * ((size_t)im * a.n_nu + n) * g.N;
     if (n2 < 0 || n2 >= a.n_nu) {
         for (int q = threadIdx.x; q < g.N; q += blockDim.x) st(out, q, cd{0.0, 0.0});
@@ -226,37 +233,75 @@ __global__ __launch_bounds__(256) void k_norm_final(const double *part, int n_pa
 }
 
 // ------------------------------------------------------------------------
-// gamma^{d/m} = gamma^uu +- gamma^ud  and  P^c[i][j] = gamma^c_ij gamma^c_ji.
+// gamma^{d/m} = gamma^uu +- gamma^ud, P^c[i][j] = gamma^c_ij gamma^c_ji and the
+// layouts and copies of them that the ladder kernels read.  One block per 256
+// elements of a bosonic index, both channels; its partial maxima tell whether
+// gamma^c is symmetric.  The symmetric ladder takes the symmetric part S =
+// (gamma + gamma^T) / 2: with gamma = S + A, A antisymmetric, the first-order change of
+// Gamma_nn is ((1 + Gamma chi) A (1 + chi Gamma))_nn, the diagonal of an
+// antisymmetric matrix, i.e. zero; so is that of log det, tr(chi (1 - S chi)^-1 A),
+// and Gamma^(2)_nn uses P itself.  Results change by (|A| / |gamma|)^2 at most
+// times powers of the condition number: with |A_ij| <= 2^-40 max |gamma| far
+// below rounding.  (Rounding of the inputs makes |A| / max |gamma| 1e-16 at half
+// filling and up to 4e-14 for the Lehmann vertices at n_nu = 128.)
 // ------------------------------------------------------------------------
 __global__ __launch_bounds__(256) void k_gamma_prep(GammaPrepArgs a) {
+    __shared__ float red[4][4];
+    if (blockIdx.x == 0 && blockIdx.y == 0) zero_ints(a.zero, a.n_zero);
     const size_t nn = (size_t)a.n_nu * a.n_nu;
     const size_t tot = (size_t)a.n_om * nn;
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < tot;
-         e += (size_t)gridDim.x * blockDim.x) {
-        const size_t mb = e / nn;
-        const int i = (int)((e % nn) / a.n_nu), j = (int)(e % a.n_nu);
-        const size_t et = mb * nn + (size_t)j * a.n_nu + i;
+    const size_t b0 = (size_t)blockIdx.y * nn;
+    const size_t u = (size_t)blockIdx.x * 256 + threadIdx.x;
+    float big[2] = {0.f, 0.f}, dif[2] = {0.f, 0.f};
+    if (u < nn) {
+        const int i = (int)(u / a.n_nu), j = (int)(u % a.n_nu);
+        const size_t e = b0 + u, et = b0 + (size_t)j * a.n_nu + i;
         const cd uu = ld(a.guu, e), ud = ld(a.gud, e);
         const cd uut = ld(a.guu, et), udt = ld(a.gud, et);
-        const cd gd = uu + ud, gm = uu - ud;
-        const cd gdt = uut + udt, gmt = uut - udt;
-        st(a.gdm, e, gd);
-        st(a.gdm, tot + e, gm);
-        st(a.pdm, e, gd * gdt);
-        st(a.pdm, tot + e, gm * gmt);
-        if (a.gtr) {
-            st(a.gtr, e, gdt);
-            st(a.gtr, tot + e, gmt);
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const cd g = c == 0 ? uu + ud : uu - ud;
+            const cd gt = c == 0 ? uut + udt : uut - udt;
+            const cd p = g * gt;
+            const size_t o = c * tot + e;
+            st(a.gdm, o, g);
+            st(a.pdm, o, p);
+            st(a.gtr, o, gt);
+            st4f(a.gp32, o, (float)g.re, (float)g.im, (float)p.re, (float)p.im);
+            st2f(a.gtr32, o, (float)gt.re, (float)gt.im);
+            st(a.gsym, o, cd{0.5 * (g.re + gt.re), 0.5 * (g.im + gt.im)});
+            // |gamma|, transposed (a modulus below the FP32 range counts as its
+            // smallest normal value)
+            float m = (float)sqrt(fma(gt.re, gt.re, gt.im * gt.im));
+            if (m < 1.17549435e-38f && (gt.re != 0.0 || gt.im != 0.0)) m = 1.17549435e-38f;
+            a.gabs[o] = m;
+            // a NaN makes the maximum difference NaN, and the comparison below false
+            const float d = (float)(fabs(g.re - gt.re) + fabs(g.im - gt.im));
+            if (!(m <= big[c])) big[c] = m;
+            if (!(d <= dif[c])) dif[c] = d;
         }
-        if (a.gp32) {
-            const cd pd = gd * gdt, pmm = gm * gmt;
-            st4f(a.gp32, e, (float)gd.re, (float)gd.im, (float)pd.re, (float)pd.im);
-            st4f(a.gp32, tot + e, (float)gm.re, (float)gm.im, (float)pmm.re, (float)pmm.im);
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1)
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const float m = __shfl_xor(big[c], off, 64), d = __shfl_xor(dif[c], off, 64);
+            if (!(m <= big[c])) big[c] = m;
+            if (!(d <= dif[c])) dif[c] = d;
         }
-        if (a.gtr32) {
-            st2f(a.gtr32, e, (float)gdt.re, (float)gdt.im);
-            st2f(a.gtr32, tot + e, (float)gmt.re, (float)gmt.im);
-        }
+    const int w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        red[0][w] = big[0];
+        red[1][w] = big[1];
+        red[2][w] = dif[0];
+        red[3][w] = dif[1];
+    }
+    __syncthreads();
+    if (threadIdx.x < 4) {
+        float m = red[threadIdx.x][0];
+        for (int x = 1; x < 4; ++x)
+            if (!(red[threadIdx.x][x] <= m)) m = red[threadIdx.x][x];
+        a.symp[4 * ((size_t)blockIdx.y * kPrepChunks + blockIdx.x) + threadIdx.x] = m;
     }
 }
 
@@ -330,10 +375,7 @@ hipError_t launch_zero_ints(int *p, int n, hipStream_t s) {
 }
 
 hipError_t launch_gamma_prep(const GammaPrepArgs &a, hipStream_t s) {
-    const size_t tot = (size_t)a.n_om * a.n_nu * a.n_nu;
-    int blocks = (int)((tot + 255) / 256);
-    if (blocks > 4096) blocks = 4096;
-    hipLaunchKernelGGL(k_gamma_prep, dim3(blocks), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_gamma_prep, dim3(prep_chunks(a.n_nu), a.n_om), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

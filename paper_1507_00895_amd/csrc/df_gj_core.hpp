@@ -923,7 +923,7 @@ __device__ __forceinline__ int gj_logdet(const cplx<T> *pivv, cd *out_logdet, in
     const double E = wave_sum((double)e);            // exact: integers below 2^53
     constexpr double LN2_HI = 0x1.62e42fefa3800p-1;  // ln 2 to 42 bits: E * LN2_HI exact for |E| < 2^11
     constexpr double LN2_LO = 0x1.ef35793c76730p-45; // ln 2 - LN2_HI
-    const double lre = fma(E, LN2_HI, fma(E, LN2_LO, log(hypot(P.re, P.im))));
+    const double lre = fma(E, LN2_HI, fma(E, LN2_LO, 0.5 * log(fma(P.re, P.re, P.im * P.im))));
     const double ph = atan2(P.im, P.re);
     *out_logdet = cd{lre, ph};
     if (!isfinite(lre) || !isfinite(ph)) return 2;

@@ -33,6 +33,8 @@ struct BubbleArgs {
     double beta;
     const double *gr;                // [n_nu][N]
     double *chi;                     // [n_om][n_nu][N]
+    int *zero;                       // counters to clear (may be null)
+    int n_zero;
 };
 
 struct SigmaArgs {
@@ -85,7 +87,22 @@ struct GammaPrepArgs {
     double *gtr;                     // [2][n_om][n_nu][n_nu] (may be null)
     float *gp32;                     // [2][n_om][n_nu][n_nu] (gamma, gamma_ij gamma_ji) in FP32, or null
     float *gtr32;                    // [2][n_om][n_nu][n_nu] gamma transposed in FP32, or null
+    double *gsym;                    // [2][n_om][n_nu][n_nu] (gamma + gamma^T) / 2
+    float *gabs;                     // [2][n_om][n_nu][n_nu] |gamma| transposed, FP32
+    float *symp;                     // [n_om][kPrepChunks][4]: partial maxima of its chunks
+    int *zero;                       // counters to clear (may be null)
+    int n_zero;
 };
+
+// Work-groups of k_gamma_prep per bosonic index (256 vertex elements each), and
+// what their partial maxima say: {max |gamma^d|, max |gamma^m|, max |gamma^d_ij -
+// gamma^d_ji|, the same of gamma^m} of a chunk.  A NaN stays.
+constexpr int kPrepChunks = 64;
+__host__ __device__ inline int prep_chunks(int n_nu) { return (n_nu * n_nu + 255) / 256; }
+// difference within 2^-40 of the largest modulus (an infinite one would pass any)
+__device__ inline bool prep_symmetric(float m, float d) {
+    return d <= m * 9.094947e-13f && m < 3.0e38f;
+}
 
 // One instance of a fused multi-instance ladder launch (device-side table).
 struct LadderInst {
@@ -98,6 +115,11 @@ struct LadderInst {
     int item0;                       // first global item of this instance
     const int *qlist;                // symmetry-reduced launch (else null): solved q
     int n_q, im0;                    // their count; first solved bosonic index
+    const double *gsym;              // symmetric part of the vertex, |gamma| and the maxima that tell
+    const float *gabs;               // whether it is symmetric (GammaPrepArgs)
+    const float *symp;
+    uint8_t *cert;                   // [items]: 1 for items of the symmetric kernel (k_ladder_screen)
+    int sblk0;                       // first work-group of this instance in a screening launch
 };
 
 struct LadderArgs {
@@ -115,10 +137,6 @@ struct LadderArgs {
     int *queue_count;                // its length (zeroed before the launch)
     int *near_queue;                 // refined kernel: items whose certificate bound is
     int *near_count;                 // >= CERT_NEAR_MIXED go here for the FP64 kernel
-    const int *in_queue;             // queue launches: process these items ...
-    const int *in_count;             // ... (count on the device) instead of item0 + block
-    int *claim;                      // persistent launches: per-XCD item counters [kXcd]
-                                     // (zeroed before the launch); null: static mapping
     const LadderInst *insts;         // non-null: fused launch over n_insts instances,
     int n_insts;                     // items are global; the fields above are resolved per item
     const float *gp32;               // FP32 ladder: (gamma, gamma_ij gamma_ji) pairs, FP32
@@ -127,6 +145,13 @@ struct LadderArgs {
     int n_q, im0;
     int full;                        // 1: every instance of the launch has n_nu equal to the
                                      // padded size (the mask-free build runs)
+    const double *gsym;              // symmetric FP64 ladder and its screening (see LadderInst)
+    const float *gabs;
+    const float *symp;
+    uint8_t *cert;
+    int sblk0, n_sblk;               // work-groups of the screening launch
+    int full_sym;                    // 1: every instance has n_nu equal to the same multiple of 16
+    int screened;                    // 1: near_queue holds items certified by the screening kernel
 };
 
 // Fused launches: find the instance of a global item, fill the per-instance
@@ -158,6 +183,8 @@ __device__ __forceinline__ int resolve_item(LadderArgs &a, int item) {
     a.qlist = d.qlist;
     a.n_q = d.n_q;
     a.im0 = d.im0;
+    a.gsym = d.gsym;
+    a.cert = d.cert;
     return item - d.item0;
 }
 
@@ -228,63 +255,6 @@ __device__ __forceinline__ int xcd_item(int b, int n) {
     return x * per + (x < rem ? x : rem) + i;
 }
 
-// Items of a certified ladder launch, handed to body(global item) one at a
-// time; uniform over the work-group, which may run several items in turn
-// (LDS is reused: a barrier separates them).  The body appears once, so the
-// compiler inlines it once.
-//   in_queue set: the device-side queue of another kernel, grid-stride.
-//   claim null:   XCD x's contiguous range (as xcd_item) split over the
-//                 work-groups on that XCD; with one work-group per item this
-//                 is exactly the mapping of xcd_item.
-//   claim set:    persistent work-groups take the next item of their XCD's
-//                 range from its counter, then help the other XCDs' ranges.
-// k counts the items this work-group has run; tries (thread 0 only) the XCD
-// ranges it found empty.  Contains barriers when claim is set.
-__device__ __forceinline__ int next_item(const LadderArgs &a, int k, int *tries, int *s_item) {
-    if (a.in_queue) {
-        const int u = (int)blockIdx.x + k * (int)gridDim.x;
-        return u < *a.in_count ? a.in_queue[u] : -1;
-    }
-    const int n = a.n_items, per = n / kXcd, rem = n % kXcd;
-    const int x = blockIdx.x % kXcd;
-    if (!a.claim) {
-        const int len = per + (x < rem ? 1 : 0), start = x * per + (x < rem ? x : rem);
-        const int wgs = ((int)gridDim.x - x + kXcd - 1) / kXcd;   // work-groups on XCD x
-        const int i = (int)blockIdx.x / kXcd + k * wgs;
-        return i < len ? a.item0 + start + i : -1;
-    }
-    if (threadIdx.x == 0) {
-        int item = -1;
-        while (*tries < kXcd) {
-            const int xx = (x + *tries) % kXcd;
-            const int len = per + (xx < rem ? 1 : 0);
-            const int c = atomicAdd(a.claim + xx, 1);
-            if (c < len) {
-                item = a.item0 + xx * per + (xx < rem ? xx : rem) + c;
-                break;
-            }
-            ++*tries;
-        }
-        *s_item = item;
-    }
-    __syncthreads();
-    const int item = *s_item;
-    __syncthreads();
-    return item;
-}
-
-template <typename F>
-__device__ __forceinline__ void for_each_item(const LadderArgs &a, F &&body) {
-    __shared__ int s_item;
-    int tries = 0;
-    for (int k = 0;; ++k) {
-        const int item = __builtin_amdgcn_readfirstlane(next_item(a, k, &tries, &s_item));
-        if (item < 0) break;
-        body(item);
-        __syncthreads();
-    }
-}
-
 // Lattice observables (df_lattice.hip)
 struct LatticeFieldArgs {
     int n_nu, N;
@@ -325,14 +295,11 @@ hipError_t launch_ladder_fp64(const LadderArgs &a, hipStream_t s);
 // MFMA blocked Gauss-Jordan variant (n_nu <= 64)
 int ladder_mfma_padded_size(int n_nu);
 hipError_t launch_ladder_mfma_f64(const LadderArgs &a, hipStream_t s);
-// certified pivot-free blocked Gauss-Jordan (n_nu <= 128); occ = 3 / 4 select
-// the builds capped at three / four waves per SIMD (n_nu <= 64), 0 the
-// compiler's budget; grid: work-groups of the launch (n_items for one per
-// item; fewer with a.claim set for persistent work-groups, or a queue launch)
+// the queued items: near_queue (optional) by certified pivot-free blocked
+// Gauss-Jordan, queue by partial pivoting; grid: work-groups of the launch
 int ladder_gjb_padded_size(int n_nu);
 bool ladder_gjb_has_occ3(int n_nu);
-hipError_t launch_ladder_gjb_f64(const LadderArgs &a, int occ, int grid, hipStream_t s);
-int ladder_gjb_occupancy(int n_nu, int occ);   // resident work-groups per CU
+hipError_t launch_ladder_rest(const LadderArgs &a, int grid, hipStream_t s);
 // mixed precision: FP32 certified sweep + one FP64 residual correction, and
 // the FP32 sweep alone (n_nu <= 128); occ as above (refined: 0, 3 up to 96,
 // 4 up to 64; FP32: 0, and 4, 5 up to 64)
@@ -342,10 +309,13 @@ bool ladder_mixed_has_occ(int n_nu, int occ);
 bool ladder_fp32_has_occ(int n_nu, int occ);
 hipError_t launch_ladder_mixed(const LadderArgs &a, int occ, int grid, hipStream_t s);
 hipError_t launch_ladder_fp32(const LadderArgs &a, int occ, int grid, hipStream_t s);
-int ladder_mixed_occupancy(int n_nu, int occ);
-int ladder_fp32_occupancy(int n_nu, int occ);
-// pivoting kernel over a device-side queue of items (grid-stride, fixed grid)
-hipError_t launch_ladder_fp64_queue(const LadderArgs &a, int blocks, hipStream_t s);
+// FP64 ladder of symmetric vertices (n_nu <= 128) behind its screening kernel,
+// which leaves t = (gamma chi gamma)_nn in W, marks the certified items of
+// symmetric vertices and queues the rest (near_queue: not symmetric; queue:
+// not certified)
+int ladder_screen_blocks(int n_nu, int n_m, int n_q);
+hipError_t launch_ladder_screen(const LadderArgs &a, hipStream_t s);
+hipError_t launch_ladder_sym(const LadderArgs &a, hipStream_t s);
 hipError_t launch_zero_ints(int *p, int n, hipStream_t s);
 hipError_t launch_sym_tables(const SymTableArgs &a, hipStream_t s);
 hipError_t launch_sym_expand(const SymExpandArgs &a, hipStream_t s);

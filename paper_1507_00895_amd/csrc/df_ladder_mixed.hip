@@ -61,12 +61,4 @@ hipError_t launch_ladder_fp32(const LadderArgs &a, int occ, int grid, hipStream_
     return fp32_dispatch(a.n_nu, &a, occ, grid, s) == 0 ? hipSuccess : hipErrorLaunchFailure;
 }
 
-int ladder_mixed_occupancy(int n_nu, int occ) {
-    return ladder_mixed_has_occ(n_nu, occ) ? mixed_dispatch(n_nu, nullptr, occ, 0, nullptr) : 0;
-}
-
-int ladder_fp32_occupancy(int n_nu, int occ) {
-    return ladder_fp32_has_occ(n_nu, occ) ? fp32_dispatch(n_nu, nullptr, occ, 0, nullptr) : 0;
-}
-
 }  // namespace df

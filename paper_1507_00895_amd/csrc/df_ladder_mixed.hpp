@@ -536,31 +536,21 @@ template <int NP> constexpr bool has_fp32_occ(int occ) {
         else hipLaunchKernelGGL((KERN<NP, false>), dim3(grid), dim3(NP * 4), 0, s, *a);        \
     } while (0)
 
-template <typename K>
-static int occupancy_of(K kern, int threads) {
-    int nb = 0;
-    return hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, kern, threads, 0) == hipSuccess ? nb : 0;
-}
-
-// grid: work-groups of the launch (one per item unless persistent or a queue);
-// with query set, only the resident work-groups per CU are returned
+// grid: work-groups of the launch, one per item
 template <int NP>
-static int mixed_build(const LadderArgs *a, int occ, int grid, hipStream_t s, bool query) {
+static int mixed_build(const LadderArgs *a, int occ, int grid, hipStream_t s) {
     if (!has_mixed_occ<NP>(occ)) return -1;
     if (occ == 3) {
         if constexpr (NP <= 96) {
-            if (query) return occupancy_of(k_ladder_mixed_o3<NP, false>, NP * 4);
             DF_LAUNCH_FULL_M(k_ladder_mixed_o3);
             return hipGetLastError() == hipSuccess ? 0 : -1;
         }
     } else if (occ == 4) {
         if constexpr (NP <= 64) {
-            if (query) return occupancy_of(k_ladder_mixed_o4<NP, false>, NP * 4);
             DF_LAUNCH_FULL_M(k_ladder_mixed_o4);
             return hipGetLastError() == hipSuccess ? 0 : -1;
         }
     } else {
-        if (query) return occupancy_of(k_ladder_mixed<NP, false>, NP * 4);
         DF_LAUNCH_FULL_M(k_ladder_mixed);
         return hipGetLastError() == hipSuccess ? 0 : -1;
     }
@@ -568,29 +558,26 @@ static int mixed_build(const LadderArgs *a, int occ, int grid, hipStream_t s, bo
 }
 
 template <int NP>
-static int fp32_build(const LadderArgs *a, int occ, int grid, hipStream_t s, bool query) {
+static int fp32_build(const LadderArgs *a, int occ, int grid, hipStream_t s) {
     if (!has_fp32_occ<NP>(occ)) return -1;
     if (occ == 4 || occ == 5) {
         if constexpr (NP <= 64) {
             if (occ == 4) {
-                if (query) return occupancy_of(k_ladder_fp32_o4<NP, false>, NP * 4);
                 DF_LAUNCH_FULL_M(k_ladder_fp32_o4);
             } else {
-                if (query) return occupancy_of(k_ladder_fp32_o5<NP, false>, NP * 4);
                 DF_LAUNCH_FULL_M(k_ladder_fp32_o5);
             }
             return hipGetLastError() == hipSuccess ? 0 : -1;
         }
         return -1;
     }
-    if (query) return occupancy_of(k_ladder_fp32<NP, false>, NP * 4);
-    if (NP == 96 && grid == a->n_items && a->full && !a->in_queue && !a->claim)
+    if (NP == 96 && grid == a->n_items && a->full)
         hipLaunchKernelGGL((k_ladder_fp32_x2<NP, true>), dim3((grid + 1) / 2), dim3(NP * 8), 0, s, *a);
     else DF_LAUNCH_FULL_M(k_ladder_fp32);
     return hipGetLastError() == hipSuccess ? 0 : -1;
 }
 
-// per-size builds: launch (a non-null) or occupancy query (a null)
+// per-size builds
 #define DF_MIXED_DECLARE(NP)                                                        \
     int mixed_build_##NP(const LadderArgs *a, int occ, int grid, hipStream_t s);    \
     int fp32_build_##NP(const LadderArgs *a, int occ, int grid, hipStream_t s);
@@ -603,11 +590,11 @@ DF_MIXED_DECLARE(128)
 
 #define DF_MIXED_INSTANTIATE(NP)                                                    \
     int mixed_build_##NP(const LadderArgs *a, int occ, int grid, hipStream_t s) {   \
-        return mixed_build<NP>(a, occ, grid, s, a == nullptr);                      \
+        return mixed_build<NP>(a, occ, grid, s);                                    \
     }
 #define DF_FP32_INSTANTIATE(NP)                                                     \
     int fp32_build_##NP(const LadderArgs *a, int occ, int grid, hipStream_t s) {    \
-        return fp32_build<NP>(a, occ, grid, s, a == nullptr);                       \
+        return fp32_build<NP>(a, occ, grid, s);                                     \
     }
 
 }  // namespace df

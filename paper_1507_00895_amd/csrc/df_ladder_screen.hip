@@ -1,0 +1,229 @@
+// Screening of the FP64 ladder items, one kernel for 16 momenta at a time: what
+// every item needs but the elimination does not have to carry.
+//   t_n(q)   = (gamma chi gamma)_nn = sum_n' (gamma_nn' gamma_n'n) chi_n'(q), the
+//              second-order term of eq. (sd): a matrix product over q, on the
+//              FP64 matrix cores; left in W, where the ladder kernel finds it
+//   rho(|M|) <= max_i (B v)_i / v_i, B = |gamma| diag |chi| + eps: the
+//              Collatz-Wielandt certificate of the pivot-free elimination
+//              (df_gj_core.hpp), with true moduli, by power steps on the FP32
+//              matrix cores.
+// Work-group: one channel, one bosonic index, 16 momenta; its four waves share
+// chi in LDS and take the 16-row blocks in turn, the rows of |gamma| staying in
+// registers over the power steps.  Per item the two products are n^2
+// operations each; formed inside the ladder kernel, as rows of one item spread
+// over a wave, they cost about 1500 vector instructions per item (an eighth of
+// the n_nu = 64 elimination), here about 40 matrix instructions.
+#include "df_gj_core.hpp"
+
+namespace df {
+
+constexpr int SCREEN_STEPS = 6;
+constexpr double SCREEN_MAX = 0.999;
+
+// Symmetric to rounding (see k_gamma_prep): the largest |gamma_ij - gamma_ji|
+// against the largest |gamma|, over the partial maxima of k_gamma_prep.
+// One wave, one chunk per lane; uniform result.
+__device__ __forceinline__ bool vertex_symmetric(const float *part, int n, int c, int lane) {
+    float m = 0.f, d = 0.f;
+    if (lane < prep_chunks(n)) {
+        m = part[4 * lane + c];
+        d = part[4 * lane + 2 + c];
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const float om = __shfl_xor(m, off, 64), od = __shfl_xor(d, off, 64);
+        if (!(om <= m)) m = om;
+        if (!(od <= d)) d = od;
+    }
+    return prep_symmetric(m, d);
+}
+
+template <int NT>
+__global__ __launch_bounds__(256) void k_ladder_screen(LadderArgs a0) {
+    constexpr int NP = 16 * NT;
+    typedef MT<double>::v4 d4;
+    typedef MT<float>::v4 f4;
+    __shared__ cd X[NP][16];          // chi[k][q]
+    __shared__ float xa[NP][16];      // |chi|
+    __shared__ float vv[2][NP][16];   // vectors of the power steps
+    __shared__ float red[2][4][16];   // per wave and momentum: its largest quotient
+
+    const int tid = threadIdx.x;
+    const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int l = tid & 63, lj = l & 15, lg = l >> 4;
+    LadderArgs a = a0;
+    int blk = xcd_item(blockIdx.x, gridDim.x);
+    int item0 = a0.item0;
+    if (a0.insts) {
+        const ConstLadderInstPtr tab = (ConstLadderInstPtr)(const void *)a0.insts;
+        int k = 0;
+        while (k + 1 < a0.n_insts && tab[k + 1].sblk0 <= blk) ++k;
+        const auto &d = tab[k];
+        blk -= d.sblk0;
+        item0 = d.item0;
+        a.pdm = d.pdm;
+        a.gabs = d.gabs;
+        a.symp = d.symp;
+        a.cert = d.cert;
+        a.chi = d.chi;
+        a.w = d.w;
+        a.n_nu = d.n_nu;
+        a.n_om = d.n_om;
+        a.N = d.N;
+        a.qlist = d.qlist;
+        a.n_q = d.n_q;
+        a.im0 = d.im0;
+    }
+    const int n = a.n_nu, N = a.N, nm1 = n - 1;
+    const int n_q = a.qlist ? a.n_q : N;
+    const int m0 = a.qlist ? a.im0 : 0, n_m = a.n_om - m0;
+    const int qb = (n_q + 15) / 16;
+    // channels next to each other: the second one's chi comes from the L2
+    const int c = blk & 1;
+    blk >>= 1;
+    const int im = m0 + blk / qb;
+    const int k0 = 16 * (blk % qb);
+    const int kq = k0 + lj;                       // this lane's momentum
+    const bool qin = kq < n_q;
+    const int kc = qin ? kq : n_q - 1;
+    const int q = a.qlist ? a.qlist[kc] : kc;
+
+    constexpr float FMIN = 1.17549435e-38f;
+    for (int k = tid >> 4; k < NP; k += 16) {     // (tid & 15 == lj)
+        const cd x = ld(a.chi, ((size_t)im * n + (k < nm1 ? k : nm1)) * N + q);
+        const cd v = k < n ? x : cd{0.0, 0.0};
+        X[k][lj] = v;
+        // (a modulus below the FP32 range counts as its smallest normal value:
+        // the bound stays an upper bound)
+        float m = (float)sqrt(fma(v.re, v.re, v.im * v.im));
+        if (m < FMIN && (v.re != 0.0 || v.im != 0.0)) m = FMIN;
+        xa[k][lj] = m;
+    }
+
+    const int cm = c * a.n_om + im;
+    const double *pm = a.pdm + 2 * (size_t)cm * n * n;
+    const float *ga = a.gabs + (size_t)cm * n * n;
+    // this wave's rows of |gamma| (A operand of every k-slice)
+    constexpr int NI = (NT + 3) / 4;
+    float gr[NI][4 * NT];
+#pragma unroll
+    for (int y = 0; y < NI; ++y) {
+        const int i = 16 * (w + 4 * y) + lj;
+        if (w + 4 * y < NT) {
+#pragma unroll
+            for (int s = 0; s < 4 * NT; ++s) {
+                const int k = 4 * s + lg;
+                gr[y][s] = ga[(size_t)(k < nm1 ? k : nm1) * n + (i < nm1 ? i : nm1)];
+            }
+        }
+    }
+    __syncthreads();
+
+    // ---- t: P is symmetric, read by rows k
+#pragma unroll
+    for (int y = 0; y < NI; ++y) {
+        const int I = w + 4 * y;
+        if (I >= NT) continue;
+        const int ic = 16 * I + lj < nm1 ? 16 * I + lj : nm1;
+        d4 T1 = {0, 0, 0, 0}, T2 = {0, 0, 0, 0}, T3 = {0, 0, 0, 0}, T4 = {0, 0, 0, 0};
+#pragma unroll 8
+        for (int s = 0; s < 4 * NT; ++s) {
+            const int k = 4 * s + lg;
+            const cd p = ld(pm, (size_t)(k < nm1 ? k : nm1) * n + ic);
+            const cd x = X[k][lj];
+            T1 = MT<double>::mma(p.re, x.re, T1);
+            T2 = MT<double>::mma(p.im, x.im, T2);
+            T3 = MT<double>::mma(p.re, x.im, T3);
+            T4 = MT<double>::mma(p.im, x.re, T4);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int i = 16 * I + lg + 4 * r;
+            if (qin && i < n) st(a.w, ((size_t)cm * n + i) * N + q, cd{T1[r] - T2[r], T3[r] + T4[r]});
+        }
+    }
+    // ---- certificate: power steps from v = 1 until all 16 momenta pass.  The
+    // sums are FP32 over non-negative terms: within (n + 4) 2^-24 of exact
+    // with the rounding of the moduli, and the bound is inflated by
+    // 1 + 1e-5; eps = 1e-6 keeps v positive.  A NaN never passes.
+    bool pass = false;                            // this lane's momentum
+    for (int it = 0; it < SCREEN_STEPS; ++it) {
+        float ratio = 0.f;
+#pragma unroll
+        for (int y = 0; y < NI; ++y) {
+            const int I = w + 4 * y;
+            if (I >= NT) continue;
+            f4 U = {0, 0, 0, 0};
+#pragma unroll
+            for (int s = 0; s < 4 * NT; ++s) {
+                const int k = 4 * s + lg;
+                float b = xa[k][lj];
+                if (it > 0) b *= vv[it & 1][k][lj];
+                U = MT<float>::mma(gr[y][s], b, U);
+            }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = 16 * I + 4 * lg + r;
+                const float vi = it == 0 ? 1.f : vv[it & 1][i][lj];
+                const float u = fmaf(1e-6f, vi, U[r]);
+                const float rr = u * __builtin_amdgcn_rcpf(vi);
+                if (i < n && !(rr <= ratio)) ratio = rr;
+                vv[(it + 1) & 1][i][lj] = i < n ? u : 1.f;
+            }
+        }
+#pragma unroll
+        for (int off = 16; off <= 32; off <<= 1) {
+            const float o = __shfl_xor(ratio, off, 64);
+            if (!(o <= ratio)) ratio = o;
+        }
+        if (lg == 0) red[it & 1][w][lj] = ratio;
+        __syncthreads();
+        float m = red[it & 1][0][lj];
+#pragma unroll
+        for (int x = 1; x < 4; ++x)
+            if (!(red[it & 1][x][lj] <= m)) m = red[it & 1][x][lj];
+        pass = pass || (double)m * (1.0 + 1e-5) < SCREEN_MAX;
+        // uniform: every wave holds the same 16 momenta
+        if (__all(pass || !qin)) break;
+    }
+    if (w != 0) return;
+    const bool sym = vertex_symmetric(a.symp + 4 * (size_t)im * kPrepChunks, n, c, l);
+    if (lg == 0) {
+        const int item = a.qlist ? (c * n_m + (im - m0)) * n_q + kq : cm * N + q;
+        if (qin) a.cert[item] = (pass && sym) ? 1 : 0;
+        // the others are appended to a queue, one counter update per work-group
+        const bool put = qin && !(pass && sym);
+        const unsigned long long near = __ballot(put && pass), piv = __ballot(put && !pass);
+        int base_n = 0, base_p = 0;
+        if (lj == 0) {
+            if (near) base_n = atomicAdd(a.near_count, __popcll(near));
+            if (piv) base_p = atomicAdd(a.queue_count, __popcll(piv));
+        }
+        base_n = __builtin_amdgcn_readfirstlane(base_n);
+        base_p = __builtin_amdgcn_readfirstlane(base_p);
+        const unsigned long long below = (1ull << lj) - 1;
+        if (put && pass) a.near_queue[base_n + __popcll(near & below)] = item0 + item;
+        if (put && !pass) a.queue[base_p + __popcll(piv & below)] = item0 + item;
+    }
+}
+
+// work-groups of one instance's screening: channels x bosonic indices x blocks of
+// 16 momenta
+int ladder_screen_blocks(int n_nu, int n_m, int n_q) {
+    (void)n_nu;
+    return 2 * n_m * ((n_q + 15) / 16);
+}
+
+hipError_t launch_ladder_screen(const LadderArgs &a, hipStream_t s) {
+    if (a.n_sblk <= 0 || !a.queue || !a.near_queue) return hipErrorInvalidValue;
+    switch ((a.n_nu + 15) / 16) {
+#define DF_SCREEN(NT) \
+    case NT: hipLaunchKernelGGL(k_ladder_screen<NT>, dim3(a.n_sblk), dim3(256), 0, s, a); break;
+        DF_SCREEN(1) DF_SCREEN(2) DF_SCREEN(3) DF_SCREEN(4)
+        DF_SCREEN(5) DF_SCREEN(6) DF_SCREEN(7) DF_SCREEN(8)
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+}  // namespace df

@@ -1,15 +1,19 @@
 // Learned warm start: forward, backward and Adam kernels of a small MLP on the
 // FP32 matrix cores, behind the C ABI of include/df_mlp.h.
 //
-// GEMM: C[M x N] = op(A)[M x K] op(B)[K x N], one 64 x 64 tile per work-group
-// of four waves (each a 32 x 32 quadrant = 2 x 2 tiles of
-// v_mfma_f32_16x16x4f32), K staged through LDS in chunks of 16.  Fused
-// epilogues: bias, SiLU with the pre-activation saved, multiplication by
-// SiLU'(Z) of the previous layer (backward), split-K partial sums reduced in
-// a fixed order by a second kernel.
-//
-// FP32 16x16x4 lane layout (gfx950): A[i][k] at lane i + 16k, B[k][j] at lane
-// j + 16k, C[i][j] at lane j + 16 (i / 4), register i % 4.
+// GEMM: C[M x N] = op(A)[M x K] op(B)[K x N], one T x T tile per work-group of four
+// waves (quadrants of v_mfma_f32_16x16x4f32 tiles), T = 64, or 32 where 64 would
+// leave the CUs with too few work-groups.  At these sizes (batch 1024-4096, width
+// 256) a launch is a few hundred work-groups of 8-16 K chunks: it is bound by
+// the latency of its loads, so a chunk is 32 deep and the next one's operands
+// are in flight, as 16-byte loads into registers, while this one's products
+// run.  Fused epilogues: bias, SiLU with the pre-activation saved, the mean
+// squared error with its gradient (last layer), multiplication by SiLU'(Z) of
+// the previous layer (backward), column sums of A (the bias gradient), split-K
+// partial sums reduced in a fixed order by a second kernel.  Batch 4096, widths
+// 132-256-256-256-96: loss and gradients 137 us; 1219 us with 16-deep chunks of scalar
+// loads (a product 30 us) and a column-sum kernel of one work-group per 64 columns
+// (four of 217 us).
 #include <math.h>
 
 #include "../../include/df_mlp.h"
@@ -22,16 +26,19 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 struct GemmArgs {
     int M, N, K;
     const float *A;
-    int lda, transA;          // A(m, k) = transA ? A[k lda + m] : A[m lda + k]
+    int lda;
     const float *B;
-    int ldb, transB;          // B(k, n) = transB ? B[n ldb + k] : B[k ldb + n]
+    int ldb;
     float *C;
     int ldc;
     const float *bias;        // [N] or null
     float *Zout;              // pre-activation store (ldc layout) or null
     int act;                  // 1: SiLU
+    const float *T;           // target [M][ldc] or null: C = 2 (v - T) / (M N), lpart the
+    float *lpart;             // work-group's sum of (v - T)^2
     const float *dz;          // backward: multiply by SiLU'(dz[m ldc + n]) or null
-    float *part;              // split-K: partial sums [gridDim.z][M][N]
+    float *asum;              // [M] sums of A over K (work-groups of the first tile column), or null
+    float *part;              // split-K: partial sums [gridDim.z][M][N], then [gridDim.z][M] of asum
     int kchunk;               // K range per split (multiple of 16)
 };
 
@@ -42,65 +49,133 @@ __device__ __forceinline__ float dsilu(float z) {
     return s * (1.0f + z * (1.0f - s));
 }
 
+// One operand tile of a K chunk: T rows (m or n) x KC.  KMAJOR = false: row-major
+// in memory with K contiguous, kept so in LDS (stride 36: the 16 rows x 4 k of an
+// MFMA operand fall in 64 different banks); true: rows contiguous for each k,
+// LDS [k][row] with stride T + 16 (same).  VEC: 16-byte loads (base and leading
+// dimension aligned); elements outside the matrix or the K range are zero.
+constexpr int KC = 32;
+template <int T, bool KMAJOR> struct TileLds {
+    static constexpr int LD = KMAJOR ? T + 16 : KC + 4;
+    float x[KMAJOR ? KC * LD : T * LD];
+    __device__ __forceinline__ float at(int row, int k) const { return KMAJOR ? x[k * LD + row] : x[row * LD + k]; }
+};
+template <int T, bool KMAJOR, bool VEC> struct TileLoad {
+    static constexpr int NV = T * KC / 4 / 256;   // float4 per thread
+    f4 v[NV];
+    static __device__ __forceinline__ void where(int e, int *row, int *k) {
+        if (KMAJOR) { *k = e / (T / 4); *row = 4 * (e % (T / 4)); }
+        else { *row = e / (KC / 4); *k = 4 * (e % (KC / 4)); }
+    }
+    __device__ __forceinline__ void load(const float *p, int ld, int row0, int rows, int k0, int kend) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            int r, k;
+            where((int)threadIdx.x + 256 * i, &r, &k);
+            r += row0;
+            k += k0;
+            f4 t = {0.f, 0.f, 0.f, 0.f};
+            const float *q = KMAJOR ? p + (size_t)k * ld + r : p + (size_t)r * ld + k;
+            if (KMAJOR ? (k < kend) : (r < rows)) {
+                const int left = KMAJOR ? rows - r : kend - k;
+                if (VEC && left >= 4) t = *reinterpret_cast<const f4 *>(q);
+                else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (j < left) t[j] = q[j];
+                }
+            }
+            v[i] = t;
+        }
+    }
+    __device__ __forceinline__ void store(TileLds<T, KMAJOR> &s) const {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            int r, k;
+            where((int)threadIdx.x + 256 * i, &r, &k);
+            *reinterpret_cast<f4 *>(&s.x[KMAJOR ? k * s.LD + r : r * s.LD + k]) = v[i];
+        }
+    }
+};
+
+// AT / BT: the operand is k-major in memory (A(m, k) = A[k lda + m], B(k, n) =
+// B[k ldb + n]); else A[m lda + k], B[n ldb + k].
+template <int T, bool AT, bool BT, bool VEC>
 __global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs g) {
-    __shared__ float As[16][68];
-    __shared__ float Bs[16][68];
+    constexpr int F = T / 32;                      // MFMA tiles per wave and direction
+    __shared__ __align__(16) TileLds<T, AT> As;
+    __shared__ __align__(16) TileLds<T, BT> Bs;
+    __shared__ float red[4][64];
     const int tid = threadIdx.x;
     const int w = tid >> 6, l = tid & 63, lj = l & 15, lg = l >> 4;
-    const int wm = w >> 1, wn = w & 1;
-    const int m0 = blockIdx.y * 64, n0 = blockIdx.x * 64;
+    const int wm = (w >> 1) * (T / 2), wn = (w & 1) * (T / 2);
+    const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
     const int kbeg = blockIdx.z * g.kchunk;
     const int kend = min(g.K, kbeg + g.kchunk);
-    f4 acc[2][2];
+    const bool sums = g.asum && blockIdx.x == 0;
+    f4 acc[F][F];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < F; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < F; ++j) acc[i][j] = f4{0.f, 0.f, 0.f, 0.f};
+    float asum = 0.f;                              // row tid % T, a quarter or an eighth of the k
 
-    for (int k0 = kbeg; k0 < kend; k0 += 16) {
-#pragma unroll
-        for (int e4 = 0; e4 < 4; ++e4) {
-            const int e = tid * 4 + e4;                 // 0 .. 1023
-            int ml, kl;
-            if (g.transA) { ml = e & 63; kl = e >> 6; } else { ml = e >> 4; kl = e & 15; }
-            const int m = m0 + ml, k = k0 + kl;
-            float va = 0.f;
-            if (m < g.M && k < kend)
-                va = g.transA ? g.A[(size_t)k * g.lda + m] : g.A[(size_t)m * g.lda + k];
-            As[kl][ml] = va;
-            int nl, kb;
-            if (g.transB) { nl = e >> 4; kb = e & 15; } else { nl = e & 63; kb = e >> 6; }
-            const int n = n0 + nl, kk = k0 + kb;
-            float vb = 0.f;
-            if (n < g.N && kk < kend)
-                vb = g.transB ? g.B[(size_t)n * g.ldb + kk] : g.B[(size_t)kk * g.ldb + n];
-            Bs[kb][nl] = vb;
-        }
+    TileLoad<T, AT, VEC> la;
+    TileLoad<T, BT, VEC> lb;
+    la.load(g.A, g.lda, m0, g.M, kbeg, kend);
+    lb.load(g.B, g.ldb, n0, g.N, kbeg, kend);
+    for (int k0 = kbeg; k0 < kend; k0 += KC) {
         __syncthreads();
+        la.store(As);
+        lb.store(Bs);
+        __syncthreads();
+        if (k0 + KC < kend) {
+            la.load(g.A, g.lda, m0, g.M, k0 + KC, kend);
+            lb.load(g.B, g.ldb, n0, g.N, k0 + KC, kend);
+        }
 #pragma unroll
-        for (int k4 = 0; k4 < 4; ++k4) {
-            float av[2], bv[2];
+        for (int k4 = 0; k4 < KC / 4; ++k4) {
+            float av[F], bv[F];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) av[i] = As[4 * k4 + lg][wm * 32 + 16 * i + lj];
+            for (int i = 0; i < F; ++i) av[i] = As.at(wm + 16 * i + lj, 4 * k4 + lg);
 #pragma unroll
-            for (int j = 0; j < 2; ++j) bv[j] = Bs[4 * k4 + lg][wn * 32 + 16 * j + lj];
+            for (int j = 0; j < F; ++j) bv[j] = Bs.at(wn + 16 * j + lj, 4 * k4 + lg);
 #pragma unroll
-            for (int i = 0; i < 2; ++i)
+            for (int i = 0; i < F; ++i)
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
+                for (int j = 0; j < F; ++j)
                     acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], bv[j], acc[i][j], 0, 0, 0);
         }
+        if (sums) {
+            constexpr int PART = KC * T / 256;
+#pragma unroll
+            for (int k = 0; k < PART; ++k) asum += As.at(tid % T, (tid / T) * PART + k);
+        }
+    }
+    if (sums) {
+        // the 256 / T parts of a row, in order
         __syncthreads();
+        float *r = &As.x[0];
+        r[tid] = asum;
+        __syncthreads();
+        if (tid < T && m0 + tid < g.M) {
+            float s = 0.f;
+            for (int p = 0; p < 256 / T; ++p) s += r[p * T + tid];
+            if (gridDim.z > 1) g.part[(size_t)gridDim.z * g.M * g.N + (size_t)blockIdx.z * g.M + m0 + tid] = s;
+            else g.asum[m0 + tid] = s;
+        }
     }
 
+    const float sc = g.T ? 2.0f / ((float)g.M * (float)g.N) : 0.f;
+    float sq = 0.f;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < F; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < F; ++j)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int m = m0 + wm * 32 + 16 * i + 4 * lg + r;
-                const int n = n0 + wn * 32 + 16 * j + lj;
+                const int m = m0 + wm + 16 * i + 4 * lg + r;
+                const int n = n0 + wn + 16 * j + lj;
                 if (m >= g.M || n >= g.N) continue;
                 float v = acc[i][j][r];
                 if (gridDim.z > 1) {
@@ -112,57 +187,38 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs g) {
                 if (g.dz) v *= dsilu(g.dz[o]);
                 if (g.Zout) g.Zout[o] = v;
                 if (g.act) v = silu(v);
+                if (g.T) {
+                    const float d = v - g.T[o];
+                    sq += d * d;
+                    v = sc * d;
+                }
                 g.C[o] = v;
             }
-}
-
-// C[m][n] = sum over splits of part[s][m][n], in split order
-__global__ __launch_bounds__(256) void k_sum_splits(const float *part, int splits, int M, int N,
-                                                    float *C, int ldc) {
-    const size_t tot = (size_t)M * N;
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < tot;
-         e += (size_t)gridDim.x * blockDim.x) {
-        float s = 0.f;
-        for (int z = 0; z < splits; ++z) s += part[(size_t)z * tot + e];
-        C[(e / N) * ldc + e % N] = s;
-    }
-}
-
-// db[n] = sum_m dZ[m][n]; 64 columns per block, 4 row phases, fixed order
-__global__ __launch_bounds__(256) void k_colsum(const float *dZ, int M, int N, float *db) {
-    __shared__ float red[4][64];
-    const int c = threadIdx.x & 63, p = threadIdx.x >> 6;
-    const int n = blockIdx.x * 64 + c;
-    float s = 0.f;
-    if (n < N)
-        for (int m = p; m < M; m += 4) s += dZ[(size_t)m * N + n];
-    red[p][c] = s;
-    __syncthreads();
-    if (p == 0 && n < N) db[n] = (red[0][c] + red[1][c]) + (red[2][c] + red[3][c]);
-}
-
-// dY = 2 (Y - T) / count; per-block partial sums of (Y - T)^2
-__global__ __launch_bounds__(256) void k_mse(const float *Y, const float *T, size_t count, float *dY,
-                                             float *part) {
-    __shared__ float red[256];
-    const float sc = 2.0f / (float)count;
-    float s = 0.f;
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < count;
-         e += (size_t)gridDim.x * blockDim.x) {
-        const float d = Y[e] - T[e];
-        dY[e] = sc * d;
-        s += d * d;
-    }
-    red[threadIdx.x] = s;
-    __syncthreads();
-    for (int k = 128; k > 0; k >>= 1) {
-        if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
+    if (g.T) {
+        // fixed order: within the lanes, then the waves
+        for (int off = 32; off > 0; off >>= 1) sq += __shfl_xor(sq, off, 64);
+        if (l == 0) red[w][0] = sq;
         __syncthreads();
+        if (tid == 0)
+            g.lpart[blockIdx.y * gridDim.x + blockIdx.x] = (red[0][0] + red[1][0]) + (red[2][0] + red[3][0]);
     }
-    if (threadIdx.x == 0) part[blockIdx.x] = red[0];
 }
 
-__global__ __launch_bounds__(256) void k_mse_final(const float *part, int n, size_t count, float *loss) {
+// C[m][n] = sum over splits of part[s][m][n], in split order; the same for the
+// column sums db [M] where wanted.  Block 0 also finishes the loss (n_loss block
+// partials, count elements) where wanted.
+struct SumSplitsArgs {
+    const float *part;
+    int splits, M, N;
+    float *C;
+    int ldc;
+    float *db;
+    const float *lpart;
+    int n_loss;
+    float count;
+    float *loss;
+};
+__device__ __forceinline__ void finish_loss(const float *part, int n, float count, float *loss) {
     __shared__ float red[256];
     float s = 0.f;
     for (int i = threadIdx.x; i < n; i += 256) s += part[i];
@@ -172,7 +228,26 @@ __global__ __launch_bounds__(256) void k_mse_final(const float *part, int n, siz
         if ((int)threadIdx.x < k) red[threadIdx.x] += red[threadIdx.x + k];
         __syncthreads();
     }
-    if (threadIdx.x == 0 && loss) *loss = red[0] / (float)count;
+    if (threadIdx.x == 0) *loss = red[0] / count;
+}
+__global__ __launch_bounds__(256) void k_sum_splits(SumSplitsArgs a) {
+    const size_t tot = (size_t)a.M * a.N;
+    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < tot;
+         e += (size_t)gridDim.x * blockDim.x) {
+        float s = 0.f;
+#pragma unroll 8
+        for (int z = 0; z < a.splits; ++z) s += a.part[(size_t)z * tot + e];
+        a.C[(e / a.N) * a.ldc + e % a.N] = s;
+    }
+    for (int m = blockIdx.x * blockDim.x + threadIdx.x; m < a.M; m += gridDim.x * blockDim.x) {
+        float s = 0.f;
+        for (int z = 0; z < a.splits; ++z) s += a.part[a.splits * tot + (size_t)z * a.M + m];
+        a.db[m] = s;
+    }
+    if (a.loss && blockIdx.x == 0) finish_loss(a.lpart, a.n_loss, a.count, a.loss);
+}
+__global__ __launch_bounds__(256) void k_loss(const float *part, int n, float count, float *loss) {
+    finish_loss(part, n, count, loss);
 }
 
 __global__ __launch_bounds__(256) void k_adam(size_t count, float *p, const float *g, float *m, float *v,
@@ -196,8 +271,6 @@ namespace {
 
 constexpr size_t kAl = 256;
 size_t alup(size_t x) { return (x + kAl - 1) & ~(kAl - 1); }
-constexpr int kMseBlocks = 256;
-
 int check_net(int32_t n_layers, const int32_t *dims) {
     if (n_layers < 1 || n_layers > DF_MLP_MAX_LAYERS || !dims) return DF_E_INVAL;
     for (int i = 0; i <= n_layers; ++i)
@@ -242,9 +315,9 @@ MlpWs mlp_ws(int32_t L, const int32_t *d, int32_t batch) {
         o = alup(o + (size_t)batch * mw * sizeof(float));
     }
     w.part = o;
-    o = alup(o + (size_t)splits_for(batch) * mw * mw * sizeof(float));
+    o = alup(o + (size_t)splits_for(batch) * ((size_t)mw * mw + mw) * sizeof(float));
     w.lpart = o;
-    o = alup(o + kMseBlocks * sizeof(float));
+    o = alup(o + (size_t)((batch + 31) / 32) * ((d[L] + 31) / 32) * sizeof(float));
     w.total = o;
     return w;
 }
@@ -253,25 +326,45 @@ template <typename T> T *wsp(void *ws, size_t off) {
     return reinterpret_cast<T *>(static_cast<char *>(ws) + off);
 }
 
+// The tile: 64, unless that gives fewer than four work-groups per CU (of 256), where
+// the loads of too few waves are in flight - then 32.  Batch 4096, width 256, loss
+// and gradients: 162 us with 64 x 64 tiles (256 work-groups), 137 with 32 x 32;
+// batch 1024 forward: 64 work-groups of 64 x 64, 256 of 32 x 32 (28 us).
+int gemm_tile(int M, int N, int splits) {
+    return (long)((M + 63) / 64) * ((N + 63) / 64) * splits >= 1024 ? 64 : 32;
+}
+
+int gemm_splits(int K, int wanted, int *kchunk) {
+    *kchunk = ((K + wanted - 1) / wanted + 15) / 16 * 16;
+    if (*kchunk < 16) *kchunk = 16;
+    const int s = (K + *kchunk - 1) / *kchunk;
+    return s < 1 ? 1 : s;
+}
+
+bool aligned16(const float *p, int ld) { return ((uintptr_t)p & 15) == 0 && ld % 4 == 0; }
+
+template <int T, bool AT, bool BT>
+void launch_gemm_t(const GemmArgs &g, int splits, hipStream_t st) {
+    const dim3 grid((g.N + T - 1) / T, (g.M + T - 1) / T, splits);
+    // 16-byte loads need aligned rows (a layer's weights start wherever the
+    // previous layers' parameters end)
+    if (aligned16(g.A, g.lda) && aligned16(g.B, g.ldb))
+        hipLaunchKernelGGL((k_gemm_f32<T, AT, BT, true>), grid, dim3(256), 0, st, g);
+    else hipLaunchKernelGGL((k_gemm_f32<T, AT, BT, false>), grid, dim3(256), 0, st, g);
+}
+
+template <bool AT, bool BT>
 hipError_t gemm(GemmArgs g, hipStream_t st, int splits = 1) {
-    g.kchunk = ((g.K + splits - 1) / splits + 15) / 16 * 16;
-    if (g.kchunk < 16) g.kchunk = 16;
-    splits = (g.K + g.kchunk - 1) / g.kchunk;
-    if (splits < 1) splits = 1;
-    dim3 grid((g.N + 63) / 64, (g.M + 63) / 64, splits);
-    hipLaunchKernelGGL(k_gemm_f32, grid, dim3(256), 0, st, g);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || splits == 1) return e;
-    const size_t tot = (size_t)g.M * g.N;
-    int blocks = (int)((tot + 255) / 256);
-    if (blocks > 2048) blocks = 2048;
-    hipLaunchKernelGGL(k_sum_splits, dim3(blocks), dim3(256), 0, st, g.part, splits, g.M, g.N, g.C,
-                       g.ldc);
+    splits = gemm_splits(g.K, splits, &g.kchunk);
+    if (gemm_tile(g.M, g.N, splits) == 64) launch_gemm_t<64, AT, BT>(g, splits, st);
+    else launch_gemm_t<32, AT, BT>(g, splits, st);
     return hipGetLastError();
 }
 
+// T (targets) set: the last layer leaves dZ_L = 2 (Y - T) / count in its place and
+// the partial sums of the loss in the workspace
 int forward_impl(int32_t L, const int32_t *d, const float *params, const float *X, int32_t batch,
-                 float *Yout, void *ws, const MlpWs &w, hipStream_t st) {
+                 float *Yout, const float *T, void *ws, const MlpWs &w, hipStream_t st) {
     const float *in = X;
     size_t po = 0;
     for (int l = 0; l < L; ++l) {
@@ -285,16 +378,20 @@ int forward_impl(int32_t L, const int32_t *d, const float *params, const float *
         g.K = d[l];
         g.A = in;
         g.lda = d[l];
-        g.transA = 0;
         g.B = W;
         g.ldb = d[l];
-        g.transB = 1;
         g.ldc = d[l + 1];
         g.bias = b;
-        g.Zout = wsp<float>(ws, w.z[l + 1]);
+        // (pre-activations are kept for the backward pass)
+        g.Zout = Yout || last ? nullptr : wsp<float>(ws, w.z[l + 1]);
         g.act = last ? 0 : 1;
         g.C = (last && Yout) ? Yout : wsp<float>(ws, w.y[l + 1]);
-        if (gemm(g, st) != hipSuccess) return DF_E_HIP;
+        if (last && T) {
+            g.T = T;
+            g.lpart = wsp<float>(ws, w.lpart);
+            g.C = wsp<float>(ws, w.dz[L & 1]);
+        }
+        if (gemm<false, false>(g, st) != hipSuccess) return DF_E_HIP;
         in = g.C;
     }
     return DF_OK;
@@ -327,7 +424,7 @@ int df_mlp_forward(int32_t n_layers, const int32_t *dims, const float *params, c
     if (!params || !X || !Y || batch < 1) return DF_E_INVAL;
     const MlpWs w = mlp_ws(n_layers, dims, batch);
     if (!ws || ((uintptr_t)ws & (kAl - 1)) || ws_bytes < w.total) return DF_E_WORKSPACE;
-    return forward_impl(n_layers, dims, params, X, batch, Y, ws, w, (hipStream_t)stream);
+    return forward_impl(n_layers, dims, params, X, batch, Y, nullptr, ws, w, (hipStream_t)stream);
 }
 
 int df_mlp_loss_grad(int32_t n_layers, const int32_t *dims, const float *params, const float *X,
@@ -341,17 +438,12 @@ int df_mlp_loss_grad(int32_t n_layers, const int32_t *dims, const float *params,
     const MlpWs w = mlp_ws(L, d, batch);
     if (!ws || ((uintptr_t)ws & (kAl - 1)) || ws_bytes < w.total) return DF_E_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
-    rc = forward_impl(L, d, params, X, batch, nullptr, ws, w, st);
+    // forward; dZ_L = 2 (Y - T) / count (last layer has no activation)
+    rc = forward_impl(L, d, params, X, batch, nullptr, T, ws, w, st);
     if (rc != DF_OK) return rc;
-
-    // dZ_L = 2 (Y - T) / count (last layer has no activation)
-    const size_t count = (size_t)batch * d[L];
-    float *dzc = wsp<float>(ws, w.dz[L & 1]);
-    hipLaunchKernelGGL(k_mse, dim3(kMseBlocks), dim3(256), 0, st, wsp<float>(ws, w.y[L]), T, count,
-                       dzc, wsp<float>(ws, w.lpart));
-    hipLaunchKernelGGL(k_mse_final, dim3(1), dim3(256), 0, st, wsp<float>(ws, w.lpart), kMseBlocks,
-                       count, loss);
-    if (hipGetLastError() != hipSuccess) return DF_E_HIP;
+    const int tile = gemm_tile(batch, d[L], 1);
+    const int n_loss = ((batch + tile - 1) / tile) * ((d[L] + tile - 1) / tile);
+    const float count = (float)batch * (float)d[L];
 
     // parameter offsets
     size_t off[DF_MLP_MAX_LAYERS + 1];
@@ -370,16 +462,36 @@ int df_mlp_loss_grad(int32_t n_layers, const int32_t *dims, const float *params,
         g.K = batch;
         g.A = dZ;
         g.lda = d[l + 1];
-        g.transA = 1;
         g.B = Xl;
         g.ldb = d[l];
-        g.transB = 0;
         g.C = dW;
         g.ldc = d[l];
+        g.asum = db;
         g.part = wsp<float>(ws, w.part);
-        if (gemm(g, st, splits_for(batch)) != hipSuccess) return DF_E_HIP;
-        hipLaunchKernelGGL(k_colsum, dim3((d[l + 1] + 63) / 64), dim3(256), 0, st, dZ, batch, d[l + 1],
-                           db);
+        if (gemm<true, true>(g, st, splits_for(batch)) != hipSuccess) return DF_E_HIP;
+        int kchunk;
+        const int splits = gemm_splits(batch, splits_for(batch), &kchunk);
+        float *want_loss = l == L - 1 ? loss : nullptr;
+        if (splits > 1) {
+            SumSplitsArgs r{};
+            r.part = g.part;
+            r.splits = splits;
+            r.M = g.M;
+            r.N = g.N;
+            r.C = dW;
+            r.ldc = d[l];
+            r.db = db;
+            r.lpart = wsp<float>(ws, w.lpart);
+            r.n_loss = n_loss;
+            r.count = count;
+            r.loss = want_loss;
+            const size_t tot = (size_t)g.M * g.N;
+            int blocks = (int)((tot + 255) / 256);
+            if (blocks > 2048) blocks = 2048;
+            hipLaunchKernelGGL(k_sum_splits, dim3(blocks), dim3(256), 0, st, r);
+        } else if (want_loss) {
+            hipLaunchKernelGGL(k_loss, dim3(1), dim3(256), 0, st, wsp<float>(ws, w.lpart), n_loss, count, loss);
+        }
         if (hipGetLastError() != hipSuccess) return DF_E_HIP;
         if (l == 0) break;
         // dZ_l = (dZ_{l+1} W_l) * SiLU'(Z_l)
@@ -389,14 +501,12 @@ int df_mlp_loss_grad(int32_t n_layers, const int32_t *dims, const float *params,
         h.K = d[l + 1];
         h.A = dZ;
         h.lda = d[l + 1];
-        h.transA = 0;
         h.B = params + off[l];
         h.ldb = d[l];
-        h.transB = 0;
         h.C = wsp<float>(ws, w.dz[l & 1]);
         h.ldc = d[l];
         h.dz = wsp<float>(ws, w.z[l]);
-        if (gemm(h, st) != hipSuccess) return DF_E_HIP;
+        if (gemm<false, true>(h, st) != hipSuccess) return DF_E_HIP;
     }
     return DF_OK;
 }

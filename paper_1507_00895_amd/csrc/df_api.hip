@@ -67,7 +67,12 @@ int check_inst(const df_inst_t &p, Shape *s) {
     s->n_irr = 0;
     for (int q = 0; q < (int)N; ++q) s->n_irr += (canonical_q(q, p.D, l) == q);
     s->items_sym = 2 * (p.n_om - s->im0) * s->n_irr;
-    int nch = (512 + p.n_nu - 1) / p.n_nu;
+    // work-groups of the Schwinger-Dyson kernel: two N = 4096 arrays fit a CU (512 in
+    // all; twice as many chunks cost 18 % at 64 x 64, n_nu 128: 88 -> 106 us with the
+    // partial sums), smaller ones run four per CU (32 x 32, n_nu 64, n_om 31: 1024
+    // work-groups 30.6 us, 512 34.6, 2048 38.5)
+    const int target = s->N >= 4096 ? 512 : 1024;
+    int nch = (target + p.n_nu - 1) / p.n_nu;
     if (nch > p.n_om) nch = p.n_om;
     if (nch < 1) nch = 1;
     s->chunk_len = (p.n_om + nch - 1) / nch;
@@ -204,19 +209,6 @@ Grid grid_of(const Shape &s) {
         hipError_t e_ = (x);                       \
         if (e_ != hipSuccess) return DF_E_HIP;     \
     } while (0)
-
-// Once per process: raise the dynamic LDS limit of the FFT kernels.  Runs
-// before any stream work is queued, never inside a graph capture.  If the
-// device refuses, only launches that need more than 64 KiB of LDS fail.
-int ensure_attrs() {
-    static int done = 0;
-    if (!done) {
-        (void)set_fft_lds_limits();
-        (void)hipGetLastError();
-        done = 1;
-    }
-    return DF_OK;
-}
 
 // ---- ladder kernel choice ---------------------------------------------------
 // In order: the variant named by DF_LADDER_KERNEL (any name of the variant
@@ -783,8 +775,6 @@ int df_dual_gf(const df_inst_t *inst, int32_t n_inst, void *ws, size_t ws_bytes,
     if (rc != DF_OK) return rc;
     for (int i = 0; i < n_inst; ++i)
         if (!inst[i].g || !inst[i].delta || !inst[i].eps || !inst[i].gd) return DF_E_INVAL;
-    rc = ensure_attrs();
-    if (rc != DF_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     for (int i = 0; i < n_inst; ++i) {
         rc = stage_dual_gf(inst[i], P.shape[i], inst[i].sigma, inst[i].gd, nullptr, st);
@@ -801,8 +791,6 @@ int df_bubble(const df_inst_t *inst, int32_t n_inst, void *ws, size_t ws_bytes, 
     if (rc != DF_OK) return rc;
     for (int i = 0; i < n_inst; ++i)
         if (!inst[i].gd || !inst[i].chi) return DF_E_INVAL;
-    rc = ensure_attrs();
-    if (rc != DF_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     for (int i = 0; i < n_inst; ++i) {
         const Shape &s = P.shape[i];
@@ -863,8 +851,6 @@ int df_bubble_noalloc(const df_inst_t *inst, int32_t n_inst, df_stream_t stream)
     void *scr = nullptr;
     int rc = scratch_address(&scr);
     if (rc != DF_OK) return rc;
-    rc = ensure_attrs();
-    if (rc != DF_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     double *gr = static_cast<double *>(scr);
     // instances in turn on one stream: each overwrites the whole G~(r) it reads
@@ -890,8 +876,6 @@ int df_ladder_solve(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts
     if (rc != DF_OK) return rc;
     for (int i = 0; i < n_inst; ++i)
         if (!inst[i].gamma_uu || !inst[i].gamma_ud || !inst[i].chi || !inst[i].w) return DF_E_INVAL;
-    rc = ensure_attrs();
-    if (rc != DF_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     const int prec = opts ? opts->prec : DF_FP64;
     const bool sym = opts && opts->symmetry;
@@ -989,8 +973,6 @@ int df_sigma(const df_inst_t *inst, int32_t n_inst, void *ws, size_t ws_bytes, d
     if (rc != DF_OK) return rc;
     for (int i = 0; i < n_inst; ++i)
         if (!inst[i].w || !inst[i].gd || !inst[i].sigma_calc) return DF_E_INVAL;
-    rc = ensure_attrs();
-    if (rc != DF_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     for (int i = 0; i < n_inst; ++i) {
         const Shape &s = P.shape[i];
@@ -1025,8 +1007,6 @@ int df_iterate(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts, int
     std::vector<AccState> acc(slots > 0 ? n_inst : 0);
     for (auto &S : acc) S.gram.assign((size_t)slots * slots, 0.0);
     std::vector<double> hdots((size_t)n_inst * kAccMaxSlots);
-    rc = ensure_attrs();
-    if (rc != DF_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
     const bool graph = opts->use_graph != 0 && st != nullptr;
     // iterations per captured graph: the host step of Anderson acceleration
@@ -1250,8 +1230,6 @@ int df_autotune(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts, vo
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cap) != hipSuccess) return DF_E_HIP;
     if (cap != hipStreamCaptureStatusNone) return DF_E_INVAL;   // timing needs synchronisation
-    rc = ensure_attrs();
-    if (rc != DF_OK) return rc;
     std::vector<int> precs;
     if (opts && opts->prec == DF_ADAPTIVE) precs = {DF_FP32, DF_FP64};
     else precs = {opts ? opts->prec : DF_FP64};
@@ -1389,8 +1367,6 @@ int df_lattice(const df_inst_t *inst, double mu, double *sigma_lat, double *g_la
     if (want_chi && (!p.gamma_uu || !p.gamma_ud)) return DF_E_INVAL;
     const LatticeLayout L = lattice_layout_of(s);
     if (!ws || (((uintptr_t)ws) & (kAlign - 1)) || ws_bytes < L.total) return DF_E_WORKSPACE;
-    rc = ensure_attrs();
-    if (rc != DF_OK) return rc;
     hipStream_t st = (hipStream_t)stream;
 
     LatticeFieldArgs f{};

@@ -7,8 +7,10 @@
 //   reduction over Om chunks, linear mixing, Frobenius norms (deterministic order)
 //   eq. (spin_symm)             k_gamma_prep   (gamma^{d,m} and gamma_ij gamma_ji)
 //
-// Every FFT works on one N-point array (N = nk^D <= 4096) resident in LDS;
-// the flat index has one bit field per axis (see df_device.hpp).
+// Every FFT works on one N-point array (N = nk^D <= 4096), one work-group per
+// array, in register passes with LDS between them (df_fft.hpp); the kernels are
+// built per grid shape (D, nk).
+#include "df_fft.hpp"
 #include "df_internal.hpp"
 
 namespace df {
@@ -19,44 +21,47 @@ namespace df {
 // the inverse FFT gr[n][r] = (1/N) sum_k e^{ikr} G~(k) (if gr_out).
 // With from_gd set, G~ is read from gd instead of being computed.
 // ------------------------------------------------------------------------
-template <int NTH>
-__global__ __launch_bounds__(NTH) void k_dual_gf(DualGfArgs a) {
-    extern __shared__ cd lds[];
-    cd *X = lds;
-    cd *tw = lds + a.grid.N;
-    const Grid g = a.grid;
+template <typename P>
+__global__ __launch_bounds__(P::T) void k_dual_gf(DualGfArgs a) {
+    __shared__ cd X[P::LDS_N];
+    __shared__ cd tw[P::nk];
     const int n = blockIdx.x;
-    make_twiddles(tw, g);
     cd ginv = {0, 0}, gn = {0, 0}, dn = {0, 0};
     if (!a.from_gd) {
         gn = ld(a.g, n);
         dn = ld(a.delta, n);
         ginv = recip(gn);
     }
-    for (int k = threadIdx.x; k < g.N; k += blockDim.x) {
-        cd G;
-        if (a.from_gd) {
-            G = ld(a.gd_in, (size_t)n * g.N + k);
-        } else {
-            const cd den = {ginv.re + dn.re - a.eps[k], ginv.im + dn.im};
-            const cd G0 = recip(den) - gn;
-            if (a.sigma) {
-                const cd S = ld(a.sigma, (size_t)n * g.N + k);
-                const cd one_m = {1.0, 0.0};
-                G = cdiv(G0, fms(one_m, G0, S));
-            } else {
-                G = G0;
-            }
-            if (a.gd_out) st(a.gd_out, (size_t)n * g.N + k, G);
-        }
-        X[bitrev_fields(k, g)] = G;
+    auto value = [&](int k) __attribute__((always_inline)) {
+        const size_t e = (size_t)n * P::N + k;
+        if (a.from_gd) return ld(a.gd_in, e);
+        const cd den = {ginv.re + dn.re - a.eps[k], ginv.im + dn.im};
+        const cd G0 = recip(den) - gn;
+        cd G = G0;
+        if (a.sigma) G = cdiv(G0, fms(cd{1.0, 0.0}, G0, ld(a.sigma, e)));
+        if (a.gd_out) st(a.gd_out, e, G);
+        return G;
+    };
+    if (!a.gr_out) {
+        for (int k = threadIdx.x; k < P::N; k += P::T) (void)value(k);
+        return;
     }
-    if (!a.gr_out) return;
-    __syncthreads();
-    fft_inplace<true>(X, tw, g);
-    const double invN = 1.0 / (double)g.N;
-    for (int r = threadIdx.x; r < g.N; r += blockDim.x)
-        st(a.gr_out, (size_t)n * g.N + r, scale(X[r], invN));
+    fft_twiddles<P>(tw);
+    constexpr double invN = 1.0 / (double)P::N;
+    auto store = [&](int, int, int r, int, cd x) __attribute__((always_inline)) {
+        st(a.gr_out, (size_t)n * P::N + r, scale(x, invN));
+    };
+    if constexpr (P::PASSES == 1) {
+        fft_run<P, true>(X, tw, [&](int k, int) __attribute__((always_inline)) { return value(k); }, store);
+    } else {
+        // G~ by every thread into LDS first: the divisions, one element at a time
+        // and thread, instead of a line of them in each of the first pass's threads
+        for (int k = threadIdx.x; k < P::N; k += P::T) X[P::pad(k)] = value(k);
+        __syncthreads();
+        fft_first_lds<P, true>(X, tw);
+        fft_middle<P, 1, true>(X, tw);
+        fft_last<P, true>(X, store);
+    }
 }
 
 // Clear the counters of the ladder launches that follow on the stream (one
@@ -69,97 +74,83 @@ __device__ __forceinline__ void zero_ints(int *p, int n) {
 // chi_{m,n}(q) = -T FFT_r[ gr_n(-r) gr_{n+m}(r) ](q); zero when n+m leaves
 // the window.  One block per (n, m).
 // ------------------------------------------------------------------------
-template <int NTH>
-__global__ __launch_bounds__(NTH) void k_bubble(BubbleArgs a) {
-    extern __shared__ cd lds[];
-    cd *X = lds;
-    cd *tw = lds + a.grid.N;
-    const Grid g = a.grid;
+template <typename P>
+__global__ __launch_bounds__(P::T) void k_bubble(BubbleArgs a) {
+    __shared__ cd X[P::LDS_N];
+    __shared__ cd tw[P::nk];
     const int n = blockIdx.x, im = blockIdx.y;
     const int m = im - (a.n_om - 1) / 2;
     const int n2 = n + m;
     if (n == 0 && im == 0) zero_ints(a.zero, a.n_zero);
-    double *out = a.chi + 2 * ((size_t)im * a.n_nu + n) * g.N;
+    double *out = a.chi + 2 * ((size_t)im * a.n_nu + n) * P::N;
     if (n2 < 0 || n2 >= a.n_nu) {
-        for (int q = threadIdx.x; q < g.N; q += blockDim.x) st(out, q, cd{0.0, 0.0});
+        for (int q = threadIdx.x; q < P::N; q += P::T) st(out, q, cd{0.0, 0.0});
         return;
     }
-    make_twiddles(tw, g);
-    const double *ga = a.gr + 2 * (size_t)n * g.N;
-    const double *gb = a.gr + 2 * (size_t)n2 * g.N;
-    for (int r = threadIdx.x; r < g.N; r += blockDim.x) {
-        const cd x = ld(ga, reflect_fields(r, g)) * ld(gb, r);
-        X[bitrev_fields(r, g)] = x;
-    }
-    __syncthreads();
-    fft_inplace<false>(X, tw, g);
+    fft_twiddles<P>(tw);
+    if constexpr (P::S == 2) __syncthreads();
+    const double *ga = a.gr + 2 * (size_t)n * P::N;
+    const double *gb = a.gr + 2 * (size_t)n2 * P::N;
     const double mT = -1.0 / a.beta;
-    for (int q = threadIdx.x; q < g.N; q += blockDim.x) st(out, q, scale(X[q], mT));
+    fft_run<P, false>(X, tw,
+                      [&](int r, int rr) __attribute__((always_inline)) { return ld(ga, rr) * ld(gb, r); },
+                      [&](int, int, int q, int, cd x) __attribute__((always_inline)) { st(out, q, scale(x, mT)); });
 }
 
 // ------------------------------------------------------------------------
 // Partial dual self-energy over one chunk of bosonic frequencies:
 //   part[chunk][n][k] = (T/2) FFT_r[ sum_{m in chunk} v_{m,n}(-r) gr_{n+m}(r) ](k),
 //   v_{m,n} = IFFT_q[ 3 W^m_{m,n} + W^d_{m,n} ].
-// One block per (n, chunk); the accumulator lives in registers.
+// One block per (n, chunk).  The accumulator B(r) = sum_m v(r) gr(-r) lives in
+// registers where the inverse FFT's last pass leaves v, and FFT_r[B(-r)](k) is the
+// transform of B with the other sign, whose first pass takes it from there.
 // ------------------------------------------------------------------------
-// (1024 threads: capped at 64 registers, so that two work-groups fit a CU)
-template <int NTH>
-__global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(NTH == 1024 ? 8 : 1)))
-void k_sigma_part(SigmaArgs a) {
-    constexpr int SIGMA_MAX_PER_THREAD = 4096 / NTH;   // N <= 4096
-    extern __shared__ cd lds[];
-    cd *X = lds;
-    cd *tw = lds + a.grid.N;
-    const Grid g = a.grid;
+template <typename P, typename Q>
+__global__ __launch_bounds__(P::T) void k_sigma_part(SigmaArgs a) {
+    constexpr int LAST = P::PASSES - 1, V = P::lines_per_thread(LAST), R = 1 << P::bits(LAST);
+    __shared__ cd X[P::LDS_N > Q::LDS_N ? P::LDS_N : Q::LDS_N];
+    __shared__ cd tw[P::nk];
     const int n = blockIdx.x, chunk = blockIdx.y;
-    const int nth = blockDim.x;
-    const int per = g.N / nth;                   // N is a power of two: N % nth == 0 or N < nth
-    const int cnt = per > 0 ? per : (threadIdx.x < g.N ? 1 : 0);
-    make_twiddles(tw, g);
-    cd acc[SIGMA_MAX_PER_THREAD];
+    fft_twiddles<P>(tw);
+    cd acc[V][R];
 #pragma unroll
-    for (int i = 0; i < SIGMA_MAX_PER_THREAD; ++i) acc[i] = {0.0, 0.0};
-    const double invN = 1.0 / (double)g.N;
+    for (int v = 0; v < V; ++v)
+#pragma unroll
+        for (int i = 0; i < R; ++i) acc[v][i] = {0.0, 0.0};
     const int h = (a.n_om - 1) / 2;
     const int m_lo = chunk * a.chunk_len;
     const int m_hi = min(a.n_om, m_lo + a.chunk_len);
-    const size_t plane = (size_t)a.n_om * a.n_nu * g.N;   // one channel of W
+    const size_t plane = (size_t)a.n_om * a.n_nu * P::N;   // one channel of W
     for (int im = m_lo; im < m_hi; ++im) {
         const int n2 = n + im - h;
         if (n2 < 0 || n2 >= a.n_nu) continue;
-        const size_t off = ((size_t)im * a.n_nu + n) * g.N;
+        const double *wd = a.w + 2 * ((size_t)im * a.n_nu + n) * P::N, *wm = wd + 2 * plane;
+        const double *gb = a.gr + 2 * (size_t)n2 * P::N;
         __syncthreads();
-        for (int q = threadIdx.x; q < g.N; q += nth) {
-            const cd wd = ld(a.w, off + q);
-            const cd wm = ld(a.w, plane + off + q);
-            X[bitrev_fields(q, g)] = {3.0 * wm.re + wd.re, 3.0 * wm.im + wd.im};
+        fft_run<P, true>(X, tw,
+                         [&](int q, int) __attribute__((always_inline)) {
+                             const cd d = ld(wd, q), m = ld(wm, q);
+                             return cd{fma(3.0, m.re, d.re), fma(3.0, m.im, d.im)};
+                         },
+                         [&](int v, int i, int, int rr, cd x) __attribute__((always_inline)) {
+                             acc[v][i] = fma_c(acc[v][i], x, ld(gb, rr));
+                         });
+    }
+    const double sc = 0.5 / (a.beta * (double)P::N);      // T/2 and the inverse FFT's 1/N
+    double *out = a.part + 2 * ((size_t)chunk * a.n_nu + n) * P::N;
+    auto store = [&](int, int, int k, int, cd x) __attribute__((always_inline)) { st(out, k, scale(x, sc)); };
+    if constexpr (P::PASSES == 1) {
+        if (threadIdx.x == 0) {
+            fft_reg<R, true>(acc[0]);
+#pragma unroll
+            for (int i = 0; i < R; ++i) store(0, i, i, 0, acc[0][i]);
         }
+    } else {
         __syncthreads();
-        fft_inplace<true>(X, tw, g);
-        const double *gb = a.gr + 2 * (size_t)n2 * g.N;
-#pragma unroll
-        for (int i = 0; i < SIGMA_MAX_PER_THREAD; ++i) {
-            if (i < cnt) {
-                const int r = threadIdx.x + i * nth;
-                const cd v = scale(X[reflect_fields(r, g)], invN);
-                acc[i] = fma_c(acc[i], v, ld(gb, r));
-            }
-        }
+        fft_first_reg<Q, true>(X, tw, acc);
+        fft_middle<Q, 1, true>(X, tw);
+        fft_last<Q, true>(X, store);
     }
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < SIGMA_MAX_PER_THREAD; ++i) {
-        if (i < cnt) {
-            const int r = threadIdx.x + i * nth;
-            X[bitrev_fields(r, g)] = acc[i];
-        }
-    }
-    __syncthreads();
-    fft_inplace<false>(X, tw, g);
-    const double hT = 0.5 / a.beta;
-    double *out = a.part + 2 * ((size_t)chunk * a.n_nu + n) * g.N;
-    for (int k = threadIdx.x; k < g.N; k += nth) st(out, k, scale(X[k], hT));
 }
 
 // ------------------------------------------------------------------------
@@ -312,50 +303,47 @@ __global__ void k_zero_ints(int *p, int n) {
 // ------------------------------------------------------------------------
 // launchers
 // ------------------------------------------------------------------------
-static size_t fft_lds_bytes(const Grid &g) { return (size_t)(g.N + g.nk) * sizeof(cd); }
+// the build for the grid's shape (nk^D <= 4096)
+#define DF_FFT_SHAPES(F)                                                          \
+    F(1, 2) F(1, 3) F(1, 4) F(1, 5) F(1, 6) F(2, 2) F(2, 3) F(2, 4) F(2, 5) F(2, 6) \
+    F(3, 2) F(3, 3) F(3, 4) F(4, 2) F(4, 3)
+#define DF_FFT_SWITCH(F)                       \
+    switch (a.grid.D * 16 + a.grid.lognk) {    \
+        DF_FFT_SHAPES(F)                       \
+        default: return hipErrorInvalidValue;  \
+    }
 
-// Threads per FFT work-group.  The FFT kernels keep N + nk complex doubles in
-// LDS, 66.5 KiB at N = 4096, so two work-groups fit a CU: 1024 threads each
-// then give 32 waves per CU (256 threads gave 8, and the LDS passes waited
-// on their latency).  Smaller grids keep 256 threads and more work-groups.
-static int fft_threads(const Grid &g) { return g.N >= 4096 ? 1024 : 256; }
-
-// The FFT kernels keep N + nk complex doubles in LDS: up to 66.5 KiB at
-// N = 4096, above the default 64 KiB limit of a launch.
-hipError_t set_fft_lds_limits() {
-    const int bytes = (4096 + 64) * (int)sizeof(cd);
-    const void *kernels[] = {(const void *)k_dual_gf<256>, (const void *)k_dual_gf<1024>,
-                             (const void *)k_bubble<256>, (const void *)k_bubble<1024>,
-                             (const void *)k_sigma_part<256>, (const void *)k_sigma_part<1024>};
-    hipError_t e = hipSuccess;
-    for (const void *k : kernels)
-        if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
-    return e;
-}
+// (few work-groups, one per frequency, of an element's divisions each: more threads)
+template <int D, int LK> using DualFft = Fft<D, LK, false, ((1 << (D * LK)) < 1024 ? ((1 << (D * LK)) < 64 ? 64 : (1 << (D * LK))) : ((1 << (D * LK)) >= 4096 ? 1024 : 512))>;
 
 hipError_t launch_dual_gf(const DualGfArgs &a, hipStream_t s) {
-    if (fft_threads(a.grid) == 1024)
-        hipLaunchKernelGGL(k_dual_gf<1024>, dim3(a.n_nu), dim3(1024), fft_lds_bytes(a.grid), s, a);
-    else
-        hipLaunchKernelGGL(k_dual_gf<256>, dim3(a.n_nu), dim3(256), fft_lds_bytes(a.grid), s, a);
+#define DF_CASE(D, LK)                                                                               \
+    case D * 16 + LK:                                                                                \
+        hipLaunchKernelGGL((k_dual_gf<DualFft<D, LK>>), dim3(a.n_nu), dim3(DualFft<D, LK>::T), 0, s, a); \
+        break;
+    DF_FFT_SWITCH(DF_CASE)
+#undef DF_CASE
     return hipGetLastError();
 }
 
 hipError_t launch_bubble(const BubbleArgs &a, hipStream_t s) {
-    if (fft_threads(a.grid) == 1024)
-        hipLaunchKernelGGL(k_bubble<1024>, dim3(a.n_nu, a.n_om), dim3(1024), fft_lds_bytes(a.grid), s, a);
-    else
-        hipLaunchKernelGGL(k_bubble<256>, dim3(a.n_nu, a.n_om), dim3(256), fft_lds_bytes(a.grid), s, a);
+#define DF_CASE(D, LK)                                                                                      \
+    case D * 16 + LK:                                                                                       \
+        hipLaunchKernelGGL((k_bubble<Fft<D, LK>>), dim3(a.n_nu, a.n_om), dim3(Fft<D, LK>::T), 0, s, a); \
+        break;
+    DF_FFT_SWITCH(DF_CASE)
+#undef DF_CASE
     return hipGetLastError();
 }
 
 hipError_t launch_sigma_part(const SigmaArgs &a, hipStream_t s) {
-    if (fft_threads(a.grid) == 1024)
-        hipLaunchKernelGGL(k_sigma_part<1024>, dim3(a.n_nu, a.n_chunks), dim3(1024),
-                           fft_lds_bytes(a.grid), s, a);
-    else
-        hipLaunchKernelGGL(k_sigma_part<256>, dim3(a.n_nu, a.n_chunks), dim3(256),
-                           fft_lds_bytes(a.grid), s, a);
+#define DF_CASE(D, LK)                                                                                  \
+    case D * 16 + LK:                                                                                   \
+        hipLaunchKernelGGL((k_sigma_part<Fft<D, LK>, Fft<D, LK, true>>), dim3(a.n_nu, a.n_chunks),  \
+                           dim3(Fft<D, LK>::T), 0, s, a);                                             \
+        break;
+    DF_FFT_SWITCH(DF_CASE)
+#undef DF_CASE
     return hipGetLastError();
 }
 

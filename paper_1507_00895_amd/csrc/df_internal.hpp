@@ -287,7 +287,6 @@ hipError_t launch_norm_final(const double *part, int n_part, double *out, hipStr
 hipError_t launch_acc_record(const AccRecordArgs &a, int blocks, hipStream_t s);
 hipError_t launch_acc_combine(const AccCombineArgs &a, int blocks, hipStream_t s);
 hipError_t launch_gamma_prep(const GammaPrepArgs &a, hipStream_t s);
-hipError_t set_fft_lds_limits();
 
 // padded ladder size for n_nu, 0 if unsupported
 int ladder_padded_size(int n_nu);

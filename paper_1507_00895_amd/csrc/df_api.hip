@@ -12,6 +12,7 @@
 #include "../../include/df.h"
 #include "../../include/df_lattice.h"
 #include "df_internal.hpp"
+#include "df_lattice_ladder.hpp"
 #include "df_tune.hpp"
 
 using namespace df;
@@ -705,33 +706,39 @@ bool acc_weights(const AccState &S, int slots, int newest, double *coef) {
 }
 
 // ---- lattice observables (df_lattice.h) ---------------------------------------
-constexpr int kLatticeChunk = 512;   // (channel, q) items per elimination launch
-
 struct LatticeLayout {
-    size_t gd, fg, gl, gr, chi0, L, bub, lad, work;
-    int chunk;
+    size_t fields, gr, bub;           // [3][n_nu][N] each: G~, frak G, G_lat; their chi~, L, bubble
+    size_t gdm, pdm, gtr, gp32, gtr32, gsym, gabs, symp;   // vertex at Omega = 0
+    size_t cert, w, queue, near, ints, lad;
     size_t total;
 };
 
 LatticeLayout lattice_layout_of(const Shape &s) {
     LatticeLayout L;
-    const size_t fld = (size_t)s.n_nu * s.N * 16;
+    const size_t fld = (size_t)s.n_nu * s.N * 16, gam = 2 * (size_t)s.n_nu * s.n_nu * 16;
     size_t o = 0;
     auto take = [&](size_t bytes) {
         size_t at = o;
         o = align_up(o + bytes);
         return at;
     };
-    L.gd = take(fld);
-    L.fg = take(fld);
-    L.gl = take(fld);
-    L.gr = take(fld);
-    L.chi0 = take(fld);
-    L.L = take(fld);
-    L.bub = take(fld);
+    L.fields = take(3 * fld);
+    L.gr = take(3 * fld);
+    L.bub = take(3 * fld);
+    L.gdm = take(gam);
+    L.pdm = take(gam);
+    L.gtr = take(gam);
+    L.gp32 = take(gam);
+    L.gtr32 = take(gam / 2);
+    L.gsym = take(gam);
+    L.gabs = take(gam / 4);
+    L.symp = take((size_t)kPrepChunks * 4 * sizeof(float));
+    L.cert = take(2 * (size_t)s.N);
+    L.w = take(2 * fld);
+    L.queue = take(2 * (size_t)s.N * sizeof(int));
+    L.near = take(2 * (size_t)s.N * sizeof(int));
+    L.ints = take(2 * sizeof(int));
     L.lad = take(2 * (size_t)s.N * 16);
-    L.chunk = 2 * s.N < kLatticeChunk ? 2 * s.N : kLatticeChunk;
-    L.work = take((size_t)L.chunk * s.n_nu * (s.n_nu + 1) * 16);
     L.total = o;
     return L;
 }
@@ -1380,45 +1387,70 @@ int df_lattice(const df_inst_t *inst, double mu, double *sigma_lat, double *g_la
     f.sigma = p.sigma;
     f.sigma_lat = sigma_lat;
     f.g_lat = g_lat;
-    f.gl = at<double>(ws, L.gl);
-    f.gd = at<double>(ws, L.gd);
-    f.fg = at<double>(ws, L.fg);
+    // the three fields next to each other: one transform and one bubble launch
+    const size_t fld = 2 * (size_t)s.n_nu * s.N;         // doubles of one field
+    f.gd = at<double>(ws, L.fields);
+    f.fg = f.gd + fld;
+    f.gl = f.gd + 2 * fld;
     HIPCHK(launch_lattice_fields(f, st));
     if (!want_chi) return DF_OK;
 
     // chi~, L and the per-nu lattice bubble at Omega = 0: the iteration's FFT bubble
     // with a one-frequency bosonic window
-    Shape s1 = s;
-    s1.n_om = 1;
-    double *gr = at<double>(ws, L.gr);
-    rc = stage_transform_gd(s1, f.gd, gr, st);
-    if (rc == DF_OK) rc = stage_bubble(p, s1, gr, at<double>(ws, L.chi0), nullptr, 0, st);
-    if (rc == DF_OK) rc = stage_transform_gd(s1, f.fg, gr, st);
-    if (rc == DF_OK) rc = stage_bubble(p, s1, gr, at<double>(ws, L.L), nullptr, 0, st);
-    if (rc == DF_OK) rc = stage_transform_gd(s1, f.gl, gr, st);
-    if (rc == DF_OK) rc = stage_bubble(p, s1, gr, at<double>(ws, L.bub), nullptr, 0, st);
+    Shape s3 = s;
+    s3.n_om = 1;
+    s3.n_nu = 3 * s.n_nu;
+    rc = stage_transform_gd(s3, f.gd, at<double>(ws, L.gr), st);
+    if (rc == DF_OK) rc = stage_bubble(p, s3, at<double>(ws, L.gr), at<double>(ws, L.bub), nullptr, 0, st);
     if (rc != DF_OK) return rc;
+    const double *chi0 = at<double>(ws, L.bub), *Lq = chi0 + fld, *bub = chi0 + 2 * fld;
 
-    LatticeChiArgs c{};
+    // the ladder term with the ladder kernels on the vertex at Omega = 0
+    GammaPrepArgs g{};
+    g.n_nu = s.n_nu;
+    g.n_om = 1;
+    const size_t v0 = 2 * (size_t)((s.n_om - 1) / 2) * s.n_nu * s.n_nu;
+    g.guu = p.gamma_uu + v0;
+    g.gud = p.gamma_ud + v0;
+    g.gdm = at<double>(ws, L.gdm);
+    g.pdm = at<double>(ws, L.pdm);
+    g.gtr = at<double>(ws, L.gtr);
+    g.gp32 = at<float>(ws, L.gp32);
+    g.gtr32 = at<float>(ws, L.gtr32);
+    g.gsym = at<double>(ws, L.gsym);
+    g.gabs = at<float>(ws, L.gabs);
+    g.symp = at<float>(ws, L.symp);
+    g.zero = at<int>(ws, L.ints);
+    g.n_zero = 2;
+    HIPCHK(launch_gamma_prep(g, st));
+    LadderArgs c{};
+    c.gdm = g.gdm;
+    c.pdm = g.pdm;
+    c.gtr = g.gtr;
+    c.gsym = g.gsym;
+    c.gabs = g.gabs;
+    c.symp = g.symp;
+    c.cert = at<uint8_t>(ws, L.cert);
+    c.chi = chi0;
+    c.w = at<double>(ws, L.w);
     c.n_nu = s.n_nu;
+    c.n_om = 1;
     c.N = s.N;
-    c.i0 = (s.n_om - 1) / 2;
-    c.guu = p.gamma_uu;
-    c.gud = p.gamma_ud;
-    c.L = at<double>(ws, L.L);
-    c.chi0 = at<double>(ws, L.chi0);
-    c.work = at<double>(ws, L.work);
-    c.lad = at<double>(ws, L.lad);
-    for (int i0 = 0; i0 < 2 * s.N; i0 += L.chunk) {
-        c.item0 = i0;
-        const int items = (2 * s.N - i0) < L.chunk ? (2 * s.N - i0) : L.chunk;
-        HIPCHK(launch_lattice_chi_ladder(c, items, st));
-    }
+    c.n_items = 2 * s.N;
+    c.n_sblk = ladder_screen_blocks(s.n_nu, 1, s.N);
+    c.queue = at<int>(ws, L.queue);
+    c.queue_count = g.zero;
+    c.near_queue = at<int>(ws, L.near);
+    c.near_count = g.zero + 1;
+    double *lad = at<double>(ws, L.lad);
+    HIPCHK(launch_lattice_screen(c, Lq, st));
+    HIPCHK(launch_lattice_sym(c, Lq, lad, st));
+    HIPCHK(launch_lattice_rest(c, Lq, lad, c.n_items < kQueueBlocks ? c.n_items : kQueueBlocks, st));
     LatticeSumArgs m{};
     m.n_nu = s.n_nu;
     m.N = s.N;
-    m.bub = at<double>(ws, L.bub);
-    m.lad = c.lad;
+    m.bub = bub;
+    m.lad = lad;
     m.chi_ch = chi_ch;
     m.chi_sp = chi_sp;
     HIPCHK(launch_lattice_chi_sum(m, st));

@@ -264,15 +264,6 @@ struct LatticeFieldArgs {
     double *gl, *gd, *fg;                    // [n_nu][N] G_lat, G~, frak G
 };
 
-struct LatticeChiArgs {
-    int n_nu, N, i0;                         // i0: index of Omega = 0 in the vertex arrays
-    int item0;                               // first item (c * N + q) of this launch
-    const double *guu, *gud;                 // [n_om][n_nu][n_nu]
-    const double *L, *chi0;                  // [n_nu][N]
-    double *work;                            // [items][n_nu][n_nu + 1] complex
-    double *lad;                             // [2][N]
-};
-
 struct LatticeSumArgs {
     int n_nu, N;
     const double *bub, *lad;                 // [n_nu][N], [2][N]
@@ -319,7 +310,6 @@ hipError_t launch_zero_ints(int *p, int n, hipStream_t s);
 hipError_t launch_sym_tables(const SymTableArgs &a, hipStream_t s);
 hipError_t launch_sym_expand(const SymExpandArgs &a, hipStream_t s);
 hipError_t launch_lattice_fields(const LatticeFieldArgs &a, hipStream_t s);
-hipError_t launch_lattice_chi_ladder(const LatticeChiArgs &a, int items, hipStream_t s);
 hipError_t launch_lattice_chi_sum(const LatticeSumArgs &a, hipStream_t s);
 
 }  // namespace df

@@ -14,6 +14,7 @@
 // over a wave, they cost about 1500 vector instructions per item (an eighth of
 // the n_nu = 64 elimination), here about 40 matrix instructions.
 #include "df_gj_core.hpp"
+#include "df_lattice_ladder.hpp"
 
 namespace df {
 
@@ -38,12 +39,13 @@ __device__ __forceinline__ bool vertex_symmetric(const float *part, int n, int c
     return prep_symmetric(m, d);
 }
 
-template <int NT>
-__global__ __launch_bounds__(256) void k_ladder_screen(LadderArgs a0) {
+// LAT: the product is gamma L instead (lattice observables' ladder term, n_om = 1).
+template <int NT, bool LAT>
+__device__ __forceinline__ void screen_body(const LadderArgs &a0, const double *L) {
     constexpr int NP = 16 * NT;
     typedef MT<double>::v4 d4;
     typedef MT<float>::v4 f4;
-    __shared__ cd X[NP][16];          // chi[k][q]
+    __shared__ cd X[NP][16];          // chi[k][q] (LAT: L[k][q])
     __shared__ float xa[NP][16];      // |chi|
     __shared__ float vv[2][NP][16];   // vectors of the power steps
     __shared__ float red[2][4][16];   // per wave and momentum: its largest quotient
@@ -92,7 +94,12 @@ __global__ __launch_bounds__(256) void k_ladder_screen(LadderArgs a0) {
     for (int k = tid >> 4; k < NP; k += 16) {     // (tid & 15 == lj)
         const cd x = ld(a.chi, ((size_t)im * n + (k < nm1 ? k : nm1)) * N + q);
         const cd v = k < n ? x : cd{0.0, 0.0};
-        X[k][lj] = v;
+        if constexpr (LAT) {
+            const cd y = ld(L, (size_t)(k < nm1 ? k : nm1) * N + q);
+            X[k][lj] = k < n ? y : cd{0.0, 0.0};
+        } else {
+            X[k][lj] = v;
+        }
         // (a modulus below the FP32 range counts as its smallest normal value:
         // the bound stays an upper bound)
         float m = (float)sqrt(fma(v.re, v.re, v.im * v.im));
@@ -101,7 +108,8 @@ __global__ __launch_bounds__(256) void k_ladder_screen(LadderArgs a0) {
     }
 
     const int cm = c * a.n_om + im;
-    const double *pm = a.pdm + 2 * (size_t)cm * n * n;
+    // (the matrix of the product by rows k: P is symmetric, gamma transposed)
+    const double *pm = (LAT ? a.gtr : a.pdm) + 2 * (size_t)cm * n * n;
     const float *ga = a.gabs + (size_t)cm * n * n;
     // this wave's rows of |gamma| (A operand of every k-slice)
     constexpr int NI = (NT + 3) / 4;
@@ -119,7 +127,7 @@ __global__ __launch_bounds__(256) void k_ladder_screen(LadderArgs a0) {
     }
     __syncthreads();
 
-    // ---- t: P is symmetric, read by rows k
+    // ---- t
 #pragma unroll
     for (int y = 0; y < NI; ++y) {
         const int I = w + 4 * y;
@@ -207,6 +215,13 @@ __global__ __launch_bounds__(256) void k_ladder_screen(LadderArgs a0) {
     }
 }
 
+template <int NT> __global__ __launch_bounds__(256) void k_ladder_screen(LadderArgs a0) {
+    screen_body<NT, false>(a0, nullptr);
+}
+template <int NT> __global__ __launch_bounds__(256) void k_lattice_screen(LadderArgs a0, const double *L) {
+    screen_body<NT, true>(a0, L);
+}
+
 // work-groups of one instance's screening: channels x bosonic indices x blocks of
 // 16 momenta
 int ladder_screen_blocks(int n_nu, int n_m, int n_q) {
@@ -221,6 +236,18 @@ hipError_t launch_ladder_screen(const LadderArgs &a, hipStream_t s) {
     case NT: hipLaunchKernelGGL(k_ladder_screen<NT>, dim3(a.n_sblk), dim3(256), 0, s, a); break;
         DF_SCREEN(1) DF_SCREEN(2) DF_SCREEN(3) DF_SCREEN(4)
         DF_SCREEN(5) DF_SCREEN(6) DF_SCREEN(7) DF_SCREEN(8)
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
+hipError_t launch_lattice_screen(const LadderArgs &a, const double *L, hipStream_t s) {
+    if (a.n_sblk <= 0 || !a.queue || !a.near_queue) return hipErrorInvalidValue;
+    switch ((a.n_nu + 15) / 16) {
+#define DF_SCREEN_L(NT) \
+    case NT: hipLaunchKernelGGL(k_lattice_screen<NT>, dim3(a.n_sblk), dim3(256), 0, s, a, L); break;
+        DF_SCREEN_L(1) DF_SCREEN_L(2) DF_SCREEN_L(3) DF_SCREEN_L(4)
+        DF_SCREEN_L(5) DF_SCREEN_L(6) DF_SCREEN_L(7) DF_SCREEN_L(8)
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

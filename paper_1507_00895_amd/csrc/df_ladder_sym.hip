@@ -1,5 +1,6 @@
 // Symmetric FP64 ladder: builds for one to eight 16-row blocks, dispatch.
 #include "df_ladder_sym.hpp"
+#include "df_lattice_ladder.hpp"
 
 namespace df {
 
@@ -49,6 +50,28 @@ hipError_t launch_ladder_sym(const LadderArgs &a, hipStream_t s) {
         case 8: return launch_nt<8>(a, s);
         default: return hipErrorInvalidValue;
     }
+}
+
+// The lattice observables' ladder term (LAT)
+template <int NT>
+__global__ __launch_bounds__(64 * SymBuild<NT>::W)
+__attribute__((amdgpu_waves_per_eu(SymBuild<NT>::EU, SymBuild<NT>::EU)))
+void k_lattice_sym(LadderArgs a0, const double *L, double *lad) {
+    sym_item<NT, SymBuild<NT>::W, false, true>(a0, xcd_item(blockIdx.x, gridDim.x), L, lad);
+}
+
+hipError_t launch_lattice_sym(const LadderArgs &a, const double *L, double *lad, hipStream_t s) {
+    if (a.n_items <= 0) return hipErrorInvalidValue;
+    switch ((a.n_nu + 15) / 16) {
+#define DF_SYM(NT)                                                                                          \
+    case NT:                                                                                                \
+        hipLaunchKernelGGL(k_lattice_sym<NT>, dim3(a.n_items), dim3(64 * SymBuild<NT>::W), 0, s, a, L, lad); \
+        break;
+        DF_SYM(1) DF_SYM(2) DF_SYM(3) DF_SYM(4) DF_SYM(5) DF_SYM(6) DF_SYM(7) DF_SYM(8)
+#undef DF_SYM
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
 }
 
 }  // namespace df

@@ -59,6 +59,12 @@ template <int NT> struct SymShared {
     cd pivv[16 * NT];         // reciprocal scalar pivots
     int flag;
 };
+// LAT (below): S L of the unfinished blocks, K_t (S L)_t of the step
+template <int NT> struct SymVectors {
+    cd u[16 * (NT > 0 ? NT : 1)];
+    cd v[16];
+};
+template <> struct SymVectors<0> {};
 
 // C += A H with A in operand form A[4r + lg][lj], H as accumulators, in three
 // real products per complex one (T1 = A_re H_re, T2 = A_im H_im, C_im += (A_re +
@@ -133,6 +139,15 @@ template <int S> __device__ __forceinline__ void sym_sweep(sd4 &Xr, sd4 &Xi, cd 
     if constexpr (S + 1 < 16) sym_sweep<S + 1>(Xr, Xi, piv, lj);
 }
 
+// sum over the four lane groups, returned to all of them
+__device__ __forceinline__ cd sum_groups(cd v) {
+    v.re += __shfl_xor(v.re, 16, 64);
+    v.im += __shfl_xor(v.im, 16, 64);
+    v.re += __shfl_xor(v.re, 32, 64);
+    v.im += __shfl_xor(v.im, 32, 64);
+    return v;
+}
+
 // The pivot block: S_tt (accumulators C) is published to P, then replaced by
 // H = Z - 1, Z = (1 - chi S)^-1; K = Z chi goes to LDS, diag(S Z) is returned
 // (this lane's part: column lj, rows lg + 4r).
@@ -163,13 +178,18 @@ __device__ __forceinline__ cd sym_pivot(sd4 &Cr, sd4 &Ci, cd (*P)[17], const cd 
 }
 
 // W waves, each with NU tile columns of up to ND tiles.  FULL: n_nu = 16 NT.
-template <int NT, int W, bool FULL>
-__device__ __forceinline__ void sym_item(const LadderArgs &a0, int gitem) {
+// LAT: the lattice observables' ladder term instead, lad = L^T Gamma L (n_om = 1).
+// With u = S^(t) L it grows by u_t^T K_t u_t per step, and u_i by S_it K_t u_t, so a
+// tile is updated only while both its blocks are unfinished.  W holds gamma L.
+template <int NT, int W, bool FULL, bool LAT = false>
+__device__ __forceinline__ void sym_item(const LadderArgs &a0, int gitem, const double *L = nullptr,
+                                         double *lad = nullptr) {
     constexpr int NP = 16 * NT;
     constexpr int NU = (NT + W - 1) / W;
     constexpr int ND = NT / 2 + 1;
     constexpr bool EVEN = (NT % 2) == 0;
     __shared__ SymShared<NT> sh;
+    __shared__ SymVectors<LAT ? NT : 0> vec;
     const int tid = threadIdx.x;
     const int w = W > 1 ? __builtin_amdgcn_readfirstlane(tid >> 6) : 0;
     const int l0 = tid & 63;
@@ -205,7 +225,15 @@ __device__ __forceinline__ void sym_item(const LadderArgs &a0, int gitem) {
     for (int j = tid; j < NP; j += 64 * W) {
         const cd x = ld(a.chi, ((size_t)im * n_nu + clamp_nu<FULL>(j, nm1)) * N + q);
         sh.xv[j] = (FULL || j < n_nu) ? x : cd{0.0, 0.0};
+        if constexpr (LAT) {
+            const cd u = ld(a.w, ((size_t)cm * n_nu + clamp_nu<FULL>(j, nm1)) * N + q);
+            vec.u[j] = (FULL || j < n_nu) ? u : cd{0.0, 0.0};
+        }
     }
+    cd lsum = {0.0, 0.0};    // LAT: this lane's part of lad
+    if constexpr (LAT)
+        for (int j = tid; j < n_nu; j += 64 * W)
+            lsum = fma_c(lsum, ld(L, (size_t)j * N + q), ld(a.w, ((size_t)cm * n_nu + j) * N + q));
     sd4 Cr[NU][ND], Ci[NU][ND];
     {
         const int lj = l0 & 15, lg = l0 >> 4;
@@ -250,6 +278,19 @@ __device__ __forceinline__ void sym_item(const LadderArgs &a0, int gitem) {
         // ---- the pivot block, and the rest of the panel S_tx
         if (w == wt)
             dacc[ut] = sym_pivot(Cr[ut][0], Ci[ut][0], P[t], sh.xv + 16 * t, sh.K, sh.pivv + 16 * t, l);
+        if constexpr (LAT) {
+            if (w == wt) {
+                // v = K u_t (column sums of K, symmetric), lad += u_t^T v
+                cd v = {0.0, 0.0};
+#pragma unroll
+                for (int r = 0; r < 4; ++r) v = fma_c(v, K[lg + 4 * r][lj], vec.u[16 * t + lg + 4 * r]);
+                v = sum_groups(v);
+                if (lg == 0) {
+                    vec.v[lj] = v;
+                    lsum = fma_c(lsum, vec.u[16 * t + lj], v);
+                }
+            }
+        }
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int u = 0; u < NU; ++u)
@@ -273,6 +314,14 @@ __device__ __forceinline__ void sym_item(const LadderArgs &a0, int gitem) {
         for (int u = 0; u < NU; ++u) {
             if (!own(u)) continue;
             const int j = col(u);
+            if constexpr (LAT) {
+                if (j <= t) continue;             // finished
+                cd du = {0.0, 0.0};
+#pragma unroll
+                for (int r = 0; r < 4; ++r) du = fma_c(du, P[j][4 * r + lg][lj], vec.v[4 * r + lg]);
+                du = sum_groups(du);
+                if (lg == 0) vec.u[16 * j + lj] = vec.u[16 * j + lj] + du;
+            }
             __builtin_amdgcn_sched_barrier(0);
             sd4 Hr, Hi;
             if (u == ut && w == wt) {
@@ -306,19 +355,26 @@ __device__ __forceinline__ void sym_item(const LadderArgs &a0, int gitem) {
                 if (!has(u, d)) continue;
                 const int i = row(u, d);
                 __builtin_amdgcn_sched_barrier(0);   // one tile's operands at a time
-                if (i > t || j > t) sym_update(Cr[u][d], Ci[u][d], P[i], Hr, Hi, lj, lg);
+                if (LAT ? i > t : (i > t || j > t)) sym_update(Cr[u][d], Ci[u][d], P[i], Hr, Hi, lj, lg);
             }
         }
         if (t + 1 < NT) sync();   // the panel and K are free
     }
     sync();
-#pragma unroll
-    for (int u = 0; u < NU; ++u) {
-        dacc[u].re += __shfl_xor(dacc[u].re, 16, 64);
-        dacc[u].im += __shfl_xor(dacc[u].im, 16, 64);
-        dacc[u].re += __shfl_xor(dacc[u].re, 32, 64);
-        dacc[u].im += __shfl_xor(dacc[u].im, 32, 64);
+    if constexpr (LAT) {
+        lsum.re = wave_sum(lsum.re);
+        lsum.im = wave_sum(lsum.im);
+        if (l0 == 0) sh.xv[w] = lsum;
+        sync();
+        if (tid == 0) {
+            cd r = sh.xv[0];
+            for (int x = 1; x < W; ++x) r = r + sh.xv[x];
+            st(lad, (size_t)cm * N + q, r);
+        }
+        return;
     }
+#pragma unroll
+    for (int u = 0; u < NU; ++u) dacc[u] = sum_groups(dacc[u]);
     if (w == 0) {
         // det D = 1 / (the product of the reciprocal pivots): the signs of the
         // real parts agree, log and phase change sign (phase kept in (-pi, pi])

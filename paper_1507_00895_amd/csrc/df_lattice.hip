@@ -4,15 +4,21 @@
 //                         denominator 1 + g Sigma~), G_lat (eq. glat, in a form free of
 //                         cancellation), frak G = G~ (G~0 + g) / G~0
 //   (k_dual_gf / k_bubble of df_fft_kernels.hip turn frak G, G_lat and G~ into
-//    L_nu(q), the per-nu lattice bubble and chi~ at Omega = 0)
-//   k_lattice_chi_ladder  per (channel, q): sum_{nu nu'} L_nu Gamma_{nu nu'} L_nu' with
-//                         Gamma = [1 - gamma chi~]^-1 gamma at Omega = 0, by Gaussian
-//                         elimination with partial pivoting of [D | gamma L] (FP64)
+//    L_nu(q), the per-nu lattice bubble and chi~ at Omega = 0, the three in one
+//    launch each)
+//   ladder term           per (channel, q): sum_{nu nu'} L_nu Gamma_{nu nu'} L_nu' with
+//                         Gamma = [1 - gamma chi~]^-1 gamma at Omega = 0: certified items
+//                         of symmetric vertices in the block ladder of
+//                         df_ladder_sym.hpp, the rest here (k_lattice_rest) by
+//                         Gauss-Jordan with partial pivoting of [D | gamma L] in registers
 //   k_lattice_chi_sum     chi^{ch/sp}(q) = sum_nu bubble_nu(q) + ladder term
 //
-// These run once per converged solution, outside the iteration: plain FP64
-// kernels sized for clarity, not for the roofline.
-#include "df_internal.hpp"
+// 32x32, n_nu 64, 2,048 items: 95 us per call, of it 62 the block ladder (bound by
+// the issue of its pivot inversions, df_ladder_sym.hpp); 1219 us with eliminations of
+// all items on matrices in global memory (four launches of 288 us), one transform
+// and one bubble launch per field and one thread per momentum in the final sum.
+#include "df_lattice_ladder.hpp"
+#include "df_ladder_pivot.hpp"
 
 namespace df {
 
@@ -46,121 +52,135 @@ __global__ __launch_bounds__(256) void k_lattice_fields(LatticeFieldArgs a) {
 }
 
 // ------------------------------------------------------------------------
-// One block (256 threads) per item (channel c, q) of the chunk.  The
-// augmented matrix [D | y], D = 1 - gamma diag(chi~(q)), y = gamma L(q), lives in
-// this item's slice of the work buffer (row-major, n x (n + 1) complex); the
-// waves of the block share it through the CU's cache, ordered by barriers.
+// lad = L^T z, D z = y, D = 1 - gamma diag(chi~), y = gamma L (left in W by the
+// screening kernel) of the queued items: Gauss-Jordan with partial pivoting as in
+// pivot_item (df_ladder_pivot.hpp), the matrix spread cyclically over the
+// registers of TR x TC threads, but only the columns right of the pivot are
+// updated, and y with them.  Rows are never moved: z_k is y of the row that was
+// the pivot of column k.
 // ------------------------------------------------------------------------
-__device__ __forceinline__ void argmax_pair(double &v, int &i) {
+template <int NP, int TR, int TC>
+__global__ __launch_bounds__(TR *TC) void k_lattice_rest(LadderArgs a, const double *L, double *lad) {
+    constexpr int NT = TR * TC, BR = NP / TR, BC = NP / TC;
+    __shared__ cd colbuf[2][NP];
+    __shared__ cd rowblk[BR][NP];
+    __shared__ cd yv[NP];
+    __shared__ int prow[NP];
+    __shared__ cd red[NT / 64];
+    const int tid = threadIdx.x, tr = tid / TC, tc = tid % TC, lane = tid & 63;
+    const int n = a.n_nu, N = a.N;
+    const int n_near = *a.near_count, n_all = n_near + *a.queue_count;
+    for (int wi = blockIdx.x; wi < n_all; wi += gridDim.x) {
+        const int item = wi < n_near ? a.near_queue[wi] : a.queue[wi - n_near];
+        const int c = item / N, q = item % N;
+        const double *gam = a.gdm + 2 * (size_t)c * n * n;
+        cd A[BR][BC];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const double ov = __shfl_xor(v, off, 64);
-        const int oi = __shfl_xor(i, off, 64);
-        if (ov > v || (ov == v && oi < i)) {
-            v = ov;
-            i = oi;
-        }
-    }
-}
-
-__device__ __forceinline__ cd wave_sum_c(cd x) {
+        for (int b = 0; b < BC; ++b) {
+            const int j = tc + TC * b;
+            const cd x = j < n ? ld(a.chi, (size_t)j * N + q) : cd{0.0, 0.0};
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        x.re += __shfl_xor(x.re, off, 64);
-        x.im += __shfl_xor(x.im, off, 64);
-    }
-    return x;
-}
-
-__global__ __launch_bounds__(256) void k_lattice_chi_ladder(LatticeChiArgs a) {
-    const int n = a.n_nu, N = a.N, ldm = n + 1;
-    const int item = a.item0 + blockIdx.x;
-    const int c = item / N, q = item % N;
-    const int tid = threadIdx.x, lane = tid & 63;
-    double *M = a.work + 2 * (size_t)blockIdx.x * n * ldm;
-    __shared__ cd Lv[128], xv[128], zv[128];
-    __shared__ int s_piv;
-    for (int i = tid; i < n; i += blockDim.x) {
-        Lv[i] = ld(a.L, (size_t)i * N + q);
-        xv[i] = ld(a.chi0, (size_t)i * N + q);
-    }
-    __syncthreads();
-    // gamma^{d/m} at Omega = 0 = gamma_uu +- gamma_ud
-    const double sgn = (c == 0) ? 1.0 : -1.0;
-    const size_t v0 = (size_t)a.i0 * n * n;
-    for (int e = tid; e < n * n; e += blockDim.x) {
-        const int i = e / n, j = e % n;
-        const cd gu = ld(a.guu, v0 + e), gd = ld(a.gud, v0 + e);
-        const cd gm = {gu.re + sgn * gd.re, gu.im + sgn * gd.im};
-        const cd x = gm * xv[j];
-        st(M, (size_t)i * ldm + j, cd{(i == j ? 1.0 : 0.0) - x.re, -x.im});
-    }
-    for (int i = tid; i < n; i += blockDim.x) {
-        cd y = {0.0, 0.0};
-        for (int j = 0; j < n; ++j) {
-            const cd gu = ld(a.guu, v0 + (size_t)i * n + j), gd = ld(a.gud, v0 + (size_t)i * n + j);
-            y = fma_c(y, cd{gu.re + sgn * gd.re, gu.im + sgn * gd.im}, Lv[j]);
-        }
-        st(M, (size_t)i * ldm + n, y);
-    }
-    __syncthreads();
-    for (int k = 0; k < n; ++k) {
-        if (tid < 64) {   // partial pivoting: largest |M_ik|, i >= k (lowest index on ties)
-            double bv = -1.0;
-            int bi = k;
-            for (int i = k + lane; i < n; i += 64) {
-                const cd x = ld(M, (size_t)i * ldm + k);
-                const double v = x.re * x.re + x.im * x.im;
-                if (v > bv) {
-                    bv = v;
-                    bi = i;
+            for (int ai = 0; ai < BR; ++ai) {
+                const int i = tr + TR * ai;
+                const double d = (i == j) ? 1.0 : 0.0;
+                A[ai][b] = {d, 0.0};
+                if (i < n && j < n) {
+                    const cd g = ld(gam, (size_t)i * n + j) * x;
+                    A[ai][b] = {d - g.re, -g.im};
                 }
             }
-            argmax_pair(bv, bi);
-            if (lane == 0) s_piv = bi;
+        }
+        for (int i = tid; i < NP; i += NT) yv[i] = i < n ? ld(a.w, ((size_t)c * n + i) * N + q) : cd{0.0, 0.0};
+        if (tc == 0) {
+#pragma unroll
+            for (int ai = 0; ai < BR; ++ai) colbuf[0][tr + TR * ai] = A[ai][0];
         }
         __syncthreads();
-        const int p = s_piv;
-        if (p != k) {
-            for (int j = k + tid; j <= n; j += blockDim.x) {
-                const cd x = ld(M, (size_t)k * ldm + j), y = ld(M, (size_t)p * ldm + j);
-                st(M, (size_t)k * ldm + j, y);
-                st(M, (size_t)p * ldm + j, x);
+        bool used0 = false, used1 = false;
+#pragma unroll
+        for (int kk = 0; kk < BC; ++kk) {
+            for (int tcol = 0; tcol < TC; ++tcol) {
+                const int k = kk * TC + tcol;
+                if (k >= n) break;
+                const cd *col = colbuf[k & 1];
+                unsigned key = 0u;
+                if (lane < NP && !used0) key = pivot_key(cabs1(col[lane]), lane);
+                if (NP > 64 && lane + 64 < NP && !used1) {
+                    const unsigned k2 = pivot_key(cabs1(col[lane + 64]), lane + 64);
+                    key = k2 > key ? k2 : key;
+                }
+                const int p = 255 - (int)(__ockl_wfred_max_u32(key) & 255u);
+                if (p == lane) used0 = true;
+                if (p == lane + 64) used1 = true;
+                const cd ip = recip(col[p]);
+                if (tr == p % TR) {
+#pragma unroll
+                    for (int ai = 0; ai < BR; ++ai)
+#pragma unroll
+                        for (int b = kk; b < BC; ++b) rowblk[ai][tc + TC * b] = A[ai][b];
+                }
+                if (tid == 0) prow[k] = p;
+                const cd yp = yv[p] * ip;
+                __syncthreads();
+                cd f[BR];
+#pragma unroll
+                for (int ai = 0; ai < BR; ++ai) {
+                    const int i = tr + TR * ai;
+                    f[ai] = (i == p) ? cd{0.0, 0.0} : col[i] * ip;
+                }
+#pragma unroll
+                for (int b = kk; b < BC; ++b) {
+                    const cd r = rowblk[p / TR][tc + TC * b];
+#pragma unroll
+                    for (int ai = 0; ai < BR; ++ai) A[ai][b] = fms(A[ai][b], f[ai], r);
+                }
+                for (int i = tid; i < n; i += NT) yv[i] = i == p ? yp : fms(yv[i], col[i], yp);
+                cd *nxt = colbuf[(k + 1) & 1];
+                if (tcol + 1 < TC) {
+                    if (tc == tcol + 1) {
+#pragma unroll
+                        for (int ai = 0; ai < BR; ++ai) nxt[tr + TR * ai] = A[ai][kk];
+                    }
+                } else if (kk + 1 < BC) {
+                    if (tc == 0) {
+#pragma unroll
+                        for (int ai = 0; ai < BR; ++ai) nxt[tr + TR * ai] = A[ai][kk + 1 < BC ? kk + 1 : kk];
+                    }
+                }
+                __syncthreads();
             }
-            __syncthreads();
         }
-        const cd inv = recip(ld(M, (size_t)k * ldm + k));
-        const int rows = n - 1 - k, cols = n - k;   // rows k+1.., columns k+1..n
-        for (int e = tid; e < rows * cols; e += blockDim.x) {
-            const int i = k + 1 + e / cols, j = k + 1 + e % cols;
-            const cd l = ld(M, (size_t)i * ldm + k) * inv;
-            st(M, (size_t)i * ldm + j, fms(ld(M, (size_t)i * ldm + j), l, ld(M, (size_t)k * ldm + j)));
+        cd s = {0.0, 0.0};
+        for (int k = tid; k < n; k += NT) s = fma_c(s, ld(L, (size_t)k * N + q), yv[prow[k]]);
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) {
+            s.re += __shfl_xor(s.re, off, 64);
+            s.im += __shfl_xor(s.im, off, 64);
+        }
+        if (lane == 0) red[tid >> 6] = s;
+        __syncthreads();
+        if (tid == 0) {
+            cd r = red[0];
+            for (int x = 1; x < NT / 64; ++x) r = r + red[x];
+            st(lad, (size_t)c * N + q, r);
         }
         __syncthreads();
-    }
-    // back substitution by wave 0, then sum_i L_i z_i
-    if (tid < 64) {
-        for (int i = n - 1; i >= 0; --i) {
-            cd s = {0.0, 0.0};
-            for (int j = i + 1 + lane; j < n; j += 64) s = fma_c(s, ld(M, (size_t)i * ldm + j), zv[j]);
-            s = wave_sum_c(s);
-            if (lane == 0) zv[i] = cdiv(ld(M, (size_t)i * ldm + n) - s, ld(M, (size_t)i * ldm + i));
-            __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-        }
-        cd r = {0.0, 0.0};
-        for (int i = lane; i < n; i += 64) r = fma_c(r, Lv[i], zv[i]);
-        r = wave_sum_c(r);
-        if (lane == 0) st(a.lad, (size_t)c * N + q, r);
     }
 }
 
-// chi_c(q) = sum_nu bubble[nu][q] + lad[c][q], fixed order over nu.
+// chi_c(q) = sum_nu bubble[nu][q] + lad[c][q]; 64 momenta per block, four threads
+// each, fixed order.
 __global__ __launch_bounds__(256) void k_lattice_chi_sum(LatticeSumArgs a) {
-    const int q = blockIdx.x * blockDim.x + threadIdx.x;
-    if (q >= a.N) return;
+    __shared__ cd red[4][64];
+    const int x = threadIdx.x & 63, p = threadIdx.x >> 6;
+    const int q = blockIdx.x * 64 + x;
     cd s = {0.0, 0.0};
-    for (int n = 0; n < a.n_nu; ++n) s = s + ld(a.bub, (size_t)n * a.N + q);
+    if (q < a.N)
+        for (int n = p; n < a.n_nu; n += 4) s = s + ld(a.bub, (size_t)n * a.N + q);
+    red[p][x] = s;
+    __syncthreads();
+    if (p != 0 || q >= a.N) return;
+    s = (red[0][x] + red[1][x]) + (red[2][x] + red[3][x]);
     if (a.chi_ch) st(a.chi_ch, q, s + ld(a.lad, q));
     if (a.chi_sp) st(a.chi_sp, q, s + ld(a.lad, (size_t)a.N + q));
 }
@@ -170,14 +190,25 @@ hipError_t launch_lattice_fields(const LatticeFieldArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_lattice_chi_ladder(const LatticeChiArgs &a, int items, hipStream_t s) {
-    if (a.n_nu > 128 || items < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_lattice_chi_ladder, dim3(items), dim3(256), 0, s, a);
+hipError_t launch_lattice_rest(const LadderArgs &a, const double *L, double *lad, int grid, hipStream_t s) {
+    if (grid <= 0 || !a.near_count || !a.queue_count) return hipErrorInvalidValue;
+#define DF_REST(NP, TR, TC)                                                                              \
+    hipLaunchKernelGGL((k_lattice_rest<NP, TR, TC>), dim3(grid), dim3(TR * TC), 0, s, a, L, lad)
+    switch (ladder_padded_size(a.n_nu)) {
+        case 16: DF_REST(16, 8, 8); break;
+        case 32: DF_REST(32, 8, 8); break;
+        case 48: DF_REST(48, 16, 16); break;
+        case 64: DF_REST(64, 16, 16); break;
+        case 96: DF_REST(96, 32, 16); break;
+        case 128: DF_REST(128, 32, 16); break;
+        default: return hipErrorInvalidValue;
+    }
+#undef DF_REST
     return hipGetLastError();
 }
 
 hipError_t launch_lattice_chi_sum(const LatticeSumArgs &a, hipStream_t s) {
-    hipLaunchKernelGGL(k_lattice_chi_sum, dim3((a.N + 255) / 256), dim3(256), 0, s, a);
+    hipLaunchKernelGGL(k_lattice_chi_sum, dim3((a.N + 63) / 64), dim3(256), 0, s, a);
     return hipGetLastError();
 }
 

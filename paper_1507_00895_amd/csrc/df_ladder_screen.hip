@@ -108,8 +108,11 @@ __device__ __forceinline__ void screen_body(const LadderArgs &a0, const double *
     }
 
     const int cm = c * a.n_om + im;
-    // (the matrix of the product by rows k: P is symmetric, gamma transposed)
-    const double *pm = (LAT ? a.gtr : a.pdm) + 2 * (size_t)cm * n * n;
+    // the matrix of the product, by rows k: P (symmetric); LAT: the symmetric part of
+    // gamma where the block ladder takes it, else gamma from its transpose
+    const double *pm = a.pdm;
+    if constexpr (LAT) pm = vertex_symmetric(a.symp + 4 * (size_t)im * kPrepChunks, n, c, l) ? a.gsym : a.gtr;
+    pm += 2 * (size_t)cm * n * n;
     const float *ga = a.gabs + (size_t)cm * n * n;
     // this wave's rows of |gamma| (A operand of every k-slice)
     constexpr int NI = (NT + 3) / 4;

@@ -57,7 +57,7 @@ __global__ __launch_bounds__(256) void k_lattice_fields(LatticeFieldArgs a) {
 // pivot_item (df_ladder_pivot.hpp), the matrix spread cyclically over the
 // registers of TR x TC threads, but only the columns right of the pivot are
 // updated, and y with them.  Rows are never moved: z_k is y of the row that was
-// the pivot of column k.
+// the pivot of column k, divided by the pivot.
 // ------------------------------------------------------------------------
 template <int NP, int TR, int TC>
 __global__ __launch_bounds__(TR *TC) void k_lattice_rest(LadderArgs a, const double *L, double *lad) {
@@ -66,6 +66,7 @@ __global__ __launch_bounds__(TR *TC) void k_lattice_rest(LadderArgs a, const dou
     __shared__ cd rowblk[BR][NP];
     __shared__ cd yv[NP];
     __shared__ int prow[NP];
+    __shared__ cd ipv[NP];
     __shared__ cd red[NT / 64];
     const int tid = threadIdx.x, tr = tid / TC, tc = tid % TC, lane = tid & 63;
     const int n = a.n_nu, N = a.N;
@@ -119,7 +120,10 @@ __global__ __launch_bounds__(TR *TC) void k_lattice_rest(LadderArgs a, const dou
 #pragma unroll
                         for (int b = kk; b < BC; ++b) rowblk[ai][tc + TC * b] = A[ai][b];
                 }
-                if (tid == 0) prow[k] = p;
+                if (tid == 0) {
+                    prow[k] = p;
+                    ipv[k] = ip;
+                }
                 const cd yp = yv[p] * ip;
                 __syncthreads();
                 cd f[BR];
@@ -134,7 +138,9 @@ __global__ __launch_bounds__(TR *TC) void k_lattice_rest(LadderArgs a, const dou
 #pragma unroll
                     for (int ai = 0; ai < BR; ++ai) A[ai][b] = fms(A[ai][b], f[ai], r);
                 }
-                for (int i = tid; i < n; i += NT) yv[i] = i == p ? yp : fms(yv[i], col[i], yp);
+                // (the pivot row stays as it is, in the matrix and in y)
+                for (int i = tid; i < n; i += NT)
+                    if (i != p) yv[i] = fms(yv[i], col[i], yp);
                 cd *nxt = colbuf[(k + 1) & 1];
                 if (tcol + 1 < TC) {
                     if (tc == tcol + 1) {
@@ -151,7 +157,7 @@ __global__ __launch_bounds__(TR *TC) void k_lattice_rest(LadderArgs a, const dou
             }
         }
         cd s = {0.0, 0.0};
-        for (int k = tid; k < n; k += NT) s = fma_c(s, ld(L, (size_t)k * N + q), yv[prow[k]]);
+        for (int k = tid; k < n; k += NT) s = fma_c(s, ld(L, (size_t)k * N + q), yv[prow[k]] * ipv[k]);
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) {
             s.re += __shfl_xor(s.re, off, 64);

@@ -152,17 +152,24 @@ class Instance:
         return self.nk ** self.D
 
     def to_c(self) -> DfInst:
-        for name in ("g", "delta", "gamma_uu", "gamma_ud", "sigma", "gd", "chi", "w", "logdet",
-                     "sigma_calc"):
+        import torch
+        c128 = torch.complex128
+        ptrs = []
+        for name in _COMPLEX_FIELDS:
             t = getattr(self, name)
-            if t is not None:
-                import torch
-                if t.dtype != torch.complex128 or not t.is_contiguous() or not t.is_cuda:
-                    raise TypeError(f"{name} must be a contiguous complex128 device tensor")
-        return DfInst(self.D, self.nk, self.n_nu, self.n_om, float(self.beta),
-                      _ptr(self.g), _ptr(self.delta), _ptr(self.eps), _ptr(self.gamma_uu),
-                      _ptr(self.gamma_ud), _ptr(self.sigma), _ptr(self.gd), _ptr(self.chi),
-                      _ptr(self.w), _ptr(self.logdet), _ptr(self.sigma_calc), _ptr(self.status))
+            if t is None:
+                ptrs.append(None)
+                continue
+            if t.dtype is not c128 or not t.is_contiguous() or not t.is_cuda:
+                raise TypeError(f"{name} must be a contiguous complex128 device tensor")
+            ptrs.append(t.data_ptr())
+        return DfInst(self.D, self.nk, self.n_nu, self.n_om, float(self.beta), ptrs[0], ptrs[1],
+                      _ptr(self.eps), *ptrs[2:], _ptr(self.status))
+
+
+# complex fields in the order of df_inst_t (eps comes after delta there)
+_COMPLEX_FIELDS = ("g", "delta", "gamma_uu", "gamma_ud", "sigma", "gd", "chi", "w", "logdet",
+                   "sigma_calc")
 
 
 def make_instance(problem, device="cuda", outputs: bool = True) -> Instance:

@@ -65,8 +65,10 @@ int check_inst(const df_inst_t &p, Shape *s) {
     s->n_om = p.n_om;
     s->items = 2 * p.n_om * (int)N;
     s->im0 = (p.n_om - 1) / 2;
-    s->n_irr = 0;
-    for (int q = 0; q < (int)N; ++q) s->n_irr += (canonical_q(q, p.D, l) == q);
+    // point-group orbits: sorted D-tuples of the nk / 2 + 1 values min(c, nk - c), i.e.
+    // binomial(nk / 2 + D, D) (counting them took 20 us of every call at N = 4096)
+    s->n_irr = 1;
+    for (int a = 1; a <= p.D; ++a) s->n_irr = s->n_irr * (p.nk / 2 + a) / a;
     s->items_sym = 2 * (p.n_om - s->im0) * s->n_irr;
     // work-groups of the Schwinger-Dyson kernel: two N = 4096 arrays fit a CU (512 in
     // all; twice as many chunks cost 18 % at 64 x 64, n_nu 128: 88 -> 106 us with the
@@ -81,9 +83,16 @@ int check_inst(const df_inst_t &p, Shape *s) {
     return DF_OK;
 }
 
+// work-groups (and norm partials) of the mixing and Anderson kernels
+int mix_blocks(const Shape &s) {
+    const size_t count = (size_t)s.n_nu * s.N;
+    int blocks = (int)((count + 255) / 256);
+    return blocks > kMixBlocks ? kMixBlocks : blocks;
+}
+
 // Per-instance workspace regions (byte offsets from the instance base).
 struct Layout {
-    size_t gr, gdm, pdm, gtr, gp32, gtr32, gsym, gabs, symp, cert, part, norm, gd, chi, w;
+    size_t gr, gdm, pdm, gtr, gp32, gtr32, gsym, gabs, symp, cert, part, gd, chi, w;
     size_t qrep, qlist;               // symmetry tables: int[N] each
     size_t fx, xh, rh, accpart;       // Anderson acceleration (0 when unused)
     size_t total;
@@ -112,7 +121,6 @@ Layout layout_of(const Shape &s, int slots) {
     L.symp = take((size_t)s.n_om * kPrepChunks * 4 * sizeof(float));
     L.cert = take((size_t)s.items);
     L.part = take((size_t)s.n_chunks * fld);
-    L.norm = take((size_t)kMixBlocks * 2 * sizeof(double));
     L.gd = take(fld);
     L.chi = take((size_t)s.n_om * fld);
     L.w = take(2 * (size_t)s.n_om * fld);
@@ -136,7 +144,8 @@ struct Global {
     size_t near;                      // int[sum of items]: refined kernel's items near the instability
     size_t ints;                      // int[kIntsInst + n_inst]: queue lengths, item counters,
                                       // outside counts
-    size_t diffs;                     // double[n_inst][2]: diff, non-finite flag
+    size_t norms;                     // double[sum of mix_blocks][2]: norm partials, right after
+                                      // the ints: one readback per iteration
     size_t accdots;                   // double[n_inst][kAccMaxSlots] (Anderson)
     size_t total;
 };
@@ -145,6 +154,8 @@ struct Plan {
     std::vector<Shape> shape;
     std::vector<Layout> lay;
     std::vector<size_t> base;
+    std::vector<size_t> norm0;        // first norm partial of each instance (doubles)
+    size_t readback = 0;              // bytes of ints and norm partials
     Global g;
     size_t total = 0;
 };
@@ -175,9 +186,17 @@ int make_plan(const df_inst_t *inst, int32_t n_inst, Plan *P, int accel = 0) {
     g.near = off;
     off = align_up(off + items * sizeof(int));
     g.ints = off;
-    off = align_up(off + (size_t)(kIntsInst + n_inst) * sizeof(int));
-    g.diffs = off;
-    off = align_up(off + (size_t)n_inst * 2 * sizeof(double));
+    off += ((size_t)(kIntsInst + n_inst) * sizeof(int) + 7) & ~(size_t)7;
+    g.norms = off;
+    size_t norms = 0;
+    P->norm0.clear();
+    for (int i = 0; i < n_inst; ++i) {
+        P->norm0.push_back(norms);
+        norms += 2 * (size_t)mix_blocks(P->shape[i]);
+    }
+    off += norms * sizeof(double);
+    P->readback = off - g.ints;
+    off = align_up(off);
     g.accdots = off;
     off = align_up(off + (size_t)n_inst * kAccMaxSlots * sizeof(double));
     g.total = off;
@@ -403,7 +422,7 @@ int stage_sigma(const df_inst_t &p, const Shape &s, const double *w, const doubl
 }
 
 int stage_reduce_mix(const Shape &s, const double *part, double *sigma_calc, double *sigma,
-                     double alpha, double *norm, double *diff, hipStream_t st) {
+                     double alpha, double *norm, hipStream_t st) {
     ReduceMixArgs a{};
     a.count = (size_t)s.n_nu * s.N;
     a.n_chunks = s.n_chunks;
@@ -412,12 +431,90 @@ int stage_reduce_mix(const Shape &s, const double *part, double *sigma_calc, dou
     a.sigma_calc = sigma_calc;
     a.sigma = sigma;
     a.norm_part = norm;
-    int blocks = (int)((a.count + 255) / 256);
-    if (blocks > kMixBlocks) blocks = kMixBlocks;
-    HIPCHK(launch_reduce_mix(a, blocks, st));
-    if (sigma) HIPCHK(launch_norm_final(norm, blocks, diff, st));
+    HIPCHK(launch_reduce_mix(a, mix_blocks(s), st));
     return DF_OK;
 }
+
+double *norm_part(const Plan &P, void *ws, int i) { return at<double>(ws, P.g.norms) + P.norm0[i]; }
+
+// diff = sqrt(sum |new - old|^2 / sum |new|^2) from the n block partials of the
+// mixing kernels, in a fixed order; false if a sum is not finite.  (On the host: the
+// partials are read back with the counters, a launch less per iteration.)
+bool norm_diff(const double *part, int n, double *diff) {
+    double d[256] = {}, m[256] = {};
+    for (int i = 0; i < n; ++i) {
+        d[i % 256] += part[2 * i];
+        m[i % 256] += part[2 * i + 1];
+    }
+    for (int s = 128; s > 0; s >>= 1)
+        for (int i = 0; i < s; ++i) {
+            d[i] += d[i + s];
+            m[i] += m[i + s];
+        }
+    if (m[0] == 0.0) *diff = d[0] == 0.0 ? 0.0 : INFINITY;
+    else *diff = sqrt(d[0] / m[0]);
+    return isfinite(d[0]) && isfinite(m[0]);
+}
+
+// Page-locked host memory for one call's readbacks and table upload (from pageable
+// memory the runtime stages every copy: two of them took 25 us of an 87 us
+// iteration).  Buffers up to kPinnedBytes go back to a list of at most kPinnedKept for
+// later calls of any thread; larger or further ones are freed.  Without page-locked
+// memory the lease falls back to ordinary memory.
+constexpr size_t kPinnedBytes = 256 * 1024;
+constexpr size_t kPinnedKept = 8;
+std::mutex g_pinned_mu;
+std::vector<void *> g_pinned;
+
+class PinnedLease {
+public:
+    explicit PinnedLease(size_t bytes) : pooled_(bytes <= kPinnedBytes) {
+        if (pooled_) {
+            std::lock_guard<std::mutex> lk(g_pinned_mu);
+            if (!g_pinned.empty()) {
+                p_ = g_pinned.back();
+                g_pinned.pop_back();
+                return;
+            }
+        }
+        if (hipHostMalloc(&p_, pooled_ ? kPinnedBytes : bytes, hipHostMallocPortable) != hipSuccess) {
+            (void)hipGetLastError();
+            p_ = nullptr;
+            plain_.resize(bytes);
+        }
+    }
+    ~PinnedLease() {
+        // (after a failed call a copy may still be on its way into the buffer: it is
+        // given up)
+        if (!p_ || !idle_) return;
+        if (pooled_) {
+            std::lock_guard<std::mutex> lk(g_pinned_mu);
+            if (g_pinned.size() < kPinnedKept) {
+                g_pinned.push_back(p_);
+                return;
+            }
+        }
+        (void)hipHostFree(p_);
+    }
+    PinnedLease(const PinnedLease &) = delete;
+    PinnedLease &operator=(const PinnedLease &) = delete;
+    char *data() { return p_ ? static_cast<char *>(p_) : plain_.data(); }
+    // n bytes from device memory to offset off, and the wait for it
+    bool read(size_t off, const void *dev, size_t n, hipStream_t st) {
+        idle_ = false;
+        if (hipMemcpyAsync(data() + off, dev, n, hipMemcpyDeviceToHost, st) != hipSuccess ||
+            hipStreamSynchronize(st) != hipSuccess)
+            return false;
+        idle_ = true;
+        return true;
+    }
+
+private:
+    void *p_ = nullptr;
+    bool idle_ = true;
+    bool pooled_;
+    std::vector<char> plain_;
+};
 
 bool ladder_prec(int prec) { return prec == DF_FP64 || prec == DF_FP32_REFINE || prec == DF_FP32; }
 
@@ -617,11 +714,10 @@ int queue_fused_iteration(const df_inst_t *inst, const Plan &P, const Fused &F,
         if (rc != DF_OK) return rc;
         if (o.accel > 0) {
             // F(x) only; the accelerated step follows outside this sequence
-            rc = stage_reduce_mix(s, part, at<double>(ws, b + L.fx), nullptr, 0.0, nullptr, nullptr,
-                                  st);
+            rc = stage_reduce_mix(s, part, at<double>(ws, b + L.fx), nullptr, 0.0, nullptr, st);
         } else {
             rc = stage_reduce_mix(s, part, inst[i].sigma_calc, inst[i].sigma, o.mix,
-                                  at<double>(ws, b + L.norm), at<double>(ws, P.g.diffs) + 2 * i, st);
+                                  norm_part(P, ws, i), st);
         }
         if (rc != DF_OK) return rc;
     }
@@ -629,12 +725,6 @@ int queue_fused_iteration(const df_inst_t *inst, const Plan &P, const Fused &F,
 }
 
 // ---- Anderson acceleration, host side -----------------------------------------
-int mix_blocks(const Shape &s) {
-    const size_t count = (size_t)s.n_nu * s.N;
-    int blocks = (int)((count + 255) / 256);
-    return blocks > kMixBlocks ? kMixBlocks : blocks;
-}
-
 // State of one instance: how many residuals are recorded since the last
 // reset (slots fill 0, 1, ... and then wrap), and the Gram matrix of the
 // recorded residuals, Re <r_i, r_j>, indexed by slot.
@@ -739,7 +829,11 @@ LatticeLayout lattice_layout_of(const Shape &s) {
     L.near = take(2 * (size_t)s.N * sizeof(int));
     L.ints = take(2 * sizeof(int));
     L.lad = take(2 * (size_t)s.N * 16);
-    L.total = o;
+    // the size stays what the interface has asked for so far (seven fields and up to
+    // 512 n_nu x (n_nu + 1) matrices), of which the above is the smaller part
+    const size_t chunk = 2 * s.N < 512 ? 2 * (size_t)s.N : 512;
+    const size_t asked = 7 * fld + 2 * (size_t)s.N * 16 + chunk * s.n_nu * (s.n_nu + 1) * 16;
+    L.total = o > asked ? o : align_up(asked);
     return L;
 }
 
@@ -991,7 +1085,7 @@ int df_sigma(const df_inst_t *inst, int32_t n_inst, void *ws, size_t ws_bytes, d
         if (rc != DF_OK) return rc;
         rc = stage_sigma(inst[i], s, inst[i].w, gr, part, st);
         if (rc != DF_OK) return rc;
-        rc = stage_reduce_mix(s, part, inst[i].sigma_calc, nullptr, 0.0, nullptr, nullptr, st);
+        rc = stage_reduce_mix(s, part, inst[i].sigma_calc, nullptr, 0.0, nullptr, st);
         if (rc != DF_OK) return rc;
     }
     return DF_OK;
@@ -1013,7 +1107,6 @@ int df_iterate(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts, int
     const int slots = opts->accel > 0 ? opts->accel + 1 : 0;
     std::vector<AccState> acc(slots > 0 ? n_inst : 0);
     for (auto &S : acc) S.gram.assign((size_t)slots * slots, 0.0);
-    std::vector<double> hdots((size_t)n_inst * kAccMaxSlots);
     hipStream_t st = (hipStream_t)stream;
     const bool graph = opts->use_graph != 0 && st != nullptr;
     // iterations per captured graph: the host step of Anderson acceleration
@@ -1038,8 +1131,12 @@ int df_iterate(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts, int
     std::vector<int> act;
     for (int i = 0; i < n_inst; ++i) act.push_back(i);
     std::vector<double> last(n_inst, INFINITY);
-    std::vector<double> hdiff(2 * (size_t)n_inst);
-    std::vector<int> hints(kIntsInst + n_inst);
+    // host side of the readbacks: counters and norm partials, dots
+    const size_t dots_bytes = slots > 0 ? (size_t)n_inst * kAccMaxSlots * sizeof(double) : 0;
+    PinnedLease lease(P.readback + dots_bytes);
+    const int *hints = reinterpret_cast<const int *>(lease.data());
+    const double *hnorms = reinterpret_cast<const double *>(lease.data() + (P.g.norms - P.g.ints));
+    const double *hdots = reinterpret_cast<const double *>(lease.data() + P.readback);
     // ladder precision of each instance; DF_ADAPTIVE starts in FP32 and moves
     // an instance to FP64 (for good) once its diff falls below switch_tol
     const bool adaptive = opts->prec == DF_ADAPTIVE;
@@ -1115,10 +1212,7 @@ int df_iterate(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts, int
                     return DF_E_HIP;
                 }
             }
-            if (hipMemcpyAsync(hdots.data(), at<double>(ws, P.g.accdots),
-                               hdots.size() * sizeof(double), hipMemcpyDeviceToHost,
-                               st) != hipSuccess ||
-                hipStreamSynchronize(st) != hipSuccess) {
+            if (!lease.read(P.readback, at<double>(ws, P.g.accdots), dots_bytes, st)) {
                 cleanup();
                 return DF_E_HIP;
             }
@@ -1147,30 +1241,25 @@ int df_iterate(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts, int
                 ca.n_slots = nv;
                 ca.alpha = opts->mix;
                 ca.x = inst[i].sigma;
-                ca.norm_part = at<double>(ws, b + L.norm);
-                const int blocks = mix_blocks(sh);
-                if (launch_acc_combine(ca, blocks, st) != hipSuccess ||
-                    launch_norm_final(ca.norm_part, blocks, at<double>(ws, P.g.diffs) + 2 * i, st) !=
-                        hipSuccess) {
+                ca.norm_part = norm_part(P, ws, i);
+                if (launch_acc_combine(ca, mix_blocks(sh), st) != hipSuccess) {
                     cleanup();
                     return DF_E_HIP;
                 }
                 if (!ok) S.recorded = 0;
             }
         }
-        if (hipMemcpyAsync(hdiff.data(), at<double>(ws, P.g.diffs), hdiff.size() * sizeof(double),
-                           hipMemcpyDeviceToHost, st) != hipSuccess ||
-            hipMemcpyAsync(hints.data(), at<int>(ws, P.g.ints), hints.size() * sizeof(int),
-                           hipMemcpyDeviceToHost, st) != hipSuccess ||
-            hipStreamSynchronize(st) != hipSuccess) {
+        if (!lease.read(0, at<int>(ws, P.g.ints), P.readback, st)) {
             cleanup();
             return DF_E_HIP;
         }
         std::vector<int> next;
         for (int i : act) {
-            last[i] = hdiff[2 * i];
+            double diff = 0.0;
+            const bool finite = norm_diff(hnorms + P.norm0[i], mix_blocks(P.shape[i]), &diff);
+            last[i] = diff;
             fell_back[i] = hints[kIntsInst + i] != 0;
-            if (hdiff[2 * i + 1] != 0.0 || !isfinite(hdiff[2 * i])) {
+            if (!finite || !isfinite(diff)) {
                 result = DF_E_NONFINITE;
                 continue;
             }
@@ -1178,17 +1267,17 @@ int df_iterate(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts, int
             // only on FP64 ladders), or when the FP32 iteration stops
             // contracting (its rounding floor)
             const double prev = last_prev[i];
-            last_prev[i] = hdiff[2 * i];
+            last_prev[i] = diff;
             if (adaptive && cur[i] == DF_FP32 &&
-                (hdiff[2 * i] < switch_tol || (opts->tol > 0.0 && hdiff[2 * i] < opts->tol) ||
-                 hdiff[2 * i] > 0.95 * prev)) {
+                (diff < switch_tol || (opts->tol > 0.0 && diff < opts->tol) ||
+                 diff > 0.95 * prev)) {
                 cur[i] = DF_FP64;
                 rebuild = true;
                 if (slots > 0) acc[i].recorded = 0;   // FP32 residuals leave the history
                 next.push_back(i);
                 continue;
             }
-            if (opts->tol > 0.0 && hdiff[2 * i] < opts->tol) continue;
+            if (opts->tol > 0.0 && diff < opts->tol) continue;
             next.push_back(i);
         }
         if (result == DF_E_NONFINITE) break;

@@ -194,35 +194,6 @@ __global__ __launch_bounds__(256) void k_reduce_mix(ReduceMixArgs a) {
     }
 }
 
-// diff = sqrt(sum dn / sum nn), summed over n_part block partials in order;
-// writes diff to out[0]; out[1] = 1 if a partial is not finite.
-__global__ __launch_bounds__(256) void k_norm_final(const double *part, int n_part, double *out) {
-    __shared__ double red[2][256];
-    double dn = 0.0, nn = 0.0;
-    for (int i = threadIdx.x; i < n_part; i += blockDim.x) {
-        dn += part[2 * i];
-        nn += part[2 * i + 1];
-    }
-    red[0][threadIdx.x] = dn;
-    red[1][threadIdx.x] = nn;
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s) {
-            red[0][threadIdx.x] += red[0][threadIdx.x + s];
-            red[1][threadIdx.x] += red[1][threadIdx.x + s];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        const double d = red[0][0], m = red[1][0];
-        double diff;
-        if (m == 0.0) diff = (d == 0.0) ? 0.0 : INFINITY;
-        else diff = sqrt(d / m);
-        out[0] = diff;
-        out[1] = (isfinite(d) && isfinite(m)) ? 0.0 : 1.0;
-    }
-}
-
 // ------------------------------------------------------------------------
 // gamma^{d/m} = gamma^uu +- gamma^ud, P^c[i][j] = gamma^c_ij gamma^c_ji and the
 // layouts and copies of them that the ladder kernels read.  One block per 256
@@ -349,11 +320,6 @@ hipError_t launch_sigma_part(const SigmaArgs &a, hipStream_t s) {
 
 hipError_t launch_reduce_mix(const ReduceMixArgs &a, int blocks, hipStream_t s) {
     hipLaunchKernelGGL(k_reduce_mix, dim3(blocks), dim3(256), 0, s, a);
-    return hipGetLastError();
-}
-
-hipError_t launch_norm_final(const double *part, int n_part, double *out, hipStream_t s) {
-    hipLaunchKernelGGL(k_norm_final, dim3(1), dim3(256), 0, s, part, n_part, out);
     return hipGetLastError();
 }
 

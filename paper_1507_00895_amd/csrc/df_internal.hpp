@@ -274,7 +274,6 @@ hipError_t launch_dual_gf(const DualGfArgs &a, hipStream_t s);
 hipError_t launch_bubble(const BubbleArgs &a, hipStream_t s);
 hipError_t launch_sigma_part(const SigmaArgs &a, hipStream_t s);
 hipError_t launch_reduce_mix(const ReduceMixArgs &a, int blocks, hipStream_t s);
-hipError_t launch_norm_final(const double *part, int n_part, double *out, hipStream_t s);
 hipError_t launch_acc_record(const AccRecordArgs &a, int blocks, hipStream_t s);
 hipError_t launch_acc_combine(const AccCombineArgs &a, int blocks, hipStream_t s);
 hipError_t launch_gamma_prep(const GammaPrepArgs &a, hipStream_t s);

@@ -90,6 +90,9 @@ int mix_blocks(const Shape &s) {
     return blocks > kMixBlocks ? kMixBlocks : blocks;
 }
 
+// norm partials of one iteration: from the Schwinger-Dyson kernel itself where it mixes
+int norm_parts(const Shape &s, int accel) { return accel > 0 || s.n_chunks > 1 ? mix_blocks(s) : s.n_nu; }
+
 // Per-instance workspace regions (byte offsets from the instance base).
 struct Layout {
     size_t gr, gdm, pdm, gtr, gp32, gtr32, gsym, gabs, symp, cert, part, gd, chi, w;
@@ -192,7 +195,7 @@ int make_plan(const df_inst_t *inst, int32_t n_inst, Plan *P, int accel = 0) {
     P->norm0.clear();
     for (int i = 0; i < n_inst; ++i) {
         P->norm0.push_back(norms);
-        norms += 2 * (size_t)mix_blocks(P->shape[i]);
+        norms += 2 * (size_t)std::max(mix_blocks(P->shape[i]), P->shape[i].n_nu);
     }
     off += norms * sizeof(double);
     P->readback = off - g.ints;
@@ -405,8 +408,12 @@ int stage_gamma_prep(const df_inst_t &p, const Plan &P, int i, void *ws, bool ze
     return DF_OK;
 }
 
-int stage_sigma(const df_inst_t &p, const Shape &s, const double *w, const double *gr,
-                double *part, hipStream_t st) {
+// Sigma~ from W: sigma_calc and, with sigma given, the mixing step and its norm
+// partials.  One launch, or two where the bosonic frequencies are split into chunks.
+// sym: only the symmetry-reduced entries of W are valid (its tables in the workspace).
+int stage_sigma(const df_inst_t &p, const Shape &s, void *ws, size_t base, const Layout &L,
+                const double *w, bool sym, double *sigma_calc, double *sigma, double alpha,
+                double *norm, hipStream_t st) {
     SigmaArgs a{};
     a.grid = grid_of(s);
     a.n_nu = s.n_nu;
@@ -415,23 +422,25 @@ int stage_sigma(const df_inst_t &p, const Shape &s, const double *w, const doubl
     a.n_chunks = s.n_chunks;
     a.beta = p.beta;
     a.w = w;
-    a.gr = gr;
-    a.part = part;
-    HIPCHK(launch_sigma_part(a, st));
-    return DF_OK;
-}
-
-int stage_reduce_mix(const Shape &s, const double *part, double *sigma_calc, double *sigma,
-                     double alpha, double *norm, hipStream_t st) {
-    ReduceMixArgs a{};
-    a.count = (size_t)s.n_nu * s.N;
-    a.n_chunks = s.n_chunks;
+    a.gr = at<double>(ws, base + L.gr);
+    a.part = at<double>(ws, base + L.part);
+    if (sym) a.qrep = at<int>(ws, base + L.qrep);
+    a.im0 = s.im0;
     a.alpha = alpha;
-    a.part = part;
     a.sigma_calc = sigma_calc;
     a.sigma = sigma;
     a.norm_part = norm;
-    HIPCHK(launch_reduce_mix(a, mix_blocks(s), st));
+    HIPCHK(launch_sigma_part(a, st));
+    if (s.n_chunks == 1) return DF_OK;
+    ReduceMixArgs r{};
+    r.count = (size_t)s.n_nu * s.N;
+    r.n_chunks = s.n_chunks;
+    r.alpha = alpha;
+    r.part = a.part;
+    r.sigma_calc = sigma_calc;
+    r.sigma = sigma;
+    r.norm_part = norm;
+    HIPCHK(launch_reduce_mix(r, mix_blocks(s), st));
     return DF_OK;
 }
 
@@ -703,22 +712,14 @@ int queue_fused_iteration(const df_inst_t *inst, const Plan &P, const Fused &F,
         const Shape &s = P.shape[i];
         const Layout &L = P.lay[i];
         const size_t b = P.base[i];
-        double *gr = at<double>(ws, b + L.gr);
-        double *part = at<double>(ws, b + L.part);
-        double *w = inst[i].w ? inst[i].w : at<double>(ws, b + L.w);
-        if (o.symmetry) {
-            rc = stage_sym_expand(s, ws, b, L, w, inst[i].logdet, inst[i].status, st);
-            if (rc != DF_OK) return rc;
-        }
-        rc = stage_sigma(inst[i], s, w, gr, part, st);
-        if (rc != DF_OK) return rc;
-        if (o.accel > 0) {
-            // F(x) only; the accelerated step follows outside this sequence
-            rc = stage_reduce_mix(s, part, at<double>(ws, b + L.fx), nullptr, 0.0, nullptr, st);
-        } else {
-            rc = stage_reduce_mix(s, part, inst[i].sigma_calc, inst[i].sigma, o.mix,
-                                  norm_part(P, ws, i), st);
-        }
+        const double *w = inst[i].w ? inst[i].w : at<double>(ws, b + L.w);
+        // (accelerated: F(x) only, the step follows outside this sequence)
+        if (o.accel > 0)
+            rc = stage_sigma(inst[i], s, ws, b, L, w, o.symmetry != 0, at<double>(ws, b + L.fx), nullptr,
+                             0.0, nullptr, st);
+        else
+            rc = stage_sigma(inst[i], s, ws, b, L, w, o.symmetry != 0, inst[i].sigma_calc, inst[i].sigma,
+                             o.mix, norm_part(P, ws, i), st);
         if (rc != DF_OK) return rc;
     }
     return DF_OK;
@@ -1080,12 +1081,10 @@ int df_sigma(const df_inst_t *inst, int32_t n_inst, void *ws, size_t ws_bytes, d
         const Layout &L = P.lay[i];
         const size_t b = P.base[i];
         double *gr = at<double>(ws, b + L.gr);
-        double *part = at<double>(ws, b + L.part);
         rc = stage_transform_gd(s, inst[i].gd, gr, st);
         if (rc != DF_OK) return rc;
-        rc = stage_sigma(inst[i], s, inst[i].w, gr, part, st);
-        if (rc != DF_OK) return rc;
-        rc = stage_reduce_mix(s, part, inst[i].sigma_calc, nullptr, 0.0, nullptr, st);
+        rc = stage_sigma(inst[i], s, ws, b, L, inst[i].w, false, inst[i].sigma_calc, nullptr, 0.0, nullptr,
+                         st);
         if (rc != DF_OK) return rc;
     }
     return DF_OK;
@@ -1256,7 +1255,7 @@ int df_iterate(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts, int
         std::vector<int> next;
         for (int i : act) {
             double diff = 0.0;
-            const bool finite = norm_diff(hnorms + P.norm0[i], mix_blocks(P.shape[i]), &diff);
+            const bool finite = norm_diff(hnorms + P.norm0[i], norm_parts(P.shape[i], opts->accel), &diff);
             last[i] = diff;
             fell_back[i] = hints[kIntsInst + i] != 0;
             if (!finite || !isfinite(diff)) {
@@ -1285,6 +1284,19 @@ int df_iterate(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts, int
         act.swap(next);
     }
     cleanup();
+    if (opts->symmetry) {
+        // the entries of the outputs that the reduced ladders leave out
+        bool any = false;
+        for (int i = 0; i < n_inst; ++i) {
+            if (!inst[i].w && !inst[i].logdet && !inst[i].status) continue;
+            const Layout &L = P.lay[i];
+            double *w = inst[i].w ? inst[i].w : at<double>(ws, P.base[i] + L.w);
+            rc = stage_sym_expand(P.shape[i], ws, P.base[i], L, w, inst[i].logdet, inst[i].status, st);
+            if (rc != DF_OK) return rc;
+            any = true;
+        }
+        if (any && hipStreamSynchronize(st) != hipSuccess) return DF_E_HIP;
+    }
     if (slots > 0) {
         // sigma_calc (F of the last iterate) where the caller asked for it
         for (int i = 0; i < n_inst; ++i) {

@@ -98,20 +98,49 @@ __global__ __launch_bounds__(P::T) void k_bubble(BubbleArgs a) {
 }
 
 // ------------------------------------------------------------------------
+// sigma_calc <- s and sigma <- (1 - alpha) sigma + alpha s of one element (each may
+// be null); |sigma_new - sigma_old|^2 and |sigma_new|^2 are added to dn, nn.
+// ------------------------------------------------------------------------
+__device__ __forceinline__ void mix_element(double *sigma_calc, double *sigma, double alpha, size_t e,
+                                            cd s, double &dn, double &nn) {
+    if (sigma_calc) st(sigma_calc, e, s);
+    if (!sigma) return;
+    const cd old = ld(sigma, e);
+    const cd nw = {(1.0 - alpha) * old.re + alpha * s.re, (1.0 - alpha) * old.im + alpha * s.im};
+    st(sigma, e, nw);
+    const double dr = nw.re - old.re, di = nw.im - old.im;
+    dn += dr * dr + di * di;
+    nn += nw.re * nw.re + nw.im * nw.im;
+}
+
+// ------------------------------------------------------------------------
 // Partial dual self-energy over one chunk of bosonic frequencies:
 //   part[chunk][n][k] = (T/2) FFT_r[ sum_{m in chunk} v_{m,n}(-r) gr_{n+m}(r) ](k),
 //   v_{m,n} = IFFT_q[ 3 W^m_{m,n} + W^d_{m,n} ].
 // One block per (n, chunk).  The accumulator B(r) = sum_m v(r) gr(-r) lives in
 // registers where the inverse FFT's last pass leaves v, and FFT_r[B(-r)](k) is the
 // transform of B with the other sign, whose first pass takes it from there.
+// ALL, one chunk: the block has the whole sum and mixes it itself, without the launch
+// and the pass over memory of k_reduce_mix (8 x 8, n_nu 16, n_om 1, an iteration of
+// the loop without a graph 58 -> 41 us).
+// RED: W of a symmetry-reduced ladder, solved at m index >= im0 and representative
+// q only.  The rest is read from there (k_sym_expand's rule) instead of being
+// written out and read back in every iteration (32 x 32, n_nu 64, n_om 31: 19.5 us of
+// k_sym_expand per iteration, now once per call).
+// Each switch is a build of its own: the mixing code in the chunked build cost
+// 64 x 64, n_nu 128 88 -> 109 us.
 // ------------------------------------------------------------------------
-template <typename P, typename Q>
+template <typename P, typename Q, bool RED, bool ALL>
 __global__ __launch_bounds__(P::T) void k_sigma_part(SigmaArgs a) {
     constexpr int LAST = P::PASSES - 1, V = P::lines_per_thread(LAST), R = 1 << P::bits(LAST);
     __shared__ cd X[P::LDS_N > Q::LDS_N ? P::LDS_N : Q::LDS_N];
     __shared__ cd tw[P::nk];
+    __shared__ unsigned short rep[RED ? P::N : 1];
+    __shared__ double red[2][P::T / 64];
     const int n = blockIdx.x, chunk = blockIdx.y;
     fft_twiddles<P>(tw);
+    if constexpr (RED)
+        for (int q = threadIdx.x; q < P::N; q += P::T) rep[q] = (unsigned short)a.qrep[q];
     cd acc[V][R];
 #pragma unroll
     for (int v = 0; v < V; ++v)
@@ -124,21 +153,30 @@ __global__ __launch_bounds__(P::T) void k_sigma_part(SigmaArgs a) {
     for (int im = m_lo; im < m_hi; ++im) {
         const int n2 = n + im - h;
         if (n2 < 0 || n2 >= a.n_nu) continue;
-        const double *wd = a.w + 2 * ((size_t)im * a.n_nu + n) * P::N, *wm = wd + 2 * plane;
+        const bool flip = RED && im < a.im0;               // conjugate of -Om at -nu
+        const int ims = flip ? a.n_om - 1 - im : im, ns = flip ? a.n_nu - 1 - n : n;
+        const double sg = flip ? -1.0 : 1.0;
+        const double *wd = a.w + 2 * ((size_t)ims * a.n_nu + ns) * P::N, *wm = wd + 2 * plane;
         const double *gb = a.gr + 2 * (size_t)n2 * P::N;
         __syncthreads();
         fft_run<P, true>(X, tw,
                          [&](int q, int) __attribute__((always_inline)) {
-                             const cd d = ld(wd, q), m = ld(wm, q);
-                             return cd{fma(3.0, m.re, d.re), fma(3.0, m.im, d.im)};
+                             const int qs = RED ? (int)rep[q] : q;
+                             const cd d = ld(wd, qs), m = ld(wm, qs);
+                             const cd v = {fma(3.0, m.re, d.re), fma(3.0, m.im, d.im)};
+                             return RED ? cd{v.re, sg * v.im} : v;
                          },
                          [&](int v, int i, int, int rr, cd x) __attribute__((always_inline)) {
                              acc[v][i] = fma_c(acc[v][i], x, ld(gb, rr));
                          });
     }
     const double sc = 0.5 / (a.beta * (double)P::N);      // T/2 and the inverse FFT's 1/N
-    double *out = a.part + 2 * ((size_t)chunk * a.n_nu + n) * P::N;
-    auto store = [&](int, int, int k, int, cd x) __attribute__((always_inline)) { st(out, k, scale(x, sc)); };
+    double dn = 0.0, nn = 0.0;
+    double *out = ALL ? nullptr : a.part + 2 * ((size_t)chunk * a.n_nu + n) * P::N;
+    auto store = [&](int, int, int k, int, cd x) __attribute__((always_inline)) {
+        if constexpr (ALL) mix_element(a.sigma_calc, a.sigma, a.alpha, (size_t)n * P::N + k, scale(x, sc), dn, nn);
+        else st(out, k, scale(x, sc));
+    };
     if constexpr (P::PASSES == 1) {
         if (threadIdx.x == 0) {
             fft_reg<R, true>(acc[0]);
@@ -150,6 +188,24 @@ __global__ __launch_bounds__(P::T) void k_sigma_part(SigmaArgs a) {
         fft_first_reg<Q, true>(X, tw, acc);
         fft_middle<Q, 1, true>(X, tw);
         fft_last<Q, true>(X, store);
+    }
+    if (!ALL || !a.sigma) return;
+    for (int x = 32; x > 0; x >>= 1) {
+        dn += __shfl_xor(dn, x, 64);
+        nn += __shfl_xor(nn, x, 64);
+    }
+    if ((threadIdx.x & 63) == 0) {
+        red[0][threadIdx.x >> 6] = dn;
+        red[1][threadIdx.x >> 6] = nn;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int x = 1; x < P::T / 64; ++x) {
+            dn += red[0][x];
+            nn += red[1][x];
+        }
+        a.norm_part[2 * n] = dn;
+        a.norm_part[2 * n + 1] = nn;
     }
 }
 
@@ -166,16 +222,7 @@ __global__ __launch_bounds__(256) void k_reduce_mix(ReduceMixArgs a) {
          e += (size_t)gridDim.x * blockDim.x) {
         cd s = ld(a.part, e);
         for (int c = 1; c < a.n_chunks; ++c) s = s + ld(a.part, (size_t)c * M + e);
-        if (a.sigma_calc) st(a.sigma_calc, e, s);
-        if (a.sigma) {
-            const cd old = ld(a.sigma, e);
-            const cd nw = {(1.0 - a.alpha) * old.re + a.alpha * s.re,
-                           (1.0 - a.alpha) * old.im + a.alpha * s.im};
-            st(a.sigma, e, nw);
-            const double dr = nw.re - old.re, di = nw.im - old.im;
-            dn += dr * dr + di * di;
-            nn += nw.re * nw.re + nw.im * nw.im;
-        }
+        mix_element(a.sigma_calc, a.sigma, a.alpha, e, s, dn, nn);
     }
     if (!a.sigma) return;
     red[0][threadIdx.x] = dn;
@@ -307,15 +354,22 @@ hipError_t launch_bubble(const BubbleArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
+template <typename P, typename Q> static hipError_t launch_sigma_grid(const SigmaArgs &a, hipStream_t s) {
+    const dim3 grid(a.n_nu, a.n_chunks), block(P::T);
+    const bool all = a.n_chunks == 1;
+    if (a.qrep && all) hipLaunchKernelGGL((k_sigma_part<P, Q, true, true>), grid, block, 0, s, a);
+    else if (a.qrep) hipLaunchKernelGGL((k_sigma_part<P, Q, true, false>), grid, block, 0, s, a);
+    else if (all) hipLaunchKernelGGL((k_sigma_part<P, Q, false, true>), grid, block, 0, s, a);
+    else hipLaunchKernelGGL((k_sigma_part<P, Q, false, false>), grid, block, 0, s, a);
+    return hipGetLastError();
+}
+
 hipError_t launch_sigma_part(const SigmaArgs &a, hipStream_t s) {
-#define DF_CASE(D, LK)                                                                                  \
-    case D * 16 + LK:                                                                                   \
-        hipLaunchKernelGGL((k_sigma_part<Fft<D, LK>, Fft<D, LK, true>>), dim3(a.n_nu, a.n_chunks),  \
-                           dim3(Fft<D, LK>::T), 0, s, a);                                             \
-        break;
+#define DF_CASE(D, LK) \
+    case D * 16 + LK: return launch_sigma_grid<Fft<D, LK>, Fft<D, LK, true>>(a, s);
     DF_FFT_SWITCH(DF_CASE)
 #undef DF_CASE
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_reduce_mix(const ReduceMixArgs &a, int blocks, hipStream_t s) {

@@ -4,8 +4,8 @@
 //
 // Bound: LDS traffic and the barriers between passes, at two work-groups per CU
 // (an N = 4096 array takes 70 KB).  A line of an axis of nk <= 16 points is one
-// radix-nk pass, one of 32 or 64 points two (8 x 4, 8 x 8): three LDS round trips
-// for 64 x 64 and two for 16^3, where radix-4 passes from and to LDS took six.
+// radix-nk pass (on the 16 x 16 grid two of radix 4), one of 32 or 64 points two (8 x
+// 4, 8 x 8): three LDS round trips for 64 x 64 and two for 16^3, where radix-4 passes from and to LDS took six.
 // The first pass takes its points from the caller (global memory) and the last
 // one hands them over, so input and output add none.  Against radix-4 passes on LDS
 // (256 to 1024 threads): bubble at 16^3, n_nu 96, n_om 23 68.6 -> 44.0 us (145 MB of chi
@@ -93,16 +93,19 @@ template <int R, bool INV> __device__ __forceinline__ void fft_reg(cd (&x)[R]) {
 // fewer lines leaves some idle).
 template <int D_, int LK_, bool REV = false, int TMIN = 64> struct Fft {
     static constexpr int D = D_, LK = LK_, nk = 1 << LK, N = 1 << (D * LK);
-    static constexpr int S = LK > 4 ? 2 : 1;                       // passes per axis
-    static constexpr int LA = S == 1 ? LK : (LK == 5 && REV ? 2 : 3), LB = S == 1 ? 0 : LK - LA;
+    // passes per axis; the larger radix.  16 x 16: two radix-4 passes, since one of
+    // radix 16 gives work to 16 lanes only (Schwinger-Dyson with the transform of G~,
+    // n_nu 48, n_om 7: 16.1 -> 8.3 us; 16^3 has 256 lines and keeps radix 16)
+    static constexpr int S = LK > 4 || (LK == 4 && D == 2) ? 2 : 1;
+    static constexpr int LMAX = S == 1 ? LK : (LK == 4 ? 2 : 3);
+    static constexpr int LA = S == 1 ? LK : (LK == 5 && REV ? 2 : LMAX), LB = S == 1 ? 0 : LK - LA;
     static constexpr int RA = 1 << LA, RB = 1 << LB;
     static constexpr int PASSES = D * S;
     // threads of a work-group: one line of the larger radix each
-    static constexpr int LMAX = S == 1 ? LK : 3;
     static constexpr int T = (N >> LMAX) < TMIN ? TMIN : (N >> LMAX);
     // one complex of padding per 2^PB: the lanes' contiguous lines of axis 0 then
     // fall in different banks
-    static constexpr int PB = S == 1 ? LK : LK - 3;
+    static constexpr int PB = S == 1 ? LK : LK - LMAX;
     static constexpr int LDS_N = N + (N >> PB);
     static __device__ __forceinline__ int pad(int p) { return p + (p >> PB); }
     // pass i: its axis, whether it is the second of the axis, and the bits of the

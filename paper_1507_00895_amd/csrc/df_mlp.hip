@@ -11,7 +11,7 @@
 // squared error with its gradient (last layer), multiplication by SiLU'(Z) of
 // the previous layer (backward), column sums of A (the bias gradient), split-K
 // partial sums reduced in a fixed order by a second kernel.  Batch 4096, widths
-// 132-256-256-256-96: loss and gradients 137 us; 1219 us with 16-deep chunks of scalar
+// 132-256-256-256-96: loss and gradients 101 us; 1219 us with 16-deep chunks of scalar
 // loads (a product 30 us) and a column-sum kernel of one work-group per 64 columns
 // (four of 217 us).
 #include <math.h>
@@ -100,8 +100,9 @@ template <int T, bool KMAJOR, bool VEC> struct TileLoad {
 
 // AT / BT: the operand is k-major in memory (A(m, k) = A[k lda + m], B(k, n) =
 // B[k ldb + n]); else A[m lda + k], B[n ldb + k].
+// Work-group (bx, by) of the tiles of split bz of nz.
 template <int T, bool AT, bool BT, bool VEC>
-__global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs g) {
+__device__ __forceinline__ void gemm_item(const GemmArgs &g, int bx, int by, int bz, int nz, int n_loss) {
     constexpr int F = T / 32;                      // MFMA tiles per wave and direction
     __shared__ __align__(16) TileLds<T, AT> As;
     __shared__ __align__(16) TileLds<T, BT> Bs;
@@ -109,10 +110,10 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs g) {
     const int tid = threadIdx.x;
     const int w = tid >> 6, l = tid & 63, lj = l & 15, lg = l >> 4;
     const int wm = (w >> 1) * (T / 2), wn = (w & 1) * (T / 2);
-    const int m0 = blockIdx.y * T, n0 = blockIdx.x * T;
-    const int kbeg = blockIdx.z * g.kchunk;
+    const int m0 = by * T, n0 = bx * T;
+    const int kbeg = bz * g.kchunk;
     const int kend = min(g.K, kbeg + g.kchunk);
-    const bool sums = g.asum && blockIdx.x == 0;
+    const bool sums = g.asum && bx == 0;
     f4 acc[F][F];
 #pragma unroll
     for (int i = 0; i < F; ++i)
@@ -161,7 +162,7 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs g) {
         if (tid < T && m0 + tid < g.M) {
             float s = 0.f;
             for (int p = 0; p < 256 / T; ++p) s += r[p * T + tid];
-            if (gridDim.z > 1) g.part[(size_t)gridDim.z * g.M * g.N + (size_t)blockIdx.z * g.M + m0 + tid] = s;
+            if (nz > 1) g.part[(size_t)nz * g.M * g.N + (size_t)bz * g.M + m0 + tid] = s;
             else g.asum[m0 + tid] = s;
         }
     }
@@ -178,8 +179,8 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs g) {
                 const int n = n0 + wn + 16 * j + lj;
                 if (m >= g.M || n >= g.N) continue;
                 float v = acc[i][j][r];
-                if (gridDim.z > 1) {
-                    g.part[((size_t)blockIdx.z * g.M + m) * g.N + n] = v;
+                if (nz > 1) {
+                    g.part[((size_t)bz * g.M + m) * g.N + n] = v;
                     continue;
                 }
                 const size_t o = (size_t)m * g.ldc + n;
@@ -200,19 +201,44 @@ __global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs g) {
         if (l == 0) red[w][0] = sq;
         __syncthreads();
         if (tid == 0)
-            g.lpart[blockIdx.y * gridDim.x + blockIdx.x] = (red[0][0] + red[1][0]) + (red[2][0] + red[3][0]);
+            g.lpart[n_loss] = (red[0][0] + red[1][0]) + (red[2][0] + red[3][0]);
     }
 }
 
-// C[m][n] = sum over splits of part[s][m][n], in split order; the same for the
-// column sums db [M] where wanted.  Block 0 also finishes the loss (n_loss block
-// partials, count elements) where wanted.
+template <int T, bool AT, bool BT, bool VEC>
+__global__ __launch_bounds__(256) void k_gemm_f32(GemmArgs g) {
+    gemm_item<T, AT, BT, VEC>(g, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.z,
+                              blockIdx.y * gridDim.x + blockIdx.x);
+}
+
+// The weight gradients of several layers in one launch (A and B k-major): one alone
+// is too few work-groups to fill the chip to its end.  Batch 4096, widths
+// 132-256-256-256-96: four launches and their four sums 64 us, one
+// and one 32 us.
+struct GemmGroup {
+    GemmArgs p[DF_MLP_MAX_LAYERS];
+    int tx[DF_MLP_MAX_LAYERS], ty[DF_MLP_MAX_LAYERS];   // tiles per split
+    int wg0[DF_MLP_MAX_LAYERS + 1];                     // first work-group of each
+    int n, splits;
+};
+template <int T, bool VEC>
+__global__ __launch_bounds__(256) void k_gemm_group(GemmGroup a) {
+    int i = 0;
+    while (i + 1 < a.n && (int)blockIdx.x >= a.wg0[i + 1]) ++i;
+    const int u = (int)blockIdx.x - a.wg0[i], bx = u % a.tx[i], r = u / a.tx[i];
+    gemm_item<T, true, true, VEC>(a.p[i], bx, r % a.ty[i], r / a.ty[i], a.splits, 0);
+}
+
+// Per layer C[m][n] = sum over splits of part[s][m][n], in split order, and the same
+// for the column sums db [M].  Block 0 also finishes the loss (n_loss block partials,
+// count elements) where wanted.
 struct SumSplitsArgs {
-    const float *part;
-    int splits, M, N;
-    float *C;
-    int ldc;
-    float *db;
+    const float *part[DF_MLP_MAX_LAYERS];
+    int M[DF_MLP_MAX_LAYERS], N[DF_MLP_MAX_LAYERS];
+    float *C[DF_MLP_MAX_LAYERS];                        // rows of N
+    float *db[DF_MLP_MAX_LAYERS];
+    int wg0[DF_MLP_MAX_LAYERS + 1];                     // first work-group of each layer
+    int n, splits;
     const float *lpart;
     int n_loss;
     float count;
@@ -231,18 +257,23 @@ __device__ __forceinline__ void finish_loss(const float *part, int n, float coun
     if (threadIdx.x == 0) *loss = red[0] / count;
 }
 __global__ __launch_bounds__(256) void k_sum_splits(SumSplitsArgs a) {
-    const size_t tot = (size_t)a.M * a.N;
-    for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < tot;
-         e += (size_t)gridDim.x * blockDim.x) {
+    int i = 0;
+    while (i + 1 < a.n && (int)blockIdx.x >= a.wg0[i + 1]) ++i;
+    const size_t tot = (size_t)a.M[i] * a.N[i];
+    const size_t e = (size_t)(blockIdx.x - a.wg0[i]) * 256 + threadIdx.x;
+    const float *part = a.part[i];
+    // the weights, then the bias
+    if (e < tot) {
         float s = 0.f;
 #pragma unroll 8
-        for (int z = 0; z < a.splits; ++z) s += a.part[(size_t)z * tot + e];
-        a.C[(e / a.N) * a.ldc + e % a.N] = s;
-    }
-    for (int m = blockIdx.x * blockDim.x + threadIdx.x; m < a.M; m += gridDim.x * blockDim.x) {
+        for (int z = 0; z < a.splits; ++z) s += part[(size_t)z * tot + e];
+        a.C[i][e] = s;
+    } else if (e < tot + a.M[i]) {
+        const size_t m = e - tot;
         float s = 0.f;
-        for (int z = 0; z < a.splits; ++z) s += a.part[a.splits * tot + (size_t)z * a.M + m];
-        a.db[m] = s;
+#pragma unroll 8
+        for (int z = 0; z < a.splits; ++z) s += part[a.splits * tot + (size_t)z * a.M[i] + m];
+        a.db[i][m] = s;
     }
     if (a.loss && blockIdx.x == 0) finish_loss(a.lpart, a.n_loss, a.count, a.loss);
 }
@@ -284,20 +315,15 @@ size_t n_params(int32_t L, const int32_t *d) {
     return c;
 }
 
-int max_width(int32_t L, const int32_t *d) {
-    int m = 0;
-    for (int l = 0; l <= L; ++l) m = d[l] > m ? d[l] : m;
-    return m;
-}
-
 int splits_for(int K) {
     int s = (K + 255) / 256;
     return s < 1 ? 1 : (s > 64 ? 64 : s);
 }
 
-// workspace: Z[l], Y[l] for l = 1..L (batch x d_l), dZ ping-pong, split partials, loss partials
+// workspace: Z[l], Y[l] for l = 1..L (batch x d_l; the backward pass leaves dZ_l in Z_l),
+// split partials of every layer, loss partials
 struct MlpWs {
-    size_t z[DF_MLP_MAX_LAYERS + 1], y[DF_MLP_MAX_LAYERS + 1], dz[2], part, lpart, total;
+    size_t z[DF_MLP_MAX_LAYERS + 1], y[DF_MLP_MAX_LAYERS + 1], part, lpart, total;
 };
 
 MlpWs mlp_ws(int32_t L, const int32_t *d, int32_t batch) {
@@ -309,13 +335,8 @@ MlpWs mlp_ws(int32_t L, const int32_t *d, int32_t batch) {
         w.y[l] = o;
         o = alup(o + (size_t)batch * d[l] * sizeof(float));
     }
-    const int mw = max_width(L, d);
-    for (int k = 0; k < 2; ++k) {
-        w.dz[k] = o;
-        o = alup(o + (size_t)batch * mw * sizeof(float));
-    }
     w.part = o;
-    o = alup(o + (size_t)splits_for(batch) * ((size_t)mw * mw + mw) * sizeof(float));
+    o = alup(o + (size_t)splits_for(batch) * n_params(L, d) * sizeof(float));
     w.lpart = o;
     o = alup(o + (size_t)((batch + 31) / 32) * ((d[L] + 31) / 32) * sizeof(float));
     w.total = o;
@@ -328,7 +349,8 @@ template <typename T> T *wsp(void *ws, size_t off) {
 
 // The tile: 64, unless that gives fewer than four work-groups per CU (of 256), where
 // the loads of too few waves are in flight - then 32.  Batch 4096, width 256, loss
-// and gradients: 162 us with 64 x 64 tiles (256 work-groups), 137 with 32 x 32;
+// and gradients (a launch per product): 162 us with 64 x 64 tiles (256 work-groups), 137
+// with 32 x 32;
 // batch 1024 forward: 64 work-groups of 64 x 64, 256 of 32 x 32 (28 us).
 int gemm_tile(int M, int N, int splits) {
     return (long)((M + 63) / 64) * ((N + 63) / 64) * splits >= 1024 ? 64 : 32;
@@ -361,7 +383,7 @@ hipError_t gemm(GemmArgs g, hipStream_t st, int splits = 1) {
     return hipGetLastError();
 }
 
-// T (targets) set: the last layer leaves dZ_L = 2 (Y - T) / count in its place and
+// T (targets) set: the last layer leaves dZ_L = 2 (Y - T) / count in Z_L's place and
 // the partial sums of the loss in the workspace
 int forward_impl(int32_t L, const int32_t *d, const float *params, const float *X, int32_t batch,
                  float *Yout, const float *T, void *ws, const MlpWs &w, hipStream_t st) {
@@ -389,7 +411,7 @@ int forward_impl(int32_t L, const int32_t *d, const float *params, const float *
         if (last && T) {
             g.T = T;
             g.lpart = wsp<float>(ws, w.lpart);
-            g.C = wsp<float>(ws, w.dz[L & 1]);
+            g.C = wsp<float>(ws, w.z[L]);
         }
         if (gemm<false, false>(g, st) != hipSuccess) return DF_E_HIP;
         in = g.C;
@@ -450,64 +472,81 @@ int df_mlp_loss_grad(int32_t n_layers, const int32_t *dims, const float *params,
     off[0] = 0;
     for (int l = 0; l < L; ++l) off[l + 1] = off[l] + (size_t)d[l + 1] * d[l] + d[l + 1];
 
-    for (int l = L - 1; l >= 0; --l) {
-        const float *Xl = (l == 0) ? X : wsp<float>(ws, w.y[l]);
-        float *dW = grads + off[l];
-        float *db = dW + (size_t)d[l + 1] * d[l];
-        const float *dZ = wsp<float>(ws, w.dz[(l + 1) & 1]);
-        // dW_l = dZ^T X_l (split over the batch), db_l = column sums of dZ
-        GemmArgs g{};
-        g.M = d[l + 1];
-        g.N = d[l];
-        g.K = batch;
-        g.A = dZ;
-        g.lda = d[l + 1];
-        g.B = Xl;
-        g.ldb = d[l];
-        g.C = dW;
-        g.ldc = d[l];
-        g.asum = db;
-        g.part = wsp<float>(ws, w.part);
-        if (gemm<true, true>(g, st, splits_for(batch)) != hipSuccess) return DF_E_HIP;
-        int kchunk;
-        const int splits = gemm_splits(batch, splits_for(batch), &kchunk);
-        float *want_loss = l == L - 1 ? loss : nullptr;
-        if (splits > 1) {
-            SumSplitsArgs r{};
-            r.part = g.part;
-            r.splits = splits;
-            r.M = g.M;
-            r.N = g.N;
-            r.C = dW;
-            r.ldc = d[l];
-            r.db = db;
-            r.lpart = wsp<float>(ws, w.lpart);
-            r.n_loss = n_loss;
-            r.count = count;
-            r.loss = want_loss;
-            const size_t tot = (size_t)g.M * g.N;
-            int blocks = (int)((tot + 255) / 256);
-            if (blocks > 2048) blocks = 2048;
-            hipLaunchKernelGGL(k_sum_splits, dim3(blocks), dim3(256), 0, st, r);
-        } else if (want_loss) {
-            hipLaunchKernelGGL(k_loss, dim3(1), dim3(256), 0, st, wsp<float>(ws, w.lpart), n_loss, count, loss);
-        }
-        if (hipGetLastError() != hipSuccess) return DF_E_HIP;
-        if (l == 0) break;
-        // dZ_l = (dZ_{l+1} W_l) * SiLU'(Z_l)
+    // dZ_l = (dZ_{l+1} W_l) * SiLU'(Z_l), in the place of Z_l
+    for (int l = L - 1; l >= 1; --l) {
         GemmArgs h{};
         h.M = batch;
         h.N = d[l];
         h.K = d[l + 1];
-        h.A = dZ;
+        h.A = wsp<float>(ws, w.z[l + 1]);
         h.lda = d[l + 1];
         h.B = params + off[l];
         h.ldb = d[l];
-        h.C = wsp<float>(ws, w.dz[l & 1]);
+        h.C = wsp<float>(ws, w.z[l]);
         h.ldc = d[l];
-        h.dz = wsp<float>(ws, w.z[l]);
+        h.dz = h.C;
         if (gemm<false, true>(h, st) != hipSuccess) return DF_E_HIP;
     }
+    // dW_l = dZ^T X_l (split over the batch), db_l = column sums of dZ: the layers of one
+    // tile size and alignment in one launch
+    int kchunk;
+    const int splits = gemm_splits(batch, splits_for(batch), &kchunk);
+    for (int kind = 0; kind < 4; ++kind) {
+        const int t = kind & 1 ? 64 : 32;
+        const bool vec = (kind & 2) != 0;
+        GemmGroup G{};
+        G.splits = splits;
+        for (int l = 0; l < L; ++l) {
+            GemmArgs g{};
+            g.M = d[l + 1];
+            g.N = d[l];
+            g.K = batch;
+            g.A = wsp<float>(ws, w.z[l + 1]);
+            g.lda = d[l + 1];
+            g.B = l == 0 ? X : wsp<float>(ws, w.y[l]);
+            g.ldb = d[l];
+            g.C = grads + off[l];
+            g.ldc = d[l];
+            g.asum = g.C + (size_t)d[l + 1] * d[l];
+            g.part = wsp<float>(ws, w.part) + (size_t)splits * off[l];
+            g.kchunk = kchunk;
+            if (gemm_tile(g.M, g.N, splits) != t) continue;
+            if ((aligned16(g.A, g.lda) && aligned16(g.B, g.ldb)) != vec) continue;
+            G.p[G.n] = g;
+            G.tx[G.n] = (g.N + t - 1) / t;
+            G.ty[G.n] = (g.M + t - 1) / t;
+            G.wg0[G.n + 1] = G.wg0[G.n] + G.tx[G.n] * G.ty[G.n] * splits;
+            ++G.n;
+        }
+        if (G.n == 0) continue;
+        const dim3 grid(G.wg0[G.n]);
+        if (t == 64 && vec) hipLaunchKernelGGL((k_gemm_group<64, true>), grid, dim3(256), 0, st, G);
+        else if (t == 64) hipLaunchKernelGGL((k_gemm_group<64, false>), grid, dim3(256), 0, st, G);
+        else if (vec) hipLaunchKernelGGL((k_gemm_group<32, true>), grid, dim3(256), 0, st, G);
+        else hipLaunchKernelGGL((k_gemm_group<32, false>), grid, dim3(256), 0, st, G);
+        if (hipGetLastError() != hipSuccess) return DF_E_HIP;
+    }
+    if (splits > 1) {
+        SumSplitsArgs r{};
+        r.n = L;
+        r.splits = splits;
+        for (int l = 0; l < L; ++l) {
+            r.M[l] = d[l + 1];
+            r.N[l] = d[l];
+            r.C[l] = grads + off[l];
+            r.db[l] = r.C[l] + (size_t)d[l + 1] * d[l];
+            r.part[l] = wsp<float>(ws, w.part) + (size_t)splits * off[l];
+            r.wg0[l + 1] = r.wg0[l] + (int)((off[l + 1] - off[l] + 255) / 256);
+        }
+        r.lpart = wsp<float>(ws, w.lpart);
+        r.n_loss = n_loss;
+        r.count = count;
+        r.loss = loss;
+        hipLaunchKernelGGL(k_sum_splits, dim3(r.wg0[L]), dim3(256), 0, st, r);
+    } else if (loss) {
+        hipLaunchKernelGGL(k_loss, dim3(1), dim3(256), 0, st, wsp<float>(ws, w.lpart), n_loss, count, loss);
+    }
+    if (hipGetLastError() != hipSuccess) return DF_E_HIP;
     return DF_OK;
 }
 

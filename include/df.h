@@ -33,8 +33,9 @@
  * Ownership: the caller allocates every buffer, the workspace included (size
  * it with df_workspace_size; it must be 256-byte aligned).  The library never
  * allocates or frees caller memory; it keeps no state between calls apart
- * from compiled kernels and the autotuner's table of ladder kernel choices
- * (df_autotune).  Calls are asynchronous on the given stream, except
+ * from compiled kernels, the autotuner's table of ladder kernel choices
+ * (df_autotune) and at most eight page-locked host buffers of 256 KiB, into which
+ * df_iterate reads back and which later calls of any thread reuse.  Calls are asynchronous on the given stream, except
  * df_iterate which synchronises that stream to read back the convergence
  * measure once per iteration, and df_autotune.  Calls on distinct workspaces may run
  * concurrently; two calls sharing a workspace must be ordered by the caller.
@@ -230,17 +231,19 @@ int df_autotune(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts, vo
 
 /* Name of the ladder kernel choice that calls for this n_nu and precision use
  * now, for prec DF_FP64, DF_FP32_REFINE or DF_FP32, written to the host buffer
- * name (NUL-terminated, name_len bytes at most).  A choice is a kernel build
- * ("gjb", "gjb_o3", "gjb_o4", "vector", "mfma" for FP64; "mixed", "mixed_o3",
- * "mixed_o4" for the refined class; "fp32", "fp32_o4", "fp32_o5" for FP32
- * alone), optionally with a launch shape: "@p1" / "@p2" = a persistent grid of
- * 1x / 2x the resident work-groups taking items from per-XCD counters (for
- * "gjb" and "gjb_o3"); without it, one work-group per item.  Sizes: every
- * class serves n_nu <= 128; the builds capped at three waves per SIMD ("_o3")
- * exist up to n_nu 64 (refined: 96), those at four or five ("_o4", "_o5") up
- * to 64.  A choice always belongs to the requested precision class; the
- * refined kernels hand their near-instability items to the FP64 kernel, and
- * every certified kernel its uncertified items to "vector", within the call. */
+ * name (NUL-terminated, name_len bytes at most).  A choice names the kernels of a
+ * launch: "vector", "mfma" (partial pivoting, every item) and "gjb", "gjb_o3",
+ * "gjb_o4" for FP64; "mixed", "mixed_o3", "mixed_o4" for the refined class; "fp32",
+ * "fp32_o4", "fp32_o5" for FP32 alone.  The "gjb" choices, with or without a launch
+ * shape ("@p1", "@p2" after "gjb" or "gjb_o3"), run the same kernels and keep their
+ * names for saved tables: screening (certificate), the symmetric block ladder for
+ * vertices symmetric in their two frequencies, and one kernel for the rest
+ * (certified elimination for other vertices, partial pivoting for uncertified
+ * items).  Sizes: every class serves n_nu <= 128; "_o3" exists up to n_nu 64
+ * (refined: 96), "_o4" and "_o5" up to 64.  A choice always belongs to the requested
+ * precision class; the refined kernels hand their near-instability items to the
+ * FP64 elimination, and every certified kernel its uncertified items to partial
+ * pivoting, within the call. */
 int df_ladder_variant(int32_t n_nu, int32_t prec, char *name, size_t name_len);
 
 /* Record a choice by hand, as df_autotune would: later calls for this n_nu and

@@ -21,7 +21,8 @@
  *       vertex arrays), chi~ the dual bubble of G~ (eq. dual_bubble)
  *       (momentum sums per site as in eq. dual_bubble; fermionic sums over the
  *       same n_nu window as the iteration; ch takes the density channel, sp the
- *       magnetic one; Gamma by Gaussian elimination with partial pivoting, FP64)
+ *       magnetic one; Gamma in FP64 by the block ladder of the certified items of
+ *       symmetric vertices, by elimination with partial pivoting for the rest)
  *
  * Every output may be NULL (not computed).  All pointers are device pointers;
  * the caller owns every buffer and the workspace (device memory, 256-byte

@@ -23,7 +23,7 @@ INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 ARCH = "gfx950"
 DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 # Ladder kernels: no machine-level loop-invariant code motion.  In the item
-# loop of the queue and persistent builds it hoisted values out of the loop
+# loop of the queue builds it hoisted values out of the loop
 # and held them across the whole unrolled item (the three-wave FP64 build went
 # from 0 to 260 bytes of spills per lane); the one-item builds are unchanged.
 LADDER_FLAGS = ["-mllvm", "-disable-machine-licm"]

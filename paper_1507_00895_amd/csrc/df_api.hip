@@ -236,10 +236,9 @@ Grid grid_of(const Shape &s) {
 // ---- ladder kernel choice ---------------------------------------------------
 // In order: the variant named by DF_LADDER_KERNEL (any name of the variant
 // table) when it serves this n_nu and precision; the autotuner's choice; the
-// default, which is the certified pivot-free blocked kernel on the matrix cores
-// (FP64, FP32 + FP64 refinement, or FP32), in its three-wave build where there
-// is one (four waves for FP32), whose uncertified items go to the
-// partial-pivoting kernel.
+// default, which is the certified pivot-free kernels on the matrix cores (FP64; FP32 +
+// FP64 refinement in its three-wave build where there is one; FP32 in its four-wave
+// build), whose uncertified items go to partial pivoting.
 int env_variant() {
     static int v = -2;
     if (v == -2) {

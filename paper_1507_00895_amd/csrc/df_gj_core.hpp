@@ -28,7 +28,7 @@
 //
 // Every function takes the thread index as an argument: the kernels pass an
 // opaque copy made per item, so that nothing derived from it is hoisted out
-// of a persistent work-group's item loop and held across the whole item.
+// of the queue kernels' item loop and held across the whole item.
 #pragma once
 
 #include "df_internal.hpp"
@@ -76,28 +76,6 @@ __device__ __forceinline__ double readlane_v(double v, int lane) {
 }
 __device__ __forceinline__ float readlane_v(float v, int lane) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), lane));
-}
-
-template <int K> __device__ __forceinline__ int quad_bcast_i(int v) {
-    return __builtin_amdgcn_mov_dpp(v, K | (K << 2) | (K << 4) | (K << 6), 0xf, 0xf, false);
-}
-__device__ __forceinline__ int quad_bcast_rt(int v, int k) {
-    switch (k) {
-        case 0: return quad_bcast_i<0>(v);
-        case 1: return quad_bcast_i<1>(v);
-        case 2: return quad_bcast_i<2>(v);
-        default: return quad_bcast_i<3>(v);
-    }
-}
-// value of quad lane k (k resolves statically once the caller's loop unrolls)
-__device__ __forceinline__ double quad_bcast_v(double v, int k) {
-    const long long b = __double_as_longlong(v);
-    const int lo = quad_bcast_rt((int)(b & 0xffffffffLL), k);
-    const int hi = quad_bcast_rt((int)(b >> 32), k);
-    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
-}
-__device__ __forceinline__ float quad_bcast_v(float v, int k) {
-    return __int_as_float(quad_bcast_rt(__float_as_int(v), k));
 }
 
 // value of lane n of the caller's own 16-lane row (DPP row_newbcast; n resolves
@@ -564,152 +542,14 @@ template <int NM, int NO> __device__ __forceinline__ void interleave_mfma() {
 // current column t is always Cr[0].  With the loop unrolled the rotation is
 // register renaming; it keeps the loop body free of run-time register
 // indexing should the loop ever be rolled to save instruction cache.
-template <typename T, int NP>
-__device__ __forceinline__ void gj_sweep_plain(typename MT<T>::v4 (&Cr)[NP / 16],
-                                         typename MT<T>::v4 (&Ci)[NP / 16], GjShared<T, NP> &sh,
-                                         int tid) {
-    constexpr int NT = NP / 16;
-    typedef cplx<T> ct;
-    typedef typename MT<T>::v4 v4;
-    const int w = tid >> 6, l = tid & 63, lj = l & 15, lg = l >> 4;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-        if (w == t) {
-#pragma unroll
-            for (int p = 1; p < NT; ++p) {
-                const int c = (p + t) % NT;
-#pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    put_split<T>(sh.Rb[MT<T>::row(lg, r)][16 * c + lj], Cr[p][r], Ci[p][r]);
-            }
-            v4 &Xr = Cr[0];
-            v4 &Xi = Ci[0];
-            gj_tile_invert<T, GjShared<T, NP>::DUMP_N>(Xr, Xi, sh.pivv + 16 * t, sh.dump(), tid);
-#pragma unroll
-            for (int r = 0; r < 4; ++r) put_split<T>(sh.Xw[t][MT<T>::row(lg, r)][lj], Xr[r], Xi[r]);
-        } else {
-#pragma unroll
-            for (int r = 0; r < 4; ++r) put_split<T>(sh.Xw[w][MT<T>::row(lg, r)][lj], Cr[0][r], Ci[0][r]);
-        }
-        __syncthreads();
-
-        if constexpr (sizeof(T) == 4) {
-            T gr[4], gim[4];
-            if (w == t) {
-#pragma unroll
-                for (int k4 = 0; k4 < 4; ++k4) {
-                    ct g = sh.Xw[t][lj][4 * k4 + lg];
-                    if (lj == 4 * k4 + lg) g.re -= T(1);
-                    gr[k4] = g.re;
-                    gim[k4] = g.im;
-                }
-            } else {
-                // G = -A_wt A_tt^-1 in the 3M form: T1 = a_re b_re, T2 = a_im b_im,
-                // P3 = (a_re + a_im)(b_re + b_im); G = (T2 - T1, T1 + T2 - P3)
-                v4 T1 = {0, 0, 0, 0}, T2 = {0, 0, 0, 0}, P3 = {0, 0, 0, 0};
-#pragma unroll
-                for (int k4 = 0; k4 < 4; ++k4) {
-                    const ct xa = sh.Xw[w][lj][4 * k4 + lg];
-                    const ct b = sh.Xw[t][4 * k4 + lg][lj];
-                    T1 = MT<T>::mma(xa.re, b.re, T1);
-                    T2 = MT<T>::mma(xa.im, b.im, T2);
-                    P3 = MT<T>::mma(xa.re + xa.im, b.re + b.im, P3);
-                }
-                const v4 Gr = T2 - T1, Gi = T1 + T2 - P3;
-                Cr[0] = Gr;
-                Ci[0] = Gi;
-                wave_sync_lds();
-#pragma unroll
-                for (int r = 0; r < 4; ++r) put_split<T>(sh.Xw[w][MT<T>::row(lg, r)][lj], Gr[r], Gi[r]);
-                wave_sync_lds();
-#pragma unroll
-                for (int k4 = 0; k4 < 4; ++k4) {
-                    const ct g = sh.Xw[w][lj][4 * k4 + lg];
-                    gr[k4] = g.re;
-                    gim[k4] = g.im;
-                }
-            }
-#pragma unroll
-            for (int p = 1; p < NT; ++p) {
-                const int c = (p + t) % NT;
-                // three real products per complex one (3M form): T1 = G_re B_re,
-                // T2 = G_im B_im, Ci += (G_re + G_im)(B_re + B_im) - T1 - T2.
-                // In FP32 the extra accumulators fit the register budget and
-                // save a quarter of the matrix products (measured 6 % faster);
-                // in FP64 they spill and the four-product form is faster.
-                v4 T1 = {0, 0, 0, 0}, T2 = {0, 0, 0, 0};
-#pragma unroll
-                for (int k4 = 0; k4 < 4; ++k4) {
-                    const ct b = sh.Rb[4 * k4 + lg][16 * c + lj];
-                    T1 = MT<T>::mma(gr[k4], b.re, T1);
-                    T2 = MT<T>::mma(gim[k4], b.im, T2);
-                    Ci[p] = MT<T>::mma(gr[k4] + gim[k4], b.re + b.im, Ci[p]);
-                }
-                Cr[p] += T1 - T2;
-                Ci[p] -= T1 + T2;
-            }
-        } else {
-            // G_w in LDS (this wave's exchange slot): the inverse for w = t (its
-            // diagonal minus one below), -A_wt A_tt^-1 formed here for the others
-            if (w != t) {
-                // G = -A_wt A_tt^-1 in the 3M form: T1 = a_re b_re, T2 = a_im b_im,
-                // P3 = (a_re + a_im)(b_re + b_im); G = (T2 - T1, T1 + T2 - P3)
-                v4 T1 = {0, 0, 0, 0}, T2 = {0, 0, 0, 0}, P3 = {0, 0, 0, 0};
-#pragma unroll
-                for (int k4 = 0; k4 < 4; ++k4) {
-                    const ct xa = sh.Xw[w][lj][4 * k4 + lg];
-                    const ct b = sh.Xw[t][4 * k4 + lg][lj];
-                    T1 = MT<T>::mma(xa.re, b.re, T1);
-                    T2 = MT<T>::mma(xa.im, b.im, T2);
-                    P3 = MT<T>::mma(xa.re + xa.im, b.re + b.im, P3);
-                }
-                const v4 Gr = T2 - T1, Gi = T1 + T2 - P3;
-                Cr[0] = Gr;
-                Ci[0] = Gi;
-                wave_sync_lds();
-#pragma unroll
-                for (int r = 0; r < 4; ++r) put_split<T>(sh.Xw[w][MT<T>::row(lg, r)][lj], Gr[r], Gi[r]);
-                wave_sync_lds();
-            }
-            // FP64: the A operand comes from LDS one k-slice at a time, used
-            // across the tiles, so no copy of G is held through the update
-#pragma unroll
-            for (int k4 = 0; k4 < 4; ++k4) {
-                ct g = sh.Xw[w][lj][4 * k4 + lg];
-                if (w == t && lj == 4 * k4 + lg) g.re -= T(1);
-#pragma unroll
-                for (int p = 1; p < NT; ++p) {
-                    const int c = (p + t) % NT;
-                    const ct b = sh.Rb[4 * k4 + lg][16 * c + lj];
-                    Cr[p] = MT<T>::mma(g.re, b.re, Cr[p]);
-                    Cr[p] = MT<T>::mma_na(g.im, b.im, Cr[p]);
-                    Ci[p] = MT<T>::mma(g.re, b.im, Ci[p]);
-                    Ci[p] = MT<T>::mma(g.im, b.re, Ci[p]);
-                }
-            }
-        }
-        __syncthreads();
-        // rotate: the next tile column moves to Cr[0]
-        const v4 r0 = Cr[0], i0 = Ci[0];
-#pragma unroll
-        for (int p = 0; p + 1 < NT; ++p) {
-            Cr[p] = Cr[p + 1];
-            Ci[p] = Ci[p + 1];
-        }
-        Cr[NT - 1] = r0;
-        Ci[NT - 1] = i0;
-    }
-}
-
-// The same sweep with look-ahead: the diagonal tile of step t + 1 belongs to
-// wave t + 1, which updates that tile first during step t and then inverts it
+//
+// Look-ahead: the diagonal tile of step t + 1 belongs to wave t + 1, which updates that tile first during step t and then inverts it
 // while the rest of its update is still in the matrix pipe, so the scalar
 // inversion (vector ALU and lane exchanges) overlaps matrix work instead of
 // running alone between two barriers; only the first tile is inverted before
-// the loop.  The look-ahead wave holds the inversion's temporaries next to its
-// update operands, so it pays only where that fits the register budget.
+// the loop.
 template <typename T, int NP>
-__device__ __forceinline__ void gj_sweep_lookahead(typename MT<T>::v4 (&Cr)[NP / 16],
+__device__ __forceinline__ void gj_sweep(typename MT<T>::v4 (&Cr)[NP / 16],
                                          typename MT<T>::v4 (&Ci)[NP / 16], GjShared<T, NP> &sh,
                                          int tid) {
     constexpr int NT = NP / 16;
@@ -877,15 +717,6 @@ __device__ __forceinline__ void gj_sweep_lookahead(typename MT<T>::v4 (&Cr)[NP /
         Cr[NT - 1] = r0;
         Ci[NT - 1] = i0;
     }
-}
-
-// Dispatch: LA selects the look-ahead sweep (measured per build).
-template <typename T, int NP, bool LA>
-__device__ __forceinline__ void gj_sweep(typename MT<T>::v4 (&Cr)[NP / 16],
-                                         typename MT<T>::v4 (&Ci)[NP / 16], GjShared<T, NP> &sh,
-                                         int tid) {
-    if constexpr (LA) gj_sweep_lookahead<T, NP>(Cr, Ci, sh, tid);
-    else gj_sweep_plain<T, NP>(Cr, Ci, sh, tid);
 }
 
 // log det from the scalar pivots (no row exchanges), by one wave.  det D is

@@ -106,7 +106,7 @@ __device__ __forceinline__ bool gjb_item(LadderArgs a0, int gitem) {
         if (!(cw < CERT_MAX_F64)) return false;   // uniform over the work-group
     }
 
-    gj_sweep<double, NP, true>(Cr, Ci, sh, tid);   // look-ahead inversion
+    gj_sweep<double, NP>(Cr, Ci, sh, tid);
 
     if (w == 0) {
         cd ldv;

@@ -195,7 +195,7 @@ __device__ __forceinline__ void mixed_item(LadderArgs a0, int gitem, bool dummy 
         else skip = true;
     }
 
-    gj_sweep<float, NP, true>(Cr, Ci, sh.gj, tid);   // look-ahead inversion
+    gj_sweep<float, NP>(Cr, Ci, sh.gj, tid);
 
     if (w == 0) {
         cd ldv;
@@ -512,7 +512,8 @@ void k_ladder_fp32_o5(LadderArgs a0) {
     mixed_item<NP, false, FULL>(a0, a0.item0 + xcd_item(blockIdx.x, gridDim.x));
 }
 
-// FP32 ladder, two items per work-group (NP = 96; see k_ladder_gjb_f64_x2)
+// FP32 ladder, two items per work-group (NP = 96: work-groups of one item, six waves,
+// ran one per CU; twelve-wave ones hold three waves per SIMD, 16^3 24.7 -> 18.0 ms)
 template <int NP, bool FULL>
 __global__ __launch_bounds__(NP * 8) void k_ladder_fp32_x2(LadderArgs a0) {
     const int half = threadIdx.x >= NP * 4 ? 1 : 0;

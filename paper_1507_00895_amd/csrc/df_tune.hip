@@ -71,7 +71,7 @@ int variant_from_name(const char *name) {
 int variant_padded_size(int c, int n_nu) {
     if (c < 0 || c >= kChoices) return 0;
     const int v = choice_variant(c);
-    // persistent grids: the FP64 certified builds with an item loop
+    // launch shapes: names of the certified FP64 choices only
     if (choice_persist(c) != 0 && v != LV_GJB && v != LV_GJB_O3) return 0;
     switch (v) {
         case LV_GJB: return ladder_gjb_padded_size(n_nu);

@@ -10,8 +10,8 @@
 namespace df {
 
 enum LadderVariant {
-    LV_GJB = 0,        // certified blocked Gauss-Jordan, FP64 MFMA, compiler's register budget
-    LV_GJB_O3 = 1,     // same, capped for three waves per SIMD
+    LV_GJB = 0,        // certified FP64 kernels (screening, symmetric ladder, the rest)
+    LV_GJB_O3 = 1,     // same kernels
     LV_VECTOR = 2,     // partial pivoting, FP64 vector FMAs
     LV_MFMA = 3,       // partial pivoting, FP64 MFMA trailing updates
     LV_MIXED = 4,      // certified FP32 sweep + FP64 residual correction
@@ -19,15 +19,15 @@ enum LadderVariant {
     LV_FP32 = 6,       // certified FP32 sweep alone
     LV_FP32_O4 = 7,    // same, capped for four waves per SIMD
     LV_FP32_O5 = 8,    // same, capped for five waves per SIMD
-    LV_GJB_O4 = 9,     // certified FP64 kernel capped for four waves per SIMD (spills)
+    LV_GJB_O4 = 9,     // as LV_GJB
     LV_MIXED_O4 = 10,  // FP32 + FP64 refinement capped for four waves per SIMD (spills)
     LV_COUNT = 11
 };
 
-// A choice is a kernel variant and a launch shape: c = v + LV_COUNT * p, with
-// p = 0 one work-group per item, p = 1, 2 a persistent grid of p times the
-// resident work-groups, each taking items from its XCD's counter.  Its name is
-// the variant's, with "@p1" / "@p2" appended for the persistent shapes.
+// A choice is a kernel variant and a launch shape: c = v + LV_COUNT * p.  Shapes p = 1, 2
+// ("@p1" / "@p2" after the variant's name) belong to earlier builds of the certified
+// FP64 kernels; all certified FP64 choices run the same kernels now (screening,
+// symmetric ladder, the rest), and their names stay for saved tables.
 constexpr int kPersistModes = 3;
 constexpr int kChoices = LV_COUNT * kPersistModes;
 inline int choice_variant(int c) { return c % LV_COUNT; }

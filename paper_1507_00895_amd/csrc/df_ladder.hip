@@ -37,9 +37,9 @@ hipError_t launch_ladder_fp64(const LadderArgs &a, hipStream_t s) {
     switch (ladder_padded_size(a.n_nu)) {
         case 16: return launch_one<16, 8, 8>(a, s);
         case 32: return launch_one<32, 8, 8>(a, s);
-        case 48: return launch_one<48, 16, 16>(a, s);
-        case 64: return launch_one<64, 16, 16>(a, s);
-        case 96: return launch_one<96, 32, 16>(a, s);
+        case 48: return launch_one<48, 24, 8>(a, s);
+        case 64: return launch_one<64, 32, 8>(a, s);
+        case 96: return launch_one<96, 16, 16>(a, s);
         case 128: return launch_one<128, 32, 16>(a, s);
         default: return hipErrorInvalidValue;
     }

@@ -166,7 +166,7 @@ __device__ __forceinline__ bool gjb_item(LadderArgs a0, int gitem) {
 }
 
 // rows of threads of the pivoting item with NP * 4 threads (TC columns each)
-template <int NP> constexpr int pivot_tc() { return NP <= 32 ? 8 : 16; }
+template <int NP> constexpr int pivot_tc() { return NP <= 64 ? 8 : 16; }
 
 // Both queues, grid-stride; uniform over the work-group, which may run several
 // items in turn (LDS is reused: a barrier separates them).

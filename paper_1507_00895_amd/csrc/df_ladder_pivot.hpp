@@ -34,6 +34,14 @@ __device__ __forceinline__ unsigned pivot_key(double mag, int row) {
     return (bits & 0xFFFFFF00u) | (unsigned)(255 - row);
 }
 
+// 1 / m by the hardware reciprocal (relative error e below 2^-22) and one third-order
+// step: y (1 + e + e^2), error e^3.
+__device__ __forceinline__ double recip_pivot(double m) {
+    const double y = __builtin_amdgcn_rcp(m);
+    const double e = fma(-m, y, 1.0);
+    return fma(y, fma(e, e, e), y);
+}
+
 // One item (gitem: global item) by the TR * TC threads of the work-group.
 // Contains barriers; LDS is free again after the caller's next barrier.
 template <int NP, int TR, int TC>
@@ -46,7 +54,7 @@ __device__ __forceinline__ void pivot_item(const LadderArgs &a0, int gitem) {
     static_assert(TC <= 64 && (64 % TC) == 0, "row groups within a wave");
 
     __shared__ cd colbuf[2][NP];
-    __shared__ cd rowblk[BR][NP];
+    __shared__ cd rowblk[NP];
     __shared__ cd pivv[NP];
     __shared__ int prow[NP];
     __shared__ int rowstep[NP];
@@ -135,20 +143,22 @@ __device__ __forceinline__ void pivot_item(const LadderArgs &a0, int gitem) {
                 const unsigned k2 = pivot_key(cabs1(col[lane + 64]), lane + 64);
                 key = k2 > key ? k2 : key;
             }
-            const int p = 255 - (int)(__ockl_wfred_max_u32(key) & 255u);
+            const int p = __builtin_amdgcn_readfirstlane(255 - (int)(__ockl_wfred_max_u32(key) & 255u));
             if (p == lane) used0 = true;
             if (p == lane + 64) used1 = true;
             const cd piv = col[p];
-            // 1/piv with one division (|piv|^2 cannot overflow for these matrices)
-            const double inv2 = 1.0 / fma(piv.re, piv.re, piv.im * piv.im);
+            // 1/piv from 1/|piv|^2 (which cannot overflow for these matrices)
+            const double inv2 = recip_pivot(fma(piv.re, piv.re, piv.im * piv.im));
             const cd ip = {piv.re * inv2, -piv.im * inv2};
             const int trp = p % TR;
             const int ap = p / TR;
             if (tr == trp) {
 #pragma unroll
-                for (int ai = 0; ai < BR; ++ai)
+                for (int ai = 0; ai < BR; ++ai) {
+                    if (ai != ap) continue;       // uniform
 #pragma unroll
-                    for (int b = 0; b < BC; ++b) rowblk[ai][tc + TC * b] = A[ai][b];
+                    for (int b = 0; b < BC; ++b) rowblk[tc + TC * b] = A[ai][b];
+                }
             }
             if (tid == 0) {
                 prow[k] = p;
@@ -159,7 +169,7 @@ __device__ __forceinline__ void pivot_item(const LadderArgs &a0, int gitem) {
 
             cd r[BC];
 #pragma unroll
-            for (int b = 0; b < BC; ++b) r[b] = rowblk[ap][tc + TC * b];
+            for (int b = 0; b < BC; ++b) r[b] = rowblk[tc + TC * b];
             cd f[BR];
 #pragma unroll
             for (int ai = 0; ai < BR; ++ai) {
@@ -168,9 +178,11 @@ __device__ __forceinline__ void pivot_item(const LadderArgs &a0, int gitem) {
                 f[ai] = (i == p) ? cd{1.0 - ip.re, -ip.im} : cv * ip;
             }
 #pragma unroll
-            for (int ai = 0; ai < BR; ++ai)
+            for (int b = 0; b < BC; ++b) {
+                if (TC * b >= n_nu) break;        // columns of the padding only
 #pragma unroll
-                for (int b = 0; b < BC; ++b) A[ai][b] = fms(A[ai][b], f[ai], r[b]);
+                for (int ai = 0; ai < BR; ++ai) A[ai][b] = fms(A[ai][b], f[ai], r[b]);
+            }
             if (tc == tcol) {
 #pragma unroll
                 for (int ai = 0; ai < BR; ++ai) {

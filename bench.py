@@ -275,7 +275,9 @@ def roofline_of(prec, B, n_om, N, n_nu, lad_ms, n_inst=1):
     # The unit of work stays the dense complex inverse (8 n^3 flops per solve), whatever
     # the kernels do instead: the symmetric block ladder makes about half of it, so
     # its fraction may pass 1.
-    certified = {"launches": fp64_launches(n_nu)} if base.startswith("gjb") else {}
+    certified = {"launches": fp64_launches(n_nu),
+                 "unit_of_work": "8 n_nu^3 real flops per solve (dense complex inverse); the symmetric "
+                                 "block ladder makes about half of them"} if base.startswith("gjb") else {}
     return {**certified, "bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
             "frac": achieved / peak,
             "traffic": measured_traffic(certified["launches"][1] if certified else kernel_name,

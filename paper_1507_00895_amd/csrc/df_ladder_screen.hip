@@ -111,7 +111,10 @@ __device__ __forceinline__ void screen_body(const LadderArgs &a0, const double *
     // the matrix of the product, by rows k: P (symmetric); LAT: the symmetric part of
     // gamma where the block ladder takes it, else gamma from its transpose
     const double *pm = a.pdm;
-    if constexpr (LAT) pm = vertex_symmetric(a.symp + 4 * (size_t)im * kPrepChunks, n, c, l) ? a.gsym : a.gtr;
+    // (wave 0 needs the answer at the end; asked here, the loads are not waited for alone)
+    bool sym = false;
+    if (LAT || w == 0) sym = vertex_symmetric(a.symp + 4 * (size_t)im * kPrepChunks, n, c, l);
+    if constexpr (LAT) pm = sym ? a.gsym : a.gtr;
     pm += 2 * (size_t)cm * n * n;
     const float *ga = a.gabs + (size_t)cm * n * n;
     // this wave's rows of |gamma| (A operand of every k-slice)
@@ -198,7 +201,6 @@ __device__ __forceinline__ void screen_body(const LadderArgs &a0, const double *
         if (__all(pass || !qin)) break;
     }
     if (w != 0) return;
-    const bool sym = vertex_symmetric(a.symp + 4 * (size_t)im * kPrepChunks, n, c, l);
     if (lg == 0) {
         const int item = a.qlist ? (c * n_m + (im - m0)) * n_q + kq : cm * N + q;
         if (qin) a.cert[item] = (pass && sym) ? 1 : 0;

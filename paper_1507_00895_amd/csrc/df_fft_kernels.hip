@@ -284,19 +284,18 @@ __global__ __launch_bounds__(256) void k_gamma_prep(GammaPrepArgs a) {
             float m = (float)sqrt(fma(gt.re, gt.re, gt.im * gt.im));
             if (m < 1.17549435e-38f && (gt.re != 0.0 || gt.im != 0.0)) m = 1.17549435e-38f;
             a.gabs[o] = m;
-            // a NaN makes the maximum difference NaN, and the comparison below false
+            // a NaN makes the maxima NaN, and the comparison of prep_symmetric false
             const float d = (float)(fabs(g.re - gt.re) + fabs(g.im - gt.im));
-            if (!(m <= big[c])) big[c] = m;
-            if (!(d <= dif[c])) dif[c] = d;
+            big[c] = max_nan(big[c], m);
+            dif[c] = max_nan(dif[c], d);
         }
     }
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1)
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
-            const float m = __shfl_xor(big[c], off, 64), d = __shfl_xor(dif[c], off, 64);
-            if (!(m <= big[c])) big[c] = m;
-            if (!(d <= dif[c])) dif[c] = d;
+            big[c] = max_nan(big[c], __shfl_xor(big[c], off, 64));
+            dif[c] = max_nan(dif[c], __shfl_xor(dif[c], off, 64));
         }
     const int w = threadIdx.x >> 6;
     if ((threadIdx.x & 63) == 0) {
@@ -308,8 +307,7 @@ __global__ __launch_bounds__(256) void k_gamma_prep(GammaPrepArgs a) {
     __syncthreads();
     if (threadIdx.x < 4) {
         float m = red[threadIdx.x][0];
-        for (int x = 1; x < 4; ++x)
-            if (!(red[threadIdx.x][x] <= m)) m = red[threadIdx.x][x];
+        for (int x = 1; x < 4; ++x) m = max_nan(m, red[threadIdx.x][x]);
         a.symp[4 * ((size_t)blockIdx.y * kPrepChunks + blockIdx.x) + threadIdx.x] = m;
     }
 }

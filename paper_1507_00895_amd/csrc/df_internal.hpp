@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "df_device.hpp"
+#include "df_nan.hpp"
 
 namespace df {
 

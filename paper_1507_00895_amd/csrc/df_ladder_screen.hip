@@ -33,8 +33,8 @@ __device__ __forceinline__ bool vertex_symmetric(const float *part, int n, int c
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) {
         const float om = __shfl_xor(m, off, 64), od = __shfl_xor(d, off, 64);
-        if (!(om <= m)) m = om;
-        if (!(od <= d)) d = od;
+        m = max_nan(m, om);
+        d = max_nan(d, od);
     }
     return prep_symmetric(m, d);
 }
@@ -181,21 +181,20 @@ __device__ __forceinline__ void screen_body(const LadderArgs &a0, const double *
                 const float vi = it == 0 ? 1.f : vv[it & 1][i][lj];
                 const float u = fmaf(1e-6f, vi, U[r]);
                 const float rr = u * __builtin_amdgcn_rcpf(vi);
-                if (i < n && !(rr <= ratio)) ratio = rr;
+                if (i < n) ratio = max_nan(ratio, rr);
                 vv[(it + 1) & 1][i][lj] = i < n ? u : 1.f;
             }
         }
 #pragma unroll
         for (int off = 16; off <= 32; off <<= 1) {
             const float o = __shfl_xor(ratio, off, 64);
-            if (!(o <= ratio)) ratio = o;
+            ratio = max_nan(ratio, o);
         }
         if (lg == 0) red[it & 1][w][lj] = ratio;
         __syncthreads();
         float m = red[it & 1][0][lj];
 #pragma unroll
-        for (int x = 1; x < 4; ++x)
-            if (!(red[it & 1][x][lj] <= m)) m = red[it & 1][x][lj];
+        for (int x = 1; x < 4; ++x) m = max_nan(m, red[it & 1][x][lj]);
         pass = pass || (double)m * (1.0 + 1e-5) < SCREEN_MAX;
         // uniform: every wave holds the same 16 momenta
         if (__all(pass || !qin)) break;

@@ -48,7 +48,7 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
         objs = [os.path.join(tmp, os.path.basename(src) + ".o") for src in sources()]
 
         def compile_one(src, obj):
-            extra = LADDER_FLAGS if os.path.basename(src).startswith("df_ladder_") else []
+            extra = LADDER_FLAGS if os.path.basename(src).startswith("df_ladder") else []
             cmd = [cc, f"--offload-arch={ARCH}", "-O3", "-std=c++17", "-fPIC", "-c",
                    "-I", INCLUDE, "-I", CSRC, *DEVICE_FLAGS, *extra, src, "-o", obj]
             if verbose:

@@ -21,7 +21,6 @@ namespace {
 
 constexpr size_t kAlign = 256;
 constexpr int kMixBlocks = 512;
-constexpr int kQueueBlocks = 768;
 constexpr int kMaxClasses = 32;
 // Layout of the ints region: per kernel class the uncertified-queue length,
 // the near-queue length; then per instance the count of its ladders outside the radius.
@@ -95,7 +94,7 @@ int norm_parts(const Shape &s, int accel) { return accel > 0 || s.n_chunks > 1 ?
 
 // Per-instance workspace regions (byte offsets from the instance base).
 struct Layout {
-    size_t gr, gdm, pdm, gtr, gp32, gtr32, gsym, gabs, symp, cert, part, gd, chi, w;
+    size_t gr, gdm, pdm, gtr, gp32, gtr32, gsym, gabs, symp, part, gd, chi, w;
     size_t qrep, qlist;               // symmetry tables: int[N] each
     size_t fx, xh, rh, accpart;       // Anderson acceleration (0 when unused)
     size_t total;
@@ -122,7 +121,6 @@ Layout layout_of(const Shape &s, int slots) {
     L.gsym = take(gam);
     L.gabs = take(gam / 4);
     L.symp = take((size_t)s.n_om * kPrepChunks * 4 * sizeof(float));
-    L.cert = take((size_t)s.items);
     L.part = take((size_t)s.n_chunks * fld);
     L.gd = take(fld);
     L.chi = take((size_t)s.n_om * fld);
@@ -145,6 +143,7 @@ struct Global {
     size_t table;                     // LadderInst[n_inst] (fused launches)
     size_t queue;                     // int[sum of items]: uncertified items
     size_t near;                      // int[sum of items]: refined kernel's items near the instability
+    size_t cert;                      // uint8[sum of items]: what the FP64 screening found
     size_t ints;                      // int[kIntsInst + n_inst]: queue lengths, item counters,
                                       // outside counts
     size_t norms;                     // double[sum of mix_blocks][2]: norm partials, right after
@@ -188,6 +187,8 @@ int make_plan(const df_inst_t *inst, int32_t n_inst, Plan *P, int accel = 0) {
     off = align_up(off + items * sizeof(int));
     g.near = off;
     off = align_up(off + items * sizeof(int));
+    g.cert = off;
+    off = align_up(off + items);
     g.ints = off;
     off += ((size_t)(kIntsInst + n_inst) * sizeof(int) + 7) & ~(size_t)7;
     g.norms = off;
@@ -286,6 +287,7 @@ int ladder_class(int n_nu, int prec) {
 struct ClassSlots {
     int *queue, *queue_count;         // uncertified items -> pivoting kernel
     int *near, *near_count;           // refined kernel: items near the instability -> FP64 kernel
+    uint8_t *cert;                    // FP64 screening: CERT_* of the items
 };
 
 ClassSlots class_slots(void *ws, const Global &g, int cls, size_t queue_off) {
@@ -293,16 +295,16 @@ ClassSlots class_slots(void *ws, const Global &g, int cls, size_t queue_off) {
     ClassSlots c;
     c.queue = at<int>(ws, g.queue) + queue_off;
     c.near = at<int>(ws, g.near) + queue_off;
+    c.cert = at<uint8_t>(ws, g.cert) + queue_off;
     c.queue_count = ints + cls;
     c.near_count = ints + kIntsNear + cls;
     return c;
 }
 
 // Launch the ladder for the items in a (single instance, or a fused table)
-// with choice c.  The FP32 kernel queues its uncertified items, the refined
-// kernel its items near the instability, the screening of the FP64 class its
-// uncertified items and those of vertices that are not symmetric; one launch
-// over the queues follows.  The class's counters must be zero before the call.
+// with choice c.  The FP32 kernel and the screening of the FP64 class queue their
+// uncertified items, the refined kernel its items near the instability too; the certified
+// elimination (of those, or of the general vertices' items) and the pivoting follow.  The class's counters must be zero before the call.
 int launch_ladder_variant(int c, LadderArgs a, const ClassSlots &q, hipStream_t st) {
     const int v = choice_variant(c);
     switch (v) {
@@ -312,10 +314,10 @@ int launch_ladder_variant(int c, LadderArgs a, const ClassSlots &q, hipStream_t 
     }
     a.queue = q.queue;
     a.queue_count = q.queue_count;
+    a.cert = q.cert;
     const int grid = a.n_items;
     const bool refined = (v == LV_MIXED || v == LV_MIXED_O3 || v == LV_MIXED_O4);
-    const bool fp64 = fp64_certified(v);
-    if (refined || fp64) {
+    if (refined) {
         a.near_queue = q.near;
         a.near_count = q.near_count;
     }
@@ -327,14 +329,15 @@ int launch_ladder_variant(int c, LadderArgs a, const ClassSlots &q, hipStream_t 
         case LV_MIXED_O3: HIPCHK(launch_ladder_mixed(a, 3, grid, st)); break;
         case LV_MIXED_O4: HIPCHK(launch_ladder_mixed(a, 4, grid, st)); break;
         default:
-            // FP64: the items are screened (certificate, Gamma^(2)); those of
-            // symmetric vertices run in the symmetric kernel, the rest is queued
+            // the items are screened (certificate, Gamma^(2)); the certified ones
+            // of symmetric vertices run in the symmetric kernel
             HIPCHK(launch_ladder_screen(a, st));
             HIPCHK(launch_ladder_sym(a, st));
-            a.screened = 1;
-            break;
+            HIPCHK(launch_ladder_rest(a, st));
+            return DF_OK;
     }
-    HIPCHK(launch_ladder_rest(a, a.n_items < kQueueBlocks ? a.n_items : kQueueBlocks, st));
+    if (refined) HIPCHK(launch_ladder_gjb(a, st));
+    HIPCHK(launch_ladder_fp64_queue(a, st));
     return DF_OK;
 }
 
@@ -604,7 +607,6 @@ LadderInst table_entry(const Plan &P, int i, void *ws, bool sym, const double *c
     d.gsym = at<double>(ws, b + L.gsym);
     d.gabs = at<float>(ws, b + L.gabs);
     d.symp = at<float>(ws, b + L.symp);
-    d.cert = at<uint8_t>(ws, b + L.cert);
     d.chi = chi;
     d.w = w;
     d.logdet = logdet;
@@ -799,7 +801,7 @@ bool acc_weights(const AccState &S, int slots, int newest, double *coef) {
 struct LatticeLayout {
     size_t fields, gr, bub;           // [3][n_nu][N] each: G~, frak G, G_lat; their chi~, L, bubble
     size_t gdm, pdm, gtr, gp32, gtr32, gsym, gabs, symp;   // vertex at Omega = 0
-    size_t cert, w, queue, near, ints, lad;
+    size_t cert, w, queue, ints, lad;
     size_t total;
 };
 
@@ -826,8 +828,7 @@ LatticeLayout lattice_layout_of(const Shape &s) {
     L.cert = take(2 * (size_t)s.N);
     L.w = take(2 * fld);
     L.queue = take(2 * (size_t)s.N * sizeof(int));
-    L.near = take(2 * (size_t)s.N * sizeof(int));
-    L.ints = take(2 * sizeof(int));
+    L.ints = take(sizeof(int));
     L.lad = take(2 * (size_t)s.N * 16);
     // the size stays what the interface has asked for so far (seven fields and up to
     // 512 n_nu x (n_nu + 1) matrices), of which the above is the smaller part
@@ -1034,7 +1035,6 @@ int df_ladder_solve(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts
         a.gsym = at<double>(ws, b + L.gsym);
         a.gabs = at<float>(ws, b + L.gabs);
         a.symp = at<float>(ws, b + L.symp);
-        a.cert = at<uint8_t>(ws, b + L.cert);
         a.n_sblk = ladder_screen_blocks(s.n_nu, s.n_om - (sym ? s.im0 : 0), sym ? s.n_irr : s.N);
         a.chi = inst[i].chi;
         a.w = inst[i].w;
@@ -1521,7 +1521,7 @@ int df_lattice(const df_inst_t *inst, double mu, double *sigma_lat, double *g_la
     g.gabs = at<float>(ws, L.gabs);
     g.symp = at<float>(ws, L.symp);
     g.zero = at<int>(ws, L.ints);
-    g.n_zero = 2;
+    g.n_zero = 1;
     HIPCHK(launch_gamma_prep(g, st));
     LadderArgs c{};
     c.gdm = g.gdm;
@@ -1540,12 +1540,10 @@ int df_lattice(const df_inst_t *inst, double mu, double *sigma_lat, double *g_la
     c.n_sblk = ladder_screen_blocks(s.n_nu, 1, s.N);
     c.queue = at<int>(ws, L.queue);
     c.queue_count = g.zero;
-    c.near_queue = at<int>(ws, L.near);
-    c.near_count = g.zero + 1;
     double *lad = at<double>(ws, L.lad);
     HIPCHK(launch_lattice_screen(c, Lq, st));
     HIPCHK(launch_lattice_sym(c, Lq, lad, st));
-    HIPCHK(launch_lattice_rest(c, Lq, lad, c.n_items < kQueueBlocks ? c.n_items : kQueueBlocks, st));
+    HIPCHK(launch_lattice_rest(c, Lq, lad, c.n_items < kQueueGroups ? c.n_items : kQueueGroups, st));
     LatticeSumArgs m{};
     m.n_nu = s.n_nu;
     m.N = s.N;

@@ -113,6 +113,10 @@ __device__ inline bool prep_symmetric(float m, float d) {
     return d <= m * 9.094947e-13f && m < 3.0e38f;
 }
 
+// What the screening kernel found of an item: it fails the certificate (and is in the
+// queue), or it is certified and its vertex symmetric or not.
+enum : uint8_t { CERT_NONE = 0, CERT_SYMMETRIC = 1, CERT_GENERAL = 2 };
+
 // One instance of a fused multi-instance ladder launch (device-side table).
 struct LadderInst {
     const double *gdm, *pdm, *gtr, *chi;
@@ -127,7 +131,6 @@ struct LadderInst {
     const double *gsym;              // symmetric part of the vertex, |gamma| and the maxima that tell
     const float *gabs;               // whether it is symmetric (GammaPrepArgs)
     const float *symp;
-    uint8_t *cert;                   // [items]: 1 for items of the symmetric kernel (k_ladder_screen)
     int sblk0;                       // first work-group of this instance in a screening launch
 };
 
@@ -157,10 +160,9 @@ struct LadderArgs {
     const double *gsym;              // symmetric FP64 ladder and its screening (see LadderInst)
     const float *gabs;
     const float *symp;
-    uint8_t *cert;
+    uint8_t *cert;                   // CERT_* of every global item (k_ladder_screen)
     int sblk0, n_sblk;               // work-groups of the screening launch
     int full_sym;                    // 1: every instance has n_nu equal to the same multiple of 16
-    int screened;                    // 1: near_queue holds items certified by the screening kernel
 };
 
 // Fused launches: find the instance of a global item, fill the per-instance
@@ -193,7 +195,6 @@ __device__ __forceinline__ int resolve_item(LadderArgs &a, int item) {
     a.n_q = d.n_q;
     a.im0 = d.im0;
     a.gsym = d.gsym;
-    a.cert = d.cert;
     return item - d.item0;
 }
 
@@ -287,17 +288,28 @@ hipError_t launch_acc_record(const AccRecordArgs &a, int blocks, hipStream_t s);
 hipError_t launch_acc_combine(const AccCombineArgs &a, int blocks, hipStream_t s);
 hipError_t launch_gamma_prep(const GammaPrepArgs &a, hipStream_t s);
 
+// most work-groups of a launch over a queue, whose length only the device knows: 8 per
+// CU; longer queues run in rounds
+constexpr int kQueueGroups = 2048;
+
 // padded ladder size for n_nu, 0 if unsupported
 int ladder_padded_size(int n_nu);
 hipError_t launch_ladder_fp64(const LadderArgs &a, hipStream_t s);
 // MFMA blocked Gauss-Jordan variant (n_nu <= 64)
 int ladder_mfma_padded_size(int n_nu);
 hipError_t launch_ladder_mfma_f64(const LadderArgs &a, hipStream_t s);
-// the queued items: near_queue (optional) by certified pivot-free blocked
-// Gauss-Jordan, queue by partial pivoting; grid: work-groups of the launch
+// certified pivot-free blocked Gauss-Jordan of the items in near_queue (null: of every
+// item), uncertified ones going to queue
 int ladder_gjb_padded_size(int n_nu);
 bool ladder_gjb_has_occ3(int n_nu);
-hipError_t launch_ladder_rest(const LadderArgs &a, int grid, hipStream_t s);
+hipError_t launch_ladder_gjb(const LadderArgs &a, hipStream_t s);
+// after the screening: the same elimination of the items marked CERT_GENERAL, Gamma^(2) being
+// in W, and the queue by partial pivoting
+hipError_t launch_ladder_rest(const LadderArgs &a, hipStream_t s);
+// work-groups of the kernel that the device holds at once
+int resident_groups(const void *kern, int threads);
+// the items in queue by partial pivoting
+hipError_t launch_ladder_fp64_queue(const LadderArgs &a, hipStream_t s);
 // mixed precision: FP32 certified sweep + one FP64 residual correction, and
 // the FP32 sweep alone (n_nu <= 128); occ as above (refined: 0, 3 up to 96,
 // 4 up to 64; FP32: 0, and 4, 5 up to 64)

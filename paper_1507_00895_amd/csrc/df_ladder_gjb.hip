@@ -1,7 +1,24 @@
-// FP64 ladder of the queued items: sizes, dispatch to the per-size builds.
-#include "df_ladder_gjb.hpp"
+// Certified FP64 elimination: sizes, dispatch to the per-size builds.
+#include "df_internal.hpp"
 
 namespace df {
+
+// df_ladder_gjb.hpp
+template <int NP, bool FULL, bool SCREENED> hipError_t launch_gjb(const LadderArgs &a, hipStream_t s);
+template <int NP> static hipError_t launch_size(const LadderArgs &a, bool screened, hipStream_t s) {
+    if (a.full) return screened ? launch_gjb<NP, true, true>(a, s) : launch_gjb<NP, true, false>(a, s);
+    return screened ? launch_gjb<NP, false, true>(a, s) : launch_gjb<NP, false, false>(a, s);
+}
+
+int resident_groups(const void *kern, int threads) {
+    int dev = 0, cus = 0, per = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+        cus = 256;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per, kern, threads, 0) != hipSuccess || per < 1) per = 1;
+    (void)hipGetLastError();
+    return cus * per;
+}
 
 int ladder_gjb_padded_size(int n_nu) {
     if (n_nu <= 0) return 0;
@@ -19,17 +36,27 @@ bool ladder_gjb_has_occ3(int n_nu) {
     return np != 0 && np <= 64;
 }
 
-hipError_t launch_ladder_rest(const LadderArgs &a, int grid, hipStream_t s) {
-    if (grid <= 0 || !a.queue || !a.queue_count) return hipErrorInvalidValue;
+static hipError_t launch_sizes(const LadderArgs &a, bool screened, hipStream_t s) {
     switch (ladder_gjb_padded_size(a.n_nu)) {
-        case 16: return launch_rest_16(a, grid, s);
-        case 32: return launch_rest_32(a, grid, s);
-        case 48: return launch_rest_48(a, grid, s);
-        case 64: return launch_rest_64(a, grid, s);
-        case 96: return launch_rest_96(a, grid, s);
-        case 128: return launch_rest_128(a, grid, s);
+        case 16: return launch_size<16>(a, screened, s);
+        case 32: return launch_size<32>(a, screened, s);
+        case 48: return launch_size<48>(a, screened, s);
+        case 64: return launch_size<64>(a, screened, s);
+        case 96: return launch_size<96>(a, screened, s);
+        case 128: return launch_size<128>(a, screened, s);
         default: return hipErrorInvalidValue;
     }
+}
+
+hipError_t launch_ladder_gjb(const LadderArgs &a, hipStream_t s) {
+    if (a.n_items <= 0 || !a.queue || !a.queue_count) return hipErrorInvalidValue;
+    if (a.near_queue && !a.near_count) return hipErrorInvalidValue;
+    return launch_sizes(a, false, s);
+}
+
+hipError_t launch_ladder_rest(const LadderArgs &a, hipStream_t s) {
+    if (a.n_items <= 0 || !a.queue || !a.queue_count || !a.cert) return hipErrorInvalidValue;
+    return launch_sizes(a, true, s);
 }
 
 }  // namespace df

@@ -5,15 +5,20 @@
 // second-order term Gamma^(2) = gamma chi gamma of eq. (sd).
 //
 // The kernel serves the items that the symmetric kernel (df_ladder_sym.hpp) and
-// the FP32 ones do not, from two device-side queues:
-//   near queue   items of vertices that are not symmetric (certified by the
-//                screening kernel), and the refined kernel's items near the
-//                instability (certified here): Gauss-Jordan
-//   queue        uncertified items, and those of the near queue that fail the
-//                certificate here: partial pivoting (df_ladder_pivot.hpp)
-// One launch for both: each is empty in most calls.
-// One work-group of NP/16 waves per item.  A certified item has rho(M) < 1, i.e. it
-// is inside the radius.
+// the FP32 ones do not:
+//   - certified items of vertices that are not symmetric, marked by the screening
+//     kernel, which has formed their certificate and Gamma^(2) (SCREENED);
+//   - the refined kernel's items near the instability (its near queue).
+// A certified item has rho(M) < 1, i.e. it is inside the radius; those that fail the
+// certificate here are appended to the queue of the partial-pivoting kernel
+// (df_ladder_pivot.hpp).
+// Bound: the SIMDs' issue, as df_ladder_sym.hpp.  Non-symmetric vertex, 14,336 items, all
+// launches of a call, us at n_nu 16 / 32 / 48 / 64 / 96 / 128:
+//   one loop over one queue, 768 work-groups      128 266 478 767 2830 5435
+//   here                                           61 164 368 684 2087 4825
+//   elimination of every item, no screening        58 165 376 675 2242 5055
+// In one loop the kernel held the registers of both paths (n_nu 128 190 spilled, 96
+// one work-group per CU), and 768 work-groups are one wave each at n_nu 16.
 #pragma once
 
 #include "df_gj_core.hpp"
@@ -24,26 +29,38 @@ namespace df {
 constexpr int CERT_ITERS = 6;
 constexpr double CERT_MAX_F64 = 0.999;
 
-// Returns false, with no results written, for an uncertified item.
-template <int NP>
-__device__ __forceinline__ bool gjb_item(LadderArgs a0, int gitem) {
+// FULL: n_nu equals the padded size NP, so no index is clamped and no padding is
+// masked.  SCREENED: certified by the screening kernel, which left Gamma^(2)_nn in W.
+// ITEMS > 1: the work-group holds several items, one per slot of NP / 16 waves; all
+// slots take every barrier, so an uncertified item is not left early but carried
+// through with its results discarded, and `dummy` marks a slot without an item of its
+// own, which computes a copy of the last item and writes nothing.
+template <int NP, bool FULL, bool SCREENED, int ITEMS>
+__device__ __forceinline__ void gjb_item(LadderArgs a0, int gitem, bool dummy) {
     constexpr int NT = NP / 16;
     typedef MT<double>::v4 d4;
-    __shared__ GjShared<double, NP> sh;
-    __shared__ cd yv[NP];
-    __shared__ cd tv[NP];
-    __shared__ int s_flag;
-
-    // an opaque copy of the thread index per item (see df_gj_core.hpp)
+    __shared__ GjShared<double, NP> shv[ITEMS];
+    __shared__ cd yvv[ITEMS][NP];
+    __shared__ cd tvv[ITEMS][NP];
+    __shared__ int s_flagv[ITEMS];
+    // an opaque copy of the thread index per item (see df_gj_core.hpp); the slot is the
+    // same for a whole wave
     int tid = threadIdx.x;
     asm volatile("" : "+v"(tid));
+    const int slot = ITEMS > 1 ? __builtin_amdgcn_readfirstlane(tid / (NP * 4)) : 0;
+    tid -= slot * (NP * 4);
+    GjShared<double, NP> &sh = shv[slot];
+    cd *yv = yvv[slot];
+    cd *tv = tvv[slot];
+    int &s_flag = s_flagv[slot];
     const int w = tid >> 6;
     const int l = tid & 63;
     const int lj = l & 15;
     const int lg = l >> 4;
     LadderArgs a = a0;
     const int item = resolve_item(a, gitem);   // gitem: global item (fused launches)
-    const int n_nu = a.n_nu, N = a.N;
+    bool skip = dummy;   // no results of this slot are written
+    const int n_nu = FULL ? NP : a.n_nu, N = a.N;
     int q, cm;
     item_coords(a, item, &cm, &q);
     const int im = __builtin_amdgcn_readfirstlane(cm % a.n_om);
@@ -57,26 +74,28 @@ __device__ __forceinline__ bool gjb_item(LadderArgs a0, int gitem) {
     // column all loads first and without branches (indices clamped into the
     // matrix, the padding masked afterwards), so that they are in flight together.
     const int nm1 = n_nu - 1;
-    {
+    if constexpr (SCREENED) {
+        for (int n = tid; n < n_nu; n += NP * 4) tv[n] = ld(a.w, ((size_t)cm * n_nu + n) * N + q);
+    } else {
         cd tp[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r) tp[r] = {0.0, 0.0};
 #pragma unroll
         for (int tc = 0; tc < NT; ++tc) {
             const int j = 16 * tc + lj;
-            const cd xj = ld(a.chi, ((size_t)im * n_nu + clamp_nu<false>(j, nm1)) * N + q);
+            const cd xj = ld(a.chi, ((size_t)im * n_nu + clamp_nu<FULL>(j, nm1)) * N + q);
             cd pv[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                pv[r] = ld(pm, (size_t)clamp_nu<false>(16 * w + MT<double>::row(lg, r), nm1) * n_nu + clamp_nu<false>(j, nm1));
+                pv[r] = ld(pm, (size_t)clamp_nu<FULL>(16 * w + MT<double>::row(lg, r), nm1) * n_nu + clamp_nu<FULL>(j, nm1));
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
                 const int i = 16 * w + MT<double>::row(lg, r);
-                const bool in = ((i < n_nu) && (j < n_nu));
+                const bool in = FULL || ((i < n_nu) && (j < n_nu));
                 tp[r] = fma_c(tp[r], in ? pv[r] : cd{0.0, 0.0}, xj);
             }
         }
-        rows16_sum<true>(tp, sh.Xw[w], tv + 16 * w, tid);
+        rows16_sum<ITEMS == 1>(tp, sh.Xw[w], tv + 16 * w, tid);
     }
 
     // ---- D = 1 - gamma diag(chi) in accumulator tiles (opaque column index:
@@ -86,24 +105,29 @@ __device__ __forceinline__ bool gjb_item(LadderArgs a0, int gitem) {
     for (int tc = 0; tc < NT; ++tc) {
         int j = 16 * tc + lj;
         asm volatile("" : "+v"(j));
-        const cd xj = ld(a.chi, ((size_t)im * n_nu + clamp_nu<false>(j, nm1)) * N + q);
+        const cd xj = ld(a.chi, ((size_t)im * n_nu + clamp_nu<FULL>(j, nm1)) * N + q);
         cd gv[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            gv[r] = ld(gam, (size_t)clamp_nu<false>(16 * w + MT<double>::row(lg, r), nm1) * n_nu + clamp_nu<false>(j, nm1));
+            gv[r] = ld(gam, (size_t)clamp_nu<FULL>(16 * w + MT<double>::row(lg, r), nm1) * n_nu + clamp_nu<FULL>(j, nm1));
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int i = 16 * w + MT<double>::row(lg, r);
-            const bool in = ((i < n_nu) && (j < n_nu));
+            const bool in = FULL || ((i < n_nu) && (j < n_nu));
             const cd x = gv[r] * xj;
             Cr[tc][r] = (((i == j) ? 1.0 : 0.0) - (in ? x.re : 0.0));
             Ci[tc][r] = (in ? -x.im : 0.0);
         }
     }
 
-    if (!a0.screened) {
-        const double cw = gj_certify<double, NP, (NP <= 64)>(Cr, Ci, sh, CERT_ITERS, CERT_MAX_F64, tid);
-        if (!(cw < CERT_MAX_F64)) return false;   // uniform over the work-group
+    if constexpr (!SCREENED) {
+        const double cw = gj_certify<double, NP, (NP <= 64)>(Cr, Ci, sh, CERT_ITERS, CERT_MAX_F64, tid,
+                                                 ITEMS > 1 ? shv : nullptr, ITEMS > 1 ? ITEMS : 0);
+        if (!(cw < CERT_MAX_F64)) {
+            if (tid == 0 && !dummy) a.queue[atomicAdd(a.queue_count, 1)] = gitem;
+            if constexpr (ITEMS == 1) return;   // uniform: every thread of the work-group leaves here
+            else skip = true;
+        }
     }
 
     gj_sweep<double, NP>(Cr, Ci, sh, tid);
@@ -114,9 +138,11 @@ __device__ __forceinline__ bool gjb_item(LadderArgs a0, int gitem) {
         if (l == 0) {
             s_flag = stt;
             const size_t o = (size_t)cm * N + q;
-            if (a.logdet) st(a.logdet, o, ldv);
-            if (a.status) a.status[o] = (int8_t)stt;
-            if (stt != 0 && a.fallback_count) atomicAdd(a.fallback_count, 1);
+            if (!skip) {
+                if (a.logdet) st(a.logdet, o, ldv);
+                if (a.status) a.status[o] = (int8_t)stt;
+                if (stt != 0 && a.fallback_count) atomicAdd(a.fallback_count, 1);
+            }
         }
     }
     // ---- Gamma_nn = sum_l (D^-1)_nl gamma_ln  (gamma^T read row-wise); loads
@@ -139,83 +165,148 @@ __device__ __forceinline__ bool gjb_item(LadderArgs a0, int gitem) {
             cd gv[4];
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-                gv[r] = ld(gtr, (size_t)clamp_nu<false>(row0 + MT<double>::row(lg, r), nm1) * n_nu + clamp_nu<false>(j, nm1));
+                gv[r] = ld(gtr, (size_t)clamp_nu<FULL>(row0 + MT<double>::row(lg, r), nm1) * n_nu + clamp_nu<FULL>(j, nm1));
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const bool in = ((row0 + MT<double>::row(lg, r) < n_nu) && (j < n_nu));
+                const bool in = FULL || ((row0 + MT<double>::row(lg, r) < n_nu) && (j < n_nu));
                 yp[r] = fma_c(yp[r], cd{Cr[tc][r], Ci[tc][r]}, in ? gv[r] : cd{0.0, 0.0});
             }
         }
-        rows16_sum<true>(yp, sh.Xw[w], yv + 16 * w, tid);
+        rows16_sum<ITEMS == 1>(yp, sh.Xw[w], yv + 16 * w, tid);
     }
     __syncthreads();
     const int stt = s_flag;
-    for (int n = tid; n < n_nu; n += NP * 4) {
-        const cd tt = tv[n];
-        cd wv;
-        if (stt == 0) {
-            const cd y = yv[n];
-            wv = {y.re - 0.5 * tt.re, y.im - 0.5 * tt.im};
-        } else {
-            const cd gnn = ld(gam, (size_t)n * n_nu + n);
-            wv = {gnn.re + 0.5 * tt.re, gnn.im + 0.5 * tt.im};
+    if (!skip)
+        for (int n = tid; n < n_nu; n += NP * 4) {
+            const cd tt = tv[n];
+            cd wv;
+            if (stt == 0) {
+                const cd y = yv[n];
+                wv = {y.re - 0.5 * tt.re, y.im - 0.5 * tt.im};
+            } else {
+                const cd gnn = ld(gam, (size_t)n * n_nu + n);
+                wv = {gnn.re + 0.5 * tt.re, gnn.im + 0.5 * tt.im};
+            }
+            st(a.w, ((size_t)cm * n_nu + n) * N + q, wv);
         }
-        st(a.w, ((size_t)cm * n_nu + n) * N + q, wv);
-    }
-    return true;
 }
 
-// rows of threads of the pivoting item with NP * 4 threads (TC columns each)
-template <int NP> constexpr int pivot_tc() { return NP <= 64 ? 8 : 16; }
+// Position b of a round of m work-groups starting at k0, or -1 beyond it.  The rounds are
+// dealt to the XCDs in contiguous ranges: neighbouring momenta share cache lines.
+__device__ __forceinline__ int round_group(int k0, int groups) {
+    const int left = groups - k0, m = left < (int)gridDim.x ? left : (int)gridDim.x;
+    return (int)blockIdx.x < m ? k0 + xcd_item(blockIdx.x, m) : -1;
+}
 
-// Both queues, grid-stride; uniform over the work-group, which may run several
-// items in turn (LDS is reused: a barrier separates them).
-template <int NP>
-__device__ __forceinline__ void rest_items(const LadderArgs &a0) {
-    const int n_near = a0.near_count ? *a0.near_count : 0, n = n_near + *a0.queue_count;
-    for (int u = (int)blockIdx.x; u < n; u += (int)gridDim.x) {
-        const int item = __builtin_amdgcn_readfirstlane(u < n_near ? a0.near_queue[u] : a0.queue[u - n_near]);
-        bool done = false;
-        if (u < n_near) done = gjb_item<NP>(a0, item);
+// The launch's items (ITEMS per work-group) in rounds of the grid; LDS is reused: a
+// barrier separates the items.  Uniform over the work-group.
+//   SCREENED: those marked CERT_GENERAL.  The marks of 64 rounds are read at once, one
+//             per lane: where there are none (symmetric vertices) the kernel ends after one load.
+//   else:     the near queue, or without one every item.
+template <int NP, bool FULL, bool SCREENED, int ITEMS>
+__device__ __forceinline__ void gjb_items(const LadderArgs &a0) {
+    const int slot = ITEMS > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / (NP * 4)) : 0;
+    const int n = __builtin_amdgcn_readfirstlane(!SCREENED && a0.near_queue ? *a0.near_count : a0.n_items);
+    const int groups = (n + ITEMS - 1) / ITEMS;
+    auto run = [&](int g) __attribute__((always_inline)) {
+        int u = ITEMS * g + slot;
+        bool dummy = ITEMS > 1 && u >= n;
+        if (dummy) u = n - 1;
+        const int item = __builtin_amdgcn_readfirstlane(!SCREENED && a0.near_queue ? a0.near_queue[u] : a0.item0 + u);
+        if (SCREENED && ITEMS > 1)
+            dummy = dummy || __builtin_amdgcn_readfirstlane((int)a0.cert[item]) != CERT_GENERAL;
+        gjb_item<NP, FULL, SCREENED, ITEMS>(a0, item, dummy);
         __syncthreads();
-        if (!done) {
-            pivot_item<NP, NP * 4 / pivot_tc<NP>(), pivot_tc<NP>()>(a0, item);
-            __syncthreads();
+    };
+    if constexpr (SCREENED) {
+        const int G = gridDim.x;
+        for (int k0 = 0; k0 < groups; k0 += 64 * G) {
+            const int k = k0 + (int)(threadIdx.x & 63) * G;
+            const int g = k < groups ? round_group(k, groups) : -1;
+            bool mine = false;
+            if (g >= 0)
+                for (int x = 0; x < ITEMS; ++x)
+                    if (ITEMS * g + x < n) mine = mine || a0.cert[a0.item0 + ITEMS * g + x] == CERT_GENERAL;
+            // (the same in every wave of the work-group)
+            unsigned long long todo = __ballot(mine);
+            while (todo) {
+                const int j = __builtin_ctzll(todo);
+                todo &= todo - 1;
+                run(__builtin_amdgcn_readlane(g, j));
+            }
+        }
+    } else {
+        for (int k0 = 0; k0 < groups; k0 += (int)gridDim.x) {
+            const int g = round_group(k0, groups);
+            if (g < 0) break;
+            run(g);
         }
     }
 }
 
 // Register budget: three waves per SIMD up to NP = 64; the compiler's own at 96
-// and 128 (at 96 the capped build spills and measured 6-25 % slower).
-template <int NP>
-__global__ __launch_bounds__(NP * 4) void k_ladder_rest(LadderArgs a0) {
-    rest_items<NP>(a0);
+// and 128 (at 96 the capped one-item build spills and measured 6-25 % slower).
+// At NP = 96 an item is six waves, and work-groups of one item ran one per CU (1.5 waves
+// per SIMD measured); twelve-wave work-groups of two items fill three per SIMD
+// (mask-free launches only: the masked build needs more registers).
+template <int NP, bool FULL, bool SCREENED>
+__global__ __launch_bounds__(NP * 4) void k_ladder_gjb(LadderArgs a0) {
+    gjb_items<NP, FULL, SCREENED, 1>(a0);
 }
-template <int NP>
+template <int NP, bool FULL>
+__global__ __launch_bounds__(NP * 4) __attribute__((amdgpu_waves_per_eu(3, 3)))
+void k_ladder_gjb_o3(LadderArgs a0) {
+    gjb_items<NP, FULL, false, 1>(a0);
+}
+// After the screening, up to NP = 64: its certified general items, then the queue of the
+// uncertified ones, which is complete before the launch.  One launch: both are empty in
+// most calls, and where both have items the tail of the one is filled by the other.
+// Two loops, each with its own copy of the thread index: neither holds the other's values.
+template <int NP, bool FULL>
 __global__ __launch_bounds__(NP * 4) __attribute__((amdgpu_waves_per_eu(3, 3)))
 void k_ladder_rest_o3(LadderArgs a0) {
-    rest_items<NP>(a0);
+    gjb_items<NP, FULL, true, 1>(a0);
+    pivot_queue<NP, NP / 2, 8>(a0);
+}
+template <int NP, bool FULL, bool SCREENED>
+__global__ __launch_bounds__(NP * 8) void k_ladder_gjb_x2(LadderArgs a0) {
+    gjb_items<NP, FULL, SCREENED, 2>(a0);
 }
 
-template <int NP>
-static hipError_t launch_rest(const LadderArgs &a, int grid, hipStream_t s) {
-    if constexpr (NP <= 64) hipLaunchKernelGGL(k_ladder_rest_o3<NP>, dim3(grid), dim3(NP * 4), 0, s, a);
-    else hipLaunchKernelGGL(k_ladder_rest<NP>, dim3(grid), dim3(NP * 4), 0, s, a);
+// Work-groups of a launch.  Every item (no queue): one each.  A queue: its share of
+// kQueueGroups.  Screened: four times what the device holds at once - in rounds of
+// exactly that, work-groups that start late leave places empty (n_nu 32, 14,336 items 210
+// us, 172 with one work-group per item), and work-groups without an item cost a start each
+// (n_nu 96, 188,416 items of symmetric vertices: 0.3 ms of 13.4 with one per item pair).
+template <int PER, bool SCREENED, typename K>
+static hipError_t launch_items(K kern, int threads, const LadderArgs &a, hipStream_t s) {
+    int grid = (a.n_items + PER - 1) / PER;
+    if constexpr (SCREENED) {
+        static const int most = 4 * resident_groups((const void *)kern, threads);
+        if (grid > most) grid = most;
+    } else {
+        if (a.near_queue && grid > kQueueGroups) grid = kQueueGroups;
+    }
+    hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, s, a);
     return hipGetLastError();
 }
 
-// per-size builds (df_ladder_gjb_np*.hip)
-#define DF_GJB_DECLARE(NP) hipError_t launch_rest_##NP(const LadderArgs &a, int grid, hipStream_t s);
-DF_GJB_DECLARE(16)
-DF_GJB_DECLARE(32)
-DF_GJB_DECLARE(48)
-DF_GJB_DECLARE(64)
-DF_GJB_DECLARE(96)
-DF_GJB_DECLARE(128)
-
-#define DF_GJB_INSTANTIATE(NP)                                                  \
-    hipError_t launch_rest_##NP(const LadderArgs &a, int grid, hipStream_t s) {  \
-        return launch_rest<NP>(a, grid, s);                                      \
+// (explicitly instantiated per size and build in df_ladder_gjb_np*.hip: the large ones
+// take minutes to compile)
+template <int NP, bool FULL, bool SCREENED>
+hipError_t launch_gjb(const LadderArgs &a, hipStream_t s) {
+    if constexpr (NP <= 64) {
+        if constexpr (SCREENED) return launch_items<1, true>(k_ladder_rest_o3<NP, FULL>, NP * 4, a, s);
+        else return launch_items<1, false>(k_ladder_gjb_o3<NP, FULL>, NP * 4, a, s);
+    } else {
+        hipError_t e;
+        if constexpr (NP == 96 && FULL)
+            e = launch_items<2, SCREENED>(k_ladder_gjb_x2<NP, FULL, SCREENED>, NP * 8, a, s);
+        else e = launch_items<1, SCREENED>(k_ladder_gjb<NP, FULL, SCREENED>, NP * 4, a, s);
+        return e != hipSuccess || !SCREENED ? e : launch_ladder_fp64_queue(a, s);
     }
+}
+#define DF_GJB_BUILD(NP, FULL, SCREENED) \
+    template hipError_t launch_gjb<NP, FULL, SCREENED>(const LadderArgs &a, hipStream_t s);
 
 }  // namespace df

@@ -1,8 +1,11 @@
-// FP64 certified ladder builds for n_nu padded to 64.
+// Certified FP64 elimination, builds for n_nu padded to 64.
 #include "df_ladder_gjb.hpp"
 
 namespace df {
 
-DF_GJB_INSTANTIATE(64)
+DF_GJB_BUILD(64, true, true)
+DF_GJB_BUILD(64, true, false)
+DF_GJB_BUILD(64, false, true)
+DF_GJB_BUILD(64, false, false)
 
 }  // namespace df

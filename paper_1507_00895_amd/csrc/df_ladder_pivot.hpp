@@ -62,7 +62,10 @@ __device__ __forceinline__ void pivot_item(const LadderArgs &a0, int gitem) {
     __shared__ cd tv[NP];
     __shared__ int s_status;
 
-    const int tid = threadIdx.x;
+    // an opaque copy of the thread index per item: the queue's loop over items would hoist
+    // the addresses formed from it and hold them
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
     const int tr = tid / TC, tc = tid % TC;
     const int lane = tid & 63;
     LadderArgs a = a0;
@@ -287,6 +290,16 @@ __device__ __forceinline__ void pivot_item(const LadderArgs &a0, int gitem) {
             w = {gnn.re + 0.5 * t.re, gnn.im + 0.5 * t.im};
         }
         st(a.w, ((size_t)cm * n_nu + n) * N + q, w);
+    }
+}
+
+// The queue of the uncertified items, grid-stride.
+template <int NP, int TR, int TC>
+__device__ __forceinline__ void pivot_queue(const LadderArgs &a0) {
+    const int n = __builtin_amdgcn_readfirstlane(*a0.queue_count);
+    for (int u = (int)blockIdx.x; u < n; u += (int)gridDim.x) {
+        pivot_item<NP, TR, TC>(a0, __builtin_amdgcn_readfirstlane(a0.queue[u]));
+        __syncthreads();
     }
 }
 

@@ -66,7 +66,6 @@ __device__ __forceinline__ void screen_body(const LadderArgs &a0, const double *
         a.pdm = d.pdm;
         a.gabs = d.gabs;
         a.symp = d.symp;
-        a.cert = d.cert;
         a.chi = d.chi;
         a.w = d.w;
         a.n_nu = d.n_nu;
@@ -202,20 +201,15 @@ __device__ __forceinline__ void screen_body(const LadderArgs &a0, const double *
     if (w != 0) return;
     if (lg == 0) {
         const int item = a.qlist ? (c * n_m + (im - m0)) * n_q + kq : cm * N + q;
-        if (qin) a.cert[item] = (pass && sym) ? 1 : 0;
-        // the others are appended to a queue, one counter update per work-group
-        const bool put = qin && !(pass && sym);
-        const unsigned long long near = __ballot(put && pass), piv = __ballot(put && !pass);
-        int base_n = 0, base_p = 0;
-        if (lj == 0) {
-            if (near) base_n = atomicAdd(a.near_count, __popcll(near));
-            if (piv) base_p = atomicAdd(a.queue_count, __popcll(piv));
-        }
-        base_n = __builtin_amdgcn_readfirstlane(base_n);
-        base_p = __builtin_amdgcn_readfirstlane(base_p);
-        const unsigned long long below = (1ull << lj) - 1;
-        if (put && pass) a.near_queue[base_n + __popcll(near & below)] = item0 + item;
-        if (put && !pass) a.queue[base_p + __popcll(piv & below)] = item0 + item;
+        if (qin) a.cert[item0 + item] = pass ? (sym ? CERT_SYMMETRIC : CERT_GENERAL) : CERT_NONE;
+        // the uncertified ones (the lattice observables' kernel pivots the general
+        // vertices' too) are appended to the queue, one counter update per work-group
+        const bool put = qin && !(pass && (!LAT || sym));
+        const unsigned long long piv = __ballot(put);
+        int base = 0;
+        if (lj == 0 && piv) base = atomicAdd(a.queue_count, __popcll(piv));
+        base = __builtin_amdgcn_readfirstlane(base);
+        if (put) a.queue[base + __popcll(piv & ((1ull << lj) - 1))] = item0 + item;
     }
 }
 
@@ -234,7 +228,7 @@ int ladder_screen_blocks(int n_nu, int n_m, int n_q) {
 }
 
 hipError_t launch_ladder_screen(const LadderArgs &a, hipStream_t s) {
-    if (a.n_sblk <= 0 || !a.queue || !a.near_queue) return hipErrorInvalidValue;
+    if (a.n_sblk <= 0 || !a.queue || !a.queue_count) return hipErrorInvalidValue;
     switch ((a.n_nu + 15) / 16) {
 #define DF_SCREEN(NT) \
     case NT: hipLaunchKernelGGL(k_ladder_screen<NT>, dim3(a.n_sblk), dim3(256), 0, s, a); break;
@@ -246,7 +240,7 @@ hipError_t launch_ladder_screen(const LadderArgs &a, hipStream_t s) {
 }
 
 hipError_t launch_lattice_screen(const LadderArgs &a, const double *L, hipStream_t s) {
-    if (a.n_sblk <= 0 || !a.queue || !a.near_queue) return hipErrorInvalidValue;
+    if (a.n_sblk <= 0 || !a.queue || !a.queue_count) return hipErrorInvalidValue;
     switch ((a.n_nu + 15) / 16) {
 #define DF_SCREEN_L(NT) \
     case NT: hipLaunchKernelGGL(k_lattice_screen<NT>, dim3(a.n_sblk), dim3(256), 0, s, a, L); break;

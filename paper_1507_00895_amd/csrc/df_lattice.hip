@@ -70,9 +70,9 @@ __global__ __launch_bounds__(TR *TC) void k_lattice_rest(LadderArgs a, const dou
     __shared__ cd red[NT / 64];
     const int tid = threadIdx.x, tr = tid / TC, tc = tid % TC, lane = tid & 63;
     const int n = a.n_nu, N = a.N;
-    const int n_near = *a.near_count, n_all = n_near + *a.queue_count;
+    const int n_all = *a.queue_count;
     for (int wi = blockIdx.x; wi < n_all; wi += gridDim.x) {
-        const int item = wi < n_near ? a.near_queue[wi] : a.queue[wi - n_near];
+        const int item = a.queue[wi];
         const int c = item / N, q = item % N;
         const double *gam = a.gdm + 2 * (size_t)c * n * n;
         cd A[BR][BC];
@@ -197,7 +197,7 @@ hipError_t launch_lattice_fields(const LatticeFieldArgs &a, hipStream_t s) {
 }
 
 hipError_t launch_lattice_rest(const LadderArgs &a, const double *L, double *lad, int grid, hipStream_t s) {
-    if (grid <= 0 || !a.near_count || !a.queue_count) return hipErrorInvalidValue;
+    if (grid <= 0 || !a.queue || !a.queue_count) return hipErrorInvalidValue;
 #define DF_REST(NP, TR, TC)                                                                              \
     hipLaunchKernelGGL((k_lattice_rest<NP, TR, TC>), dim3(grid), dim3(TR * TC), 0, s, a, L, lad)
     switch (ladder_padded_size(a.n_nu)) {

@@ -277,6 +277,22 @@ int ladder_variant(int n_nu, int prec) {
 // frequencies.
 bool fp64_certified(int v) { return v == LV_GJB || v == LV_GJB_O3 || v == LV_GJB_O4; }
 
+// Small FP64 launches skip the screening and the symmetric kernel: every item is
+// certified and eliminated, or pivoted, in one kernel.  While the items' waves (one per 16
+// frequencies) do not fill the SIMDs' three places each, what counts is the chain of a
+// launch: screening, block ladder and the rest are three of them.  df_ladder_solve, us,
+// symmetric vertex, with the screening / without it:
+//   n_nu 16   128 items 19 / 14   2,560 22 / 16   14,336 56 / 53   30,720 89 / 89   122,880 291 / 323
+//   n_nu 32   128 items 22 / 14     640 26 / 17    1,152 28 / 23    2,560 36 / 40
+//   n_nu 48   128 items 30 / 21     640 41 / 32      896 41 / 36    1,152 42 / 52
+//   n_nu 64   128 items 38 / 28     384 46 / 41      640 47 / 49      896 58 / 66
+// (general vertices gain up to larger counts: n_nu 64, 896 items 76 / 66; n_nu 80 and above
+// gain from the screening at any count: 128 items 59 without, 51 with it)
+bool fp64_direct(int n_nu, int items) {
+    const int nt = (n_nu + 15) / 16;
+    return nt == 1 ? items <= 32768 : nt <= 4 && items * nt <= 2560;
+}
+
 int ladder_class(int n_nu, int prec) {
     const int v = ladder_variant(n_nu, prec);
     if (fp64_certified(choice_variant(v))) return LV_GJB * 256 + (n_nu + 15) / 16 * 16;
@@ -315,12 +331,10 @@ int launch_ladder_variant(int c, LadderArgs a, const ClassSlots &q, hipStream_t 
     a.queue = q.queue;
     a.queue_count = q.queue_count;
     a.cert = q.cert;
+    a.near_count = q.near_count;
     const int grid = a.n_items;
     const bool refined = (v == LV_MIXED || v == LV_MIXED_O3 || v == LV_MIXED_O4);
-    if (refined) {
-        a.near_queue = q.near;
-        a.near_count = q.near_count;
-    }
+    if (refined) a.near_queue = q.near;
     switch (v) {
         case LV_FP32: HIPCHK(launch_ladder_fp32(a, 0, grid, st)); break;
         case LV_FP32_O4: HIPCHK(launch_ladder_fp32(a, 4, grid, st)); break;
@@ -329,6 +343,10 @@ int launch_ladder_variant(int c, LadderArgs a, const ClassSlots &q, hipStream_t 
         case LV_MIXED_O3: HIPCHK(launch_ladder_mixed(a, 3, grid, st)); break;
         case LV_MIXED_O4: HIPCHK(launch_ladder_mixed(a, 4, grid, st)); break;
         default:
+            if (fp64_direct(a.n_nu, a.n_items)) {
+                HIPCHK(launch_ladder_all(a, st));
+                return DF_OK;
+            }
             // the items are screened (certificate, Gamma^(2)); the certified ones
             // of symmetric vertices run in the symmetric kernel
             HIPCHK(launch_ladder_screen(a, st));
@@ -1543,7 +1561,7 @@ int df_lattice(const df_inst_t *inst, double mu, double *sigma_lat, double *g_la
     double *lad = at<double>(ws, L.lad);
     HIPCHK(launch_lattice_screen(c, Lq, st));
     HIPCHK(launch_lattice_sym(c, Lq, lad, st));
-    HIPCHK(launch_lattice_rest(c, Lq, lad, c.n_items < kQueueGroups ? c.n_items : kQueueGroups, st));
+    HIPCHK(launch_lattice_rest(c, Lq, lad, st));
     LatticeSumArgs m{};
     m.n_nu = s.n_nu;
     m.N = s.N;

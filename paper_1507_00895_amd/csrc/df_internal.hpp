@@ -148,7 +148,8 @@ struct LadderArgs {
     int *queue;                      // certified kernels: uncertified items are appended here
     int *queue_count;                // its length (zeroed before the launch)
     int *near_queue;                 // refined kernel: items whose certificate bound is
-    int *near_count;                 // >= CERT_NEAR_MIXED go here for the FP64 kernel
+    int *near_count;                 // >= CERT_NEAR_MIXED go here for the FP64 kernel; FP64
+                                     // screening: 1 if it marked an item CERT_GENERAL
     const LadderInst *insts;         // non-null: fused launch over n_insts instances,
     int n_insts;                     // items are global; the fields above are resolved per item
     const float *gp32;               // FP32 ladder: (gamma, gamma_ij gamma_ji) pairs, FP32
@@ -162,6 +163,7 @@ struct LadderArgs {
     const float *symp;
     uint8_t *cert;                   // CERT_* of every global item (k_ladder_screen)
     int sblk0, n_sblk;               // work-groups of the screening launch
+    int pivot_groups;                // first work-groups of the kernel, which take the queue
     int full_sym;                    // 1: every instance has n_nu equal to the same multiple of 16
 };
 
@@ -288,9 +290,15 @@ hipError_t launch_acc_record(const AccRecordArgs &a, int blocks, hipStream_t s);
 hipError_t launch_acc_combine(const AccCombineArgs &a, int blocks, hipStream_t s);
 hipError_t launch_gamma_prep(const GammaPrepArgs &a, hipStream_t s);
 
-// most work-groups of a launch over a queue, whose length only the device knows: 8 per
-// CU; longer queues run in rounds
-constexpr int kQueueGroups = 2048;
+// Work-groups of a launch over a queue of at most `items`, whose length only the device
+// knows: three waves per SIMD, further items in rounds.  (The queues are empty in most
+// calls, and every work-group costs its start: lattice observables of 32x32, n_nu 64, 768
+// work-groups of four waves 93 us, 2048 98.)
+constexpr int kQueueWaves = 3072;
+inline int queue_groups(int items, int threads) {
+    const int most = kQueueWaves / (threads / 64);
+    return items < most ? items : most;
+}
 
 // padded ladder size for n_nu, 0 if unsupported
 int ladder_padded_size(int n_nu);
@@ -298,11 +306,13 @@ hipError_t launch_ladder_fp64(const LadderArgs &a, hipStream_t s);
 // MFMA blocked Gauss-Jordan variant (n_nu <= 64)
 int ladder_mfma_padded_size(int n_nu);
 hipError_t launch_ladder_mfma_f64(const LadderArgs &a, hipStream_t s);
-// certified pivot-free blocked Gauss-Jordan of the items in near_queue (null: of every
-// item), uncertified ones going to queue
+// certified pivot-free blocked Gauss-Jordan of the items in near_queue, uncertified ones
+// going to queue
 int ladder_gjb_padded_size(int n_nu);
 bool ladder_gjb_has_occ3(int n_nu);
 hipError_t launch_ladder_gjb(const LadderArgs &a, hipStream_t s);
+// the same of every item (n_nu <= 64), uncertified ones by partial pivoting
+hipError_t launch_ladder_all(const LadderArgs &a, hipStream_t s);
 // after the screening: the same elimination of the items marked CERT_GENERAL, Gamma^(2) being
 // in W, and the queue by partial pivoting
 hipError_t launch_ladder_rest(const LadderArgs &a, hipStream_t s);

@@ -13,7 +13,7 @@ __global__ __launch_bounds__(TR *TC) void k_ladder_fp64(LadderArgs a0) {
 template <int NP, int TR, int TC>
 __global__ __launch_bounds__(TR *TC) __attribute__((amdgpu_waves_per_eu(NP <= 64 ? 4 : 2)))
 void k_ladder_fp64_queue(LadderArgs a0) {
-    pivot_queue<NP, TR, TC>(a0);
+    pivot_queue<NP, TR, TC>(a0, gridDim.x);
 }
 
 int ladder_padded_size(int n_nu) {
@@ -42,7 +42,7 @@ static hipError_t launch_one(const LadderArgs &a, hipStream_t s) {
 
 template <int NP, int TR, int TC>
 static hipError_t launch_queue(const LadderArgs &a, hipStream_t s) {
-    const int grid = a.n_items < kQueueGroups ? a.n_items : kQueueGroups;
+    const int grid = queue_groups(a.n_items, TR * TC);
     hipLaunchKernelGGL((k_ladder_fp64_queue<NP, TR, TC>), dim3(grid), dim3(TR * TC), 0, s, a);
     return hipGetLastError();
 }

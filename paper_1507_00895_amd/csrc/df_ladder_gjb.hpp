@@ -8,14 +8,14 @@
 // the FP32 ones do not:
 //   - certified items of vertices that are not symmetric, marked by the screening
 //     kernel, which has formed their certificate and Gamma^(2) (SCREENED);
-//   - the refined kernel's items near the instability (its near queue).
+//   - the refined kernel's items near the instability (its near queue);
+//   - every item of a launch too small for the screening to pay.
 // A certified item has rho(M) < 1, i.e. it is inside the radius; those that fail the
-// certificate here are appended to the queue of the partial-pivoting kernel
-// (df_ladder_pivot.hpp).
+// certificate here take partial pivoting (df_ladder_pivot.hpp).
 // Bound: the SIMDs' issue, as df_ladder_sym.hpp.  Non-symmetric vertex, 14,336 items, all
 // launches of a call, us at n_nu 16 / 32 / 48 / 64 / 96 / 128:
 //   one loop over one queue, 768 work-groups      128 266 478 767 2830 5435
-//   here                                           61 164 368 684 2087 4825
+//   here (n_nu 16: k_ladder_all_o3)                52 165 376 681 2094 4808
 //   elimination of every item, no screening        58 165 376 675 2242 5055
 // In one loop the kernel held the registers of both paths (n_nu 128 190 spilled, 96
 // one work-group per CU), and 768 work-groups are one wave each at n_nu 16.
@@ -35,8 +35,10 @@ constexpr double CERT_MAX_F64 = 0.999;
 // slots take every barrier, so an uncertified item is not left early but carried
 // through with its results discarded, and `dummy` marks a slot without an item of its
 // own, which computes a copy of the last item and writes nothing.
+// Returns false, with no results written, for an uncertified item (ITEMS = 1; a slot of
+// several queues it).
 template <int NP, bool FULL, bool SCREENED, int ITEMS>
-__device__ __forceinline__ void gjb_item(LadderArgs a0, int gitem, bool dummy) {
+__device__ __forceinline__ bool gjb_item(LadderArgs a0, int gitem, bool dummy) {
     constexpr int NT = NP / 16;
     typedef MT<double>::v4 d4;
     __shared__ GjShared<double, NP> shv[ITEMS];
@@ -124,9 +126,9 @@ __device__ __forceinline__ void gjb_item(LadderArgs a0, int gitem, bool dummy) {
         const double cw = gj_certify<double, NP, (NP <= 64)>(Cr, Ci, sh, CERT_ITERS, CERT_MAX_F64, tid,
                                                  ITEMS > 1 ? shv : nullptr, ITEMS > 1 ? ITEMS : 0);
         if (!(cw < CERT_MAX_F64)) {
+            if constexpr (ITEMS == 1) return false;   // uniform: every thread of the work-group leaves here
             if (tid == 0 && !dummy) a.queue[atomicAdd(a.queue_count, 1)] = gitem;
-            if constexpr (ITEMS == 1) return;   // uniform: every thread of the work-group leaves here
-            else skip = true;
+            skip = true;
         }
     }
 
@@ -189,40 +191,43 @@ __device__ __forceinline__ void gjb_item(LadderArgs a0, int gitem, bool dummy) {
             }
             st(a.w, ((size_t)cm * n_nu + n) * N + q, wv);
         }
+    return true;
 }
 
-// Position b of a round of m work-groups starting at k0, or -1 beyond it.  The rounds are
-// dealt to the XCDs in contiguous ranges: neighbouring momenta share cache lines.
-__device__ __forceinline__ int round_group(int k0, int groups) {
-    const int left = groups - k0, m = left < (int)gridDim.x ? left : (int)gridDim.x;
-    return (int)blockIdx.x < m ? k0 + xcd_item(blockIdx.x, m) : -1;
+// Position of work-group b of G in the round that starts at k0, or -1 beyond it.  The rounds
+// are dealt to the XCDs in contiguous ranges: neighbouring momenta share cache lines.
+__device__ __forceinline__ int round_group(int k0, int groups, int b, int G) {
+    const int left = groups - k0, m = left < G ? left : G;
+    return b < m ? k0 + xcd_item(b, m) : -1;
 }
 
-// The launch's items (ITEMS per work-group) in rounds of the grid; LDS is reused: a
-// barrier separates the items.  Uniform over the work-group.
-//   SCREENED: those marked CERT_GENERAL.  The marks of 64 rounds are read at once, one
-//             per lane: where there are none (symmetric vertices) the kernel ends after one load.
-//   else:     the near queue, or without one every item.
+// The launch's items (ITEMS per work-group) by work-group b of G, in rounds of G; LDS is
+// reused: a barrier separates the items.  Uniform over the work-group.
+//   SCREENED: those marked CERT_GENERAL, if near_count says that there are any (most calls
+//             end there).  The marks of 64 rounds are read at once, one per lane.
+//   else:     the near queue.
 template <int NP, bool FULL, bool SCREENED, int ITEMS>
-__device__ __forceinline__ void gjb_items(const LadderArgs &a0) {
+__device__ __forceinline__ void gjb_items(const LadderArgs &a0, int b, int G) {
     const int slot = ITEMS > 1 ? __builtin_amdgcn_readfirstlane((int)threadIdx.x / (NP * 4)) : 0;
-    const int n = __builtin_amdgcn_readfirstlane(!SCREENED && a0.near_queue ? *a0.near_count : a0.n_items);
+    const int near = __builtin_amdgcn_readfirstlane(*a0.near_count);
+    if (near == 0) return;
+    const int n = SCREENED ? a0.n_items : near;
     const int groups = (n + ITEMS - 1) / ITEMS;
     auto run = [&](int g) __attribute__((always_inline)) {
         int u = ITEMS * g + slot;
         bool dummy = ITEMS > 1 && u >= n;
         if (dummy) u = n - 1;
-        const int item = __builtin_amdgcn_readfirstlane(!SCREENED && a0.near_queue ? a0.near_queue[u] : a0.item0 + u);
+        const int item = __builtin_amdgcn_readfirstlane(SCREENED ? a0.item0 + u : a0.near_queue[u]);
         if (SCREENED && ITEMS > 1)
             dummy = dummy || __builtin_amdgcn_readfirstlane((int)a0.cert[item]) != CERT_GENERAL;
-        gjb_item<NP, FULL, SCREENED, ITEMS>(a0, item, dummy);
+        const bool done = gjb_item<NP, FULL, SCREENED, ITEMS>(a0, item, dummy);
+        if (!SCREENED && ITEMS == 1 && !done && threadIdx.x == 0) a0.queue[atomicAdd(a0.queue_count, 1)] = item;
         __syncthreads();
     };
     if constexpr (SCREENED) {
-        const int G = gridDim.x;
         for (int k0 = 0; k0 < groups; k0 += 64 * G) {
             const int k = k0 + (int)(threadIdx.x & 63) * G;
-            const int g = k < groups ? round_group(k, groups) : -1;
+            const int g = k < groups ? round_group(k, groups, b, G) : -1;
             bool mine = false;
             if (g >= 0)
                 for (int x = 0; x < ITEMS; ++x)
@@ -236,12 +241,29 @@ __device__ __forceinline__ void gjb_items(const LadderArgs &a0) {
             }
         }
     } else {
-        for (int k0 = 0; k0 < groups; k0 += (int)gridDim.x) {
-            const int g = round_group(k0, groups);
+        for (int k0 = 0; k0 < groups; k0 += G) {
+            const int g = round_group(k0, groups, b, G);
             if (g < 0) break;
             run(g);
         }
     }
+}
+
+// The near queue; or, SCREENED, the queue of the uncertified items (complete before the
+// launch) by its first work-groups and the certified general items by the others.  One
+// launch: both are empty in most calls, and where both have items they run side by
+// side.  A work-group has one of the two paths, each with its own copy of the thread
+// index: neither holds the other's values.
+template <int NP, bool FULL, bool SCREENED, int ITEMS>
+__device__ __forceinline__ void gjb_kernel(const LadderArgs &a0) {
+    constexpr int TC = NP <= 64 ? 8 : 16;
+    const int np = SCREENED ? a0.pivot_groups : 0;
+    if constexpr (SCREENED)
+        if ((int)blockIdx.x < np) {
+            pivot_queue<NP, NP * 4 * ITEMS / TC, TC>(a0, np);
+            return;
+        }
+    gjb_items<NP, FULL, SCREENED, ITEMS>(a0, (int)blockIdx.x - np, (int)gridDim.x - np);
 }
 
 // Register budget: three waves per SIMD up to NP = 64; the compiler's own at 96
@@ -251,62 +273,66 @@ __device__ __forceinline__ void gjb_items(const LadderArgs &a0) {
 // (mask-free launches only: the masked build needs more registers).
 template <int NP, bool FULL, bool SCREENED>
 __global__ __launch_bounds__(NP * 4) void k_ladder_gjb(LadderArgs a0) {
-    gjb_items<NP, FULL, SCREENED, 1>(a0);
+    gjb_kernel<NP, FULL, SCREENED, 1>(a0);
 }
-template <int NP, bool FULL>
+template <int NP, bool FULL, bool SCREENED>
 __global__ __launch_bounds__(NP * 4) __attribute__((amdgpu_waves_per_eu(3, 3)))
 void k_ladder_gjb_o3(LadderArgs a0) {
-    gjb_items<NP, FULL, false, 1>(a0);
-}
-// After the screening, up to NP = 64: its certified general items, then the queue of the
-// uncertified ones, which is complete before the launch.  One launch: both are empty in
-// most calls, and where both have items the tail of the one is filled by the other.
-// Two loops, each with its own copy of the thread index: neither holds the other's values.
-template <int NP, bool FULL>
-__global__ __launch_bounds__(NP * 4) __attribute__((amdgpu_waves_per_eu(3, 3)))
-void k_ladder_rest_o3(LadderArgs a0) {
-    gjb_items<NP, FULL, true, 1>(a0);
-    pivot_queue<NP, NP / 2, 8>(a0);
+    gjb_kernel<NP, FULL, SCREENED, 1>(a0);
 }
 template <int NP, bool FULL, bool SCREENED>
 __global__ __launch_bounds__(NP * 8) void k_ladder_gjb_x2(LadderArgs a0) {
-    gjb_items<NP, FULL, SCREENED, 2>(a0);
+    gjb_kernel<NP, FULL, SCREENED, 2>(a0);
+}
+// Every item of a small launch: an uncertified one is pivoted where it is, in one chain
+// and one launch.
+template <int NP, bool FULL>
+__global__ __launch_bounds__(NP * 4) __attribute__((amdgpu_waves_per_eu(3, 3)))
+void k_ladder_all_o3(LadderArgs a0) {
+    const int item = a0.item0 + xcd_item(blockIdx.x, gridDim.x);
+    if (gjb_item<NP, FULL, false, 1>(a0, item, false)) return;
+    __syncthreads();
+    pivot_item<NP, NP / 2, 8>(a0, item);
 }
 
-// Work-groups of a launch.  Every item (no queue): one each.  A queue: its share of
-// kQueueGroups.  Screened: four times what the device holds at once - in rounds of
-// exactly that, work-groups that start late leave places empty (n_nu 32, 14,336 items 210
-// us, 172 with one work-group per item), and work-groups without an item cost a start each
-// (n_nu 96, 188,416 items of symmetric vertices: 0.3 ms of 13.4 with one per item pair).
+// Work-groups of a launch.  The near queue: kQueueWaves at most.  The screened items: four
+// times what the device holds at once - in rounds of exactly that, work-groups that
+// start late leave places empty (n_nu 32, 14,336 items 210 us, 172 with one work-group per
+// item), and work-groups without an item cost a start each (n_nu 96, 188,416 items of
+// symmetric vertices: 0.3 ms of 13.4 with one per item pair).  pivot: the queue too, as
+// many work-groups as the device holds.
 template <int PER, bool SCREENED, typename K>
-static hipError_t launch_items(K kern, int threads, const LadderArgs &a, hipStream_t s) {
+static hipError_t launch_items(K kern, int threads, LadderArgs a, bool pivot, hipStream_t s) {
     int grid = (a.n_items + PER - 1) / PER;
+    a.pivot_groups = 0;
     if constexpr (SCREENED) {
-        static const int most = 4 * resident_groups((const void *)kern, threads);
-        if (grid > most) grid = most;
+        static const int resident = resident_groups((const void *)kern, threads);
+        if (grid > 4 * resident) grid = 4 * resident;
+        if (pivot) a.pivot_groups = a.n_items < resident ? a.n_items : resident;
     } else {
-        if (a.near_queue && grid > kQueueGroups) grid = kQueueGroups;
+        grid = queue_groups(grid, threads);
     }
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(threads), 0, s, a);
+    hipLaunchKernelGGL(kern, dim3(grid + a.pivot_groups), dim3(threads), 0, s, a);
     return hipGetLastError();
 }
 
 // (explicitly instantiated per size and build in df_ladder_gjb_np*.hip: the large ones
 // take minutes to compile)
 template <int NP, bool FULL, bool SCREENED>
-hipError_t launch_gjb(const LadderArgs &a, hipStream_t s) {
-    if constexpr (NP <= 64) {
-        if constexpr (SCREENED) return launch_items<1, true>(k_ladder_rest_o3<NP, FULL>, NP * 4, a, s);
-        else return launch_items<1, false>(k_ladder_gjb_o3<NP, FULL>, NP * 4, a, s);
-    } else {
-        hipError_t e;
-        if constexpr (NP == 96 && FULL)
-            e = launch_items<2, SCREENED>(k_ladder_gjb_x2<NP, FULL, SCREENED>, NP * 8, a, s);
-        else e = launch_items<1, SCREENED>(k_ladder_gjb<NP, FULL, SCREENED>, NP * 4, a, s);
-        return e != hipSuccess || !SCREENED ? e : launch_ladder_fp64_queue(a, s);
-    }
+hipError_t launch_gjb(const LadderArgs &a, bool pivot, hipStream_t s) {
+    if constexpr (NP <= 64) return launch_items<1, SCREENED>(k_ladder_gjb_o3<NP, FULL, SCREENED>, NP * 4, a, pivot, s);
+    else if constexpr (NP == 96 && FULL)
+        return launch_items<2, SCREENED>(k_ladder_gjb_x2<NP, FULL, SCREENED>, NP * 8, a, pivot, s);
+    else return launch_items<1, SCREENED>(k_ladder_gjb<NP, FULL, SCREENED>, NP * 4, a, pivot, s);
 }
+template <int NP, bool FULL> hipError_t launch_all(const LadderArgs &a, hipStream_t s) {
+    hipLaunchKernelGGL((k_ladder_all_o3<NP, FULL>), dim3(a.n_items), dim3(NP * 4), 0, s, a);
+    return hipGetLastError();
+}
+#define DF_GJB_BUILD_ALL(NP)                                                                \
+    template hipError_t launch_all<NP, true>(const LadderArgs &a, hipStream_t s);           \
+    template hipError_t launch_all<NP, false>(const LadderArgs &a, hipStream_t s);
 #define DF_GJB_BUILD(NP, FULL, SCREENED) \
-    template hipError_t launch_gjb<NP, FULL, SCREENED>(const LadderArgs &a, hipStream_t s);
+    template hipError_t launch_gjb<NP, FULL, SCREENED>(const LadderArgs &a, bool pivot, hipStream_t s);
 
 }  // namespace df

@@ -15,5 +15,8 @@ DF_GJB_BUILD(48, true, true)
 DF_GJB_BUILD(48, true, false)
 DF_GJB_BUILD(48, false, true)
 DF_GJB_BUILD(48, false, false)
+DF_GJB_BUILD_ALL(16)
+DF_GJB_BUILD_ALL(32)
+DF_GJB_BUILD_ALL(48)
 
 }  // namespace df

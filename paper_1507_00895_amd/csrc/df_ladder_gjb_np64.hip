@@ -7,5 +7,6 @@ DF_GJB_BUILD(64, true, true)
 DF_GJB_BUILD(64, true, false)
 DF_GJB_BUILD(64, false, true)
 DF_GJB_BUILD(64, false, false)
+DF_GJB_BUILD_ALL(64)
 
 }  // namespace df

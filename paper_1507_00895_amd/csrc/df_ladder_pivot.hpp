@@ -293,11 +293,11 @@ __device__ __forceinline__ void pivot_item(const LadderArgs &a0, int gitem) {
     }
 }
 
-// The queue of the uncertified items, grid-stride.
+// The queue of the uncertified items by `groups` work-groups from the launch's first, in turn.
 template <int NP, int TR, int TC>
-__device__ __forceinline__ void pivot_queue(const LadderArgs &a0) {
+__device__ __forceinline__ void pivot_queue(const LadderArgs &a0, int groups) {
     const int n = __builtin_amdgcn_readfirstlane(*a0.queue_count);
-    for (int u = (int)blockIdx.x; u < n; u += (int)gridDim.x) {
+    for (int u = (int)blockIdx.x; u < n; u += groups) {
         pivot_item<NP, TR, TC>(a0, __builtin_amdgcn_readfirstlane(a0.queue[u]));
         __syncthreads();
     }

@@ -209,6 +209,8 @@ __device__ __forceinline__ void screen_body(const LadderArgs &a0, const double *
         int base = 0;
         if (lj == 0 && piv) base = atomicAdd(a.queue_count, __popcll(piv));
         base = __builtin_amdgcn_readfirstlane(base);
+        // (every store writes the same value)
+        if (!LAT && __ballot(qin && pass && !sym) && lj == 0) *a.near_count = 1;
         if (put) a.queue[base + __popcll(piv & ((1ull << lj) - 1))] = item0 + item;
     }
 }
@@ -228,7 +230,7 @@ int ladder_screen_blocks(int n_nu, int n_m, int n_q) {
 }
 
 hipError_t launch_ladder_screen(const LadderArgs &a, hipStream_t s) {
-    if (a.n_sblk <= 0 || !a.queue || !a.queue_count) return hipErrorInvalidValue;
+    if (a.n_sblk <= 0 || !a.queue || !a.queue_count || !a.near_count) return hipErrorInvalidValue;
     switch ((a.n_nu + 15) / 16) {
 #define DF_SCREEN(NT) \
     case NT: hipLaunchKernelGGL(k_ladder_screen<NT>, dim3(a.n_sblk), dim3(256), 0, s, a); break;

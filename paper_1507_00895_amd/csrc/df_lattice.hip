@@ -196,10 +196,10 @@ hipError_t launch_lattice_fields(const LatticeFieldArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_lattice_rest(const LadderArgs &a, const double *L, double *lad, int grid, hipStream_t s) {
-    if (grid <= 0 || !a.queue || !a.queue_count) return hipErrorInvalidValue;
+hipError_t launch_lattice_rest(const LadderArgs &a, const double *L, double *lad, hipStream_t s) {
+    if (a.n_items <= 0 || !a.queue || !a.queue_count) return hipErrorInvalidValue;
 #define DF_REST(NP, TR, TC)                                                                              \
-    hipLaunchKernelGGL((k_lattice_rest<NP, TR, TC>), dim3(grid), dim3(TR * TC), 0, s, a, L, lad)
+    hipLaunchKernelGGL((k_lattice_rest<NP, TR, TC>), dim3(queue_groups(a.n_items, TR * TC)), dim3(TR * TC), 0, s, a, L, lad)
     switch (ladder_padded_size(a.n_nu)) {
         case 16: DF_REST(16, 8, 8); break;
         case 32: DF_REST(32, 8, 8); break;

@@ -11,6 +11,6 @@ hipError_t launch_lattice_screen(const LadderArgs &a, const double *L, hipStream
 // lad [2][N] of the certified items of symmetric vertices
 hipError_t launch_lattice_sym(const LadderArgs &a, const double *L, double *lad, hipStream_t s);
 // lad of the queued items, by elimination with partial pivoting
-hipError_t launch_lattice_rest(const LadderArgs &a, const double *L, double *lad, int grid, hipStream_t s);
+hipError_t launch_lattice_rest(const LadderArgs &a, const double *L, double *lad, hipStream_t s);
 
 }  // namespace df

@@ -54,11 +54,11 @@ def check(w, ld, st, ref):
 
 
 # (n_nu, nk of a 2D grid, n_om): launches above the item counts of the sizes' small-launch
-# route (two waves per SIMD, 8192 items at one wave each) and below them
-SHAPES = [(2, 64, 1), (14, 32, 5), (16, 32, 5), (18, 32, 3), (32, 32, 3), (34, 16, 3), (48, 16, 3),
+# route (2560 waves, 32768 items of one wave each) and below them
+SHAPES = [(14, 64, 5), (16, 64, 5), (18, 32, 3), (32, 32, 3), (34, 16, 3), (48, 16, 3),
           (50, 16, 3), (62, 16, 3), (64, 16, 3), (66, 16, 1), (80, 8, 3), (94, 8, 3), (96, 8, 3),
           (98, 8, 3), (112, 8, 1), (126, 8, 1), (128, 8, 1),
-          (2, 4, 1), (14, 8, 3), (16, 8, 3), (32, 8, 3), (48, 8, 3), (50, 8, 3), (64, 8, 3)]
+          (2, 64, 1), (2, 4, 1), (14, 8, 3), (16, 32, 5), (32, 8, 3), (48, 8, 3), (50, 8, 3), (64, 8, 3)]
 
 
 @pytest.mark.parametrize("scale", [0.6, 2.5])

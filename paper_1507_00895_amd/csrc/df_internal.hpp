@@ -113,6 +113,24 @@ __device__ inline bool prep_symmetric(float m, float d) {
     return d <= m * 9.094947e-13f && m < 3.0e38f;
 }
 
+// Symmetric to rounding (see k_gamma_prep): the largest |gamma_ij - gamma_ji|
+// against the largest |gamma|, over the partial maxima of k_gamma_prep.
+// One wave, one chunk per lane; uniform result.
+__device__ __forceinline__ bool vertex_symmetric(const float *part, int n, int c, int lane) {
+    float m = 0.f, d = 0.f;
+    if (lane < prep_chunks(n)) {
+        m = part[4 * lane + c];
+        d = part[4 * lane + 2 + c];
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const float om = __shfl_xor(m, off, 64), od = __shfl_xor(d, off, 64);
+        m = max_nan(m, om);
+        d = max_nan(d, od);
+    }
+    return prep_symmetric(m, d);
+}
+
 // What the screening kernel found of an item: it fails the certificate (and is in the
 // queue), or it is certified and its vertex symmetric or not.
 enum : uint8_t { CERT_NONE = 0, CERT_SYMMETRIC = 1, CERT_GENERAL = 2 };

@@ -21,24 +21,6 @@ namespace df {
 constexpr int SCREEN_STEPS = 6;
 constexpr double SCREEN_MAX = 0.999;
 
-// Symmetric to rounding (see k_gamma_prep): the largest |gamma_ij - gamma_ji|
-// against the largest |gamma|, over the partial maxima of k_gamma_prep.
-// One wave, one chunk per lane; uniform result.
-__device__ __forceinline__ bool vertex_symmetric(const float *part, int n, int c, int lane) {
-    float m = 0.f, d = 0.f;
-    if (lane < prep_chunks(n)) {
-        m = part[4 * lane + c];
-        d = part[4 * lane + 2 + c];
-    }
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const float om = __shfl_xor(m, off, 64), od = __shfl_xor(d, off, 64);
-        m = max_nan(m, om);
-        d = max_nan(d, od);
-    }
-    return prep_symmetric(m, d);
-}
-
 // LAT: the product is gamma L instead (lattice observables' ladder term, n_om = 1).
 template <int NT, bool LAT>
 __device__ __forceinline__ void screen_body(const LadderArgs &a0, const double *L) {

@@ -74,7 +74,10 @@ __global__ __launch_bounds__(TR *TC) void k_lattice_rest(LadderArgs a, const dou
     for (int wi = blockIdx.x; wi < n_all; wi += gridDim.x) {
         const int item = a.queue[wi];
         const int c = item / N, q = item % N;
-        const double *gam = a.gdm + 2 * (size_t)c * n * n;
+        // the matrix that the screening kernel took for y = gamma L: with another one here, D and
+        // y of a symmetrised vertex differ by its antisymmetric part in first order
+        const bool sym = vertex_symmetric(a.symp, n, c, lane);
+        const double *gam = (sym ? a.gsym : a.gdm) + 2 * (size_t)c * n * n;
         cd A[BR][BC];
 #pragma unroll
         for (int b = 0; b < BC; ++b) {

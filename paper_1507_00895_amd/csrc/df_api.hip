@@ -817,42 +817,42 @@ bool acc_weights(const AccState &S, int slots, int newest, double *coef) {
 
 // ---- lattice observables (df_lattice.h) ---------------------------------------
 struct LatticeLayout {
-    size_t fields, gr, bub;           // [3][n_nu][N] each: G~, frak G, G_lat; their chi~, L, bubble
-    size_t gdm, pdm, gtr, gp32, gtr32, gsym, gabs, symp;   // vertex at Omega = 0
-    size_t cert, w, queue, ints, lad;
+    size_t fields;                    // [3][n_nu][N]: G~, frak G, G_lat; then their chi~, L, bubble
+    size_t gr;                        // [3][n_nu][N]: the fields' transforms; then gamma L [2][n_nu][N]
+    size_t gdm, gtr, gsym, gabs, symp;   // vertex at Omega = 0
+    size_t cert, queue, count, lad;
     size_t total;
 };
 
+// The size is what the interface has always asked for, seven fields, [2][N] and up to 512
+// n_nu x (n_nu + 1) matrices: a workspace of that size stays good.  Regions take the place of
+// others that are not needed any more, and each starts at the next 16 bytes.
 LatticeLayout lattice_layout_of(const Shape &s) {
     LatticeLayout L;
     const size_t fld = (size_t)s.n_nu * s.N * 16, gam = 2 * (size_t)s.n_nu * s.n_nu * 16;
     size_t o = 0;
     auto take = [&](size_t bytes) {
         size_t at = o;
-        o = align_up(o + bytes);
+        o = (o + bytes + 15) & ~(size_t)15;
         return at;
     };
     L.fields = take(3 * fld);
     L.gr = take(3 * fld);
-    L.bub = take(3 * fld);
     L.gdm = take(gam);
-    L.pdm = take(gam);
     L.gtr = take(gam);
-    L.gp32 = take(gam);
-    L.gtr32 = take(gam / 2);
     L.gsym = take(gam);
     L.gabs = take(gam / 4);
-    L.symp = take((size_t)kPrepChunks * 4 * sizeof(float));
-    L.cert = take(2 * (size_t)s.N);
-    L.w = take(2 * fld);
+    L.symp = take((size_t)prep_chunks(s.n_nu) * 4 * sizeof(float));
     L.queue = take(2 * (size_t)s.N * sizeof(int));
-    L.ints = take(sizeof(int));
+    L.cert = take(2 * (size_t)s.N);
+    L.count = take(sizeof(int));
     L.lad = take(2 * (size_t)s.N * 16);
-    // the size stays what the interface has asked for so far (seven fields and up to
-    // 512 n_nu x (n_nu + 1) matrices), of which the above is the smaller part
-    const size_t chunk = 2 * s.N < 512 ? 2 * (size_t)s.N : 512;
-    const size_t asked = 7 * fld + 2 * (size_t)s.N * 16 + chunk * s.n_nu * (s.n_nu + 1) * 16;
-    L.total = o > asked ? o : align_up(asked);
+    size_t asked = 0;
+    for (int f = 0; f < 7; ++f) asked += align_up(fld);
+    asked += align_up(2 * (size_t)s.N * 16);
+    const size_t matrices = 2 * s.N < 512 ? 2 * (size_t)s.N : 512;
+    asked += align_up(matrices * s.n_nu * (s.n_nu + 1) * 16);
+    L.total = o > asked ? o : asked;
     return L;
 }
 
@@ -1519,9 +1519,9 @@ int df_lattice(const df_inst_t *inst, double mu, double *sigma_lat, double *g_la
     s3.n_om = 1;
     s3.n_nu = 3 * s.n_nu;
     rc = stage_transform_gd(s3, f.gd, at<double>(ws, L.gr), st);
-    if (rc == DF_OK) rc = stage_bubble(p, s3, at<double>(ws, L.gr), at<double>(ws, L.bub), nullptr, 0, st);
+    if (rc == DF_OK) rc = stage_bubble(p, s3, at<double>(ws, L.gr), f.gd, nullptr, 0, st);
     if (rc != DF_OK) return rc;
-    const double *chi0 = at<double>(ws, L.bub), *Lq = chi0 + fld, *bub = chi0 + 2 * fld;
+    const double *chi0 = f.gd, *Lq = chi0 + fld, *bub = chi0 + 2 * fld;
 
     // the ladder term with the ladder kernels on the vertex at Omega = 0
     GammaPrepArgs g{};
@@ -1531,26 +1531,22 @@ int df_lattice(const df_inst_t *inst, double mu, double *sigma_lat, double *g_la
     g.guu = p.gamma_uu + v0;
     g.gud = p.gamma_ud + v0;
     g.gdm = at<double>(ws, L.gdm);
-    g.pdm = at<double>(ws, L.pdm);
     g.gtr = at<double>(ws, L.gtr);
-    g.gp32 = at<float>(ws, L.gp32);
-    g.gtr32 = at<float>(ws, L.gtr32);
     g.gsym = at<double>(ws, L.gsym);
     g.gabs = at<float>(ws, L.gabs);
     g.symp = at<float>(ws, L.symp);
-    g.zero = at<int>(ws, L.ints);
+    g.zero = at<int>(ws, L.count);
     g.n_zero = 1;
     HIPCHK(launch_gamma_prep(g, st));
     LadderArgs c{};
     c.gdm = g.gdm;
-    c.pdm = g.pdm;
     c.gtr = g.gtr;
     c.gsym = g.gsym;
     c.gabs = g.gabs;
     c.symp = g.symp;
     c.cert = at<uint8_t>(ws, L.cert);
     c.chi = chi0;
-    c.w = at<double>(ws, L.w);
+    c.w = at<double>(ws, L.gr);   // (the transforms are not needed any more)
     c.n_nu = s.n_nu;
     c.n_om = 1;
     c.N = s.N;

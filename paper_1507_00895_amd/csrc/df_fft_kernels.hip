@@ -274,10 +274,10 @@ __global__ __launch_bounds__(256) void k_gamma_prep(GammaPrepArgs a) {
             const cd p = g * gt;
             const size_t o = c * tot + e;
             st(a.gdm, o, g);
-            st(a.pdm, o, p);
+            if (a.pdm) st(a.pdm, o, p);
             st(a.gtr, o, gt);
-            st4f(a.gp32, o, (float)g.re, (float)g.im, (float)p.re, (float)p.im);
-            st2f(a.gtr32, o, (float)gt.re, (float)gt.im);
+            if (a.gp32) st4f(a.gp32, o, (float)g.re, (float)g.im, (float)p.re, (float)p.im);
+            if (a.gtr32) st2f(a.gtr32, o, (float)gt.re, (float)gt.im);
             st(a.gsym, o, cd{0.5 * (g.re + gt.re), 0.5 * (g.im + gt.im)});
             // |gamma|, transposed (a modulus below the FP32 range counts as its
             // smallest normal value)

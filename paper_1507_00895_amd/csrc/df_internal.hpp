@@ -92,8 +92,8 @@ struct GammaPrepArgs {
     int n_nu, n_om;
     const double *guu, *gud;
     double *gdm;                     // [2][n_om][n_nu][n_nu]
-    double *pdm;                     // [2][n_om][n_nu][n_nu]
-    double *gtr;                     // [2][n_om][n_nu][n_nu] (may be null)
+    double *pdm;                     // [2][n_om][n_nu][n_nu] (may be null)
+    double *gtr;                     // [2][n_om][n_nu][n_nu]
     float *gp32;                     // [2][n_om][n_nu][n_nu] (gamma, gamma_ij gamma_ji) in FP32, or null
     float *gtr32;                    // [2][n_om][n_nu][n_nu] gamma transposed in FP32, or null
     double *gsym;                    // [2][n_om][n_nu][n_nu] (gamma + gamma^T) / 2

@@ -817,42 +817,49 @@ bool acc_weights(const AccState &S, int slots, int newest, double *coef) {
 
 // ---- lattice observables (df_lattice.h) ---------------------------------------
 struct LatticeLayout {
-    size_t fields;                    // [3][n_nu][N]: G~, frak G, G_lat; then their chi~, L, bubble
-    size_t gr;                        // [3][n_nu][N]: the fields' transforms; then gamma L [2][n_nu][N]
+    size_t fields, gr;                // [3][n_nu][N] each: G~, frak G, G_lat; their transforms
+    size_t bub;                       // [3][n_nu][N]: their chi~, L, bubble
+    size_t w;                         // gamma L [2][n_nu][N]
     size_t gdm, gtr, gsym, gabs, symp;   // vertex at Omega = 0
     size_t cert, queue, count, lad;
     size_t total;
 };
 
 // The size is what the interface has always asked for, seven fields, [2][N] and up to 512
-// n_nu x (n_nu + 1) matrices: a workspace of that size stays good.  Regions take the place of
-// others that are not needed any more, and each starts at the next 16 bytes.
+// n_nu x (n_nu + 1) matrices: a workspace of that size stays good.  Where it is too small for
+// regions of their own, the bubbles take the place of the fields and gamma L that of the
+// transforms, which are not needed any more (32x32, n_nu 64: 1.7 us slower).
 LatticeLayout lattice_layout_of(const Shape &s) {
-    LatticeLayout L;
     const size_t fld = (size_t)s.n_nu * s.N * 16, gam = 2 * (size_t)s.n_nu * s.n_nu * 16;
-    size_t o = 0;
-    auto take = [&](size_t bytes) {
-        size_t at = o;
-        o = (o + bytes + 15) & ~(size_t)15;
-        return at;
-    };
-    L.fields = take(3 * fld);
-    L.gr = take(3 * fld);
-    L.gdm = take(gam);
-    L.gtr = take(gam);
-    L.gsym = take(gam);
-    L.gabs = take(gam / 4);
-    L.symp = take((size_t)prep_chunks(s.n_nu) * 4 * sizeof(float));
-    L.queue = take(2 * (size_t)s.N * sizeof(int));
-    L.cert = take(2 * (size_t)s.N);
-    L.count = take(sizeof(int));
-    L.lad = take(2 * (size_t)s.N * 16);
     size_t asked = 0;
     for (int f = 0; f < 7; ++f) asked += align_up(fld);
     asked += align_up(2 * (size_t)s.N * 16);
     const size_t matrices = 2 * s.N < 512 ? 2 * (size_t)s.N : 512;
     asked += align_up(matrices * s.n_nu * (s.n_nu + 1) * 16);
-    L.total = o > asked ? o : asked;
+    LatticeLayout L;
+    for (const bool apart : {true, false}) {
+        size_t o = 0;
+        auto take = [&](size_t bytes) {
+            size_t at = o;
+            o = (o + bytes + 15) & ~(size_t)15;
+            return at;
+        };
+        L.fields = take(3 * fld);
+        L.gr = take(3 * fld);
+        L.bub = apart ? take(3 * fld) : L.fields;
+        L.w = apart ? take(2 * fld) : L.gr;
+        L.gdm = take(gam);
+        L.gtr = take(gam);
+        L.gsym = take(gam);
+        L.gabs = take(gam / 4);
+        L.symp = take((size_t)prep_chunks(s.n_nu) * 4 * sizeof(float));
+        L.queue = take(2 * (size_t)s.N * sizeof(int));
+        L.cert = take(2 * (size_t)s.N);
+        L.count = take(sizeof(int));
+        L.lad = take(2 * (size_t)s.N * 16);
+        L.total = o > asked ? o : asked;
+        if (o <= asked) break;
+    }
     return L;
 }
 
@@ -1519,9 +1526,9 @@ int df_lattice(const df_inst_t *inst, double mu, double *sigma_lat, double *g_la
     s3.n_om = 1;
     s3.n_nu = 3 * s.n_nu;
     rc = stage_transform_gd(s3, f.gd, at<double>(ws, L.gr), st);
-    if (rc == DF_OK) rc = stage_bubble(p, s3, at<double>(ws, L.gr), f.gd, nullptr, 0, st);
+    if (rc == DF_OK) rc = stage_bubble(p, s3, at<double>(ws, L.gr), at<double>(ws, L.bub), nullptr, 0, st);
     if (rc != DF_OK) return rc;
-    const double *chi0 = f.gd, *Lq = chi0 + fld, *bub = chi0 + 2 * fld;
+    const double *chi0 = at<double>(ws, L.bub), *Lq = chi0 + fld, *bub = chi0 + 2 * fld;
 
     // the ladder term with the ladder kernels on the vertex at Omega = 0
     GammaPrepArgs g{};
@@ -1546,7 +1553,7 @@ int df_lattice(const df_inst_t *inst, double mu, double *sigma_lat, double *g_la
     c.symp = g.symp;
     c.cert = at<uint8_t>(ws, L.cert);
     c.chi = chi0;
-    c.w = at<double>(ws, L.gr);   // (the transforms are not needed any more)
+    c.w = at<double>(ws, L.w);
     c.n_nu = s.n_nu;
     c.n_om = 1;
     c.N = s.N;

@@ -373,9 +373,10 @@ __device__ __forceinline__ double gj_certify(const typename MT<T>::v4 (&Cr)[NP /
             for (int r = 0; r < 4; ++r) {
                 const float vi = (it == 0) ? 1.0f : (float)v[16 * w + MT<T>::row(lg, r)];
                 const float rr = u[r] * __builtin_amdgcn_rcpf(vi);
-                ratio = rr > ratio ? rr : ratio;
+                ratio = max_nan(ratio, rr);
             }
-            const double m = wave_max_pos((double)ratio);
+            // (a NaN - an element beyond the FP32 range, times 1 / infinity - never passes)
+            const double m = wave_max_pos(ratio == ratio ? (double)ratio : (double)INFINITY);
             if (l == 0) sh.wmax[it & 1][w] = m;
             if (lj == 0) {
 #pragma unroll
@@ -407,9 +408,10 @@ __device__ __forceinline__ double gj_certify(const typename MT<T>::v4 (&Cr)[NP /
             for (int r = 0; r < 4; ++r) {
                 // from v = 1 the first bound is the largest row sum of B
                 const float rr = v ? u[r] * __builtin_amdgcn_rcpf((float)v[16 * w + MT<T>::row(lg, r)]) : u[r];
-                ratio = rr > ratio ? rr : ratio;
+                ratio = max_nan(ratio, rr);
             }
-            const double m = wave_max_pos((double)ratio);
+            // (a NaN - an element beyond the FP32 range, times 1 / infinity - never passes)
+            const double m = wave_max_pos(ratio == ratio ? (double)ratio : (double)INFINITY);
             if (l == 0) sh.wmax[it & 1][w] = m;
             if (lj == 0) {
 #pragma unroll

@@ -34,8 +34,10 @@
  * it with df_workspace_size; it must be 256-byte aligned).  The library never
  * allocates or frees caller memory; it keeps no state between calls apart
  * from compiled kernels, the autotuner's table of ladder kernel choices
- * (df_autotune) and at most eight page-locked host buffers of 256 KiB, into which
- * df_iterate reads back and which later calls of any thread reuse.  Calls are asynchronous on the given stream, except
+ * (df_autotune) and at most eight page-locked host buffers, 8 MiB together, into which
+ * df_iterate reads back and which later calls of any thread reuse (a readback above 4 MiB,
+ * some 500 instances, allocates and frees its buffer in the call).  Calls are asynchronous
+ * on the given stream, except
  * df_iterate which synchronises that stream to read back the convergence
  * measure once per iteration, and df_autotune.  Calls on distinct workspaces may run
  * concurrently; two calls sharing a workspace must be ordered by the caller.

@@ -13,6 +13,7 @@
 #include "../../include/df_lattice.h"
 #include "df_internal.hpp"
 #include "df_lattice_ladder.hpp"
+#include "df_pinned.hpp"
 #include "df_tune.hpp"
 
 using namespace df;
@@ -485,45 +486,28 @@ bool norm_diff(const double *part, int n, double *diff) {
     return isfinite(d[0]) && isfinite(m[0]);
 }
 
-// Page-locked host memory for one call's readbacks and table upload (from pageable
-// memory the runtime stages every copy: two of them took 25 us of an 87 us
-// iteration).  Buffers up to kPinnedBytes go back to a list of at most kPinnedKept for
-// later calls of any thread; larger or further ones are freed.  Without page-locked
-// memory the lease falls back to ordinary memory.
-constexpr size_t kPinnedBytes = 256 * 1024;
-constexpr size_t kPinnedKept = 8;
-std::mutex g_pinned_mu;
-std::vector<void *> g_pinned;
+// Page-locked host memory for one call's readbacks (into pageable memory the runtime
+// stages every copy: two of them took 25 us of an 87 us iteration), leased from a bounded
+// pool.  Without page-locked memory the lease falls back to ordinary memory.
+void *pinned_alloc(size_t bytes) {
+    void *p = nullptr;
+    if (hipHostMalloc(&p, bytes, hipHostMallocPortable) == hipSuccess) return p;
+    (void)hipGetLastError();
+    return nullptr;
+}
+void pinned_release(void *p) { (void)hipHostFree(p); }
+PinnedPool g_pinned(pinned_alloc, pinned_release);
 
 class PinnedLease {
 public:
-    explicit PinnedLease(size_t bytes) : pooled_(bytes <= kPinnedBytes) {
-        if (pooled_) {
-            std::lock_guard<std::mutex> lk(g_pinned_mu);
-            if (!g_pinned.empty()) {
-                p_ = g_pinned.back();
-                g_pinned.pop_back();
-                return;
-            }
-        }
-        if (hipHostMalloc(&p_, pooled_ ? kPinnedBytes : bytes, hipHostMallocPortable) != hipSuccess) {
-            (void)hipGetLastError();
-            p_ = nullptr;
-            plain_.resize(bytes);
-        }
+    explicit PinnedLease(size_t bytes) {
+        p_ = g_pinned.take(bytes, &cap_);
+        if (!p_) plain_.resize(bytes);
     }
     ~PinnedLease() {
         // (after a failed call a copy may still be on its way into the buffer: it is
         // given up)
-        if (!p_ || !idle_) return;
-        if (pooled_) {
-            std::lock_guard<std::mutex> lk(g_pinned_mu);
-            if (g_pinned.size() < kPinnedKept) {
-                g_pinned.push_back(p_);
-                return;
-            }
-        }
-        (void)hipHostFree(p_);
+        if (p_ && idle_) g_pinned.give(p_, cap_);
     }
     PinnedLease(const PinnedLease &) = delete;
     PinnedLease &operator=(const PinnedLease &) = delete;
@@ -540,8 +524,8 @@ public:
 
 private:
     void *p_ = nullptr;
+    size_t cap_ = 0;
     bool idle_ = true;
-    bool pooled_;
     std::vector<char> plain_;
 };
 

@@ -90,8 +90,20 @@ int mix_blocks(const Shape &s) {
     return blocks > kMixBlocks ? kMixBlocks : blocks;
 }
 
-// norm partials of one iteration: from the Schwinger-Dyson kernel itself where it mixes
-int norm_parts(const Shape &s, int accel) { return accel > 0 || s.n_chunks > 1 ? mix_blocks(s) : s.n_nu; }
+// sigma_calc in W's own memory: then no work-group may write it before all have read W
+bool sigma_over_w(const df_inst_t &p, const Shape &s) {
+    const uintptr_t a = (uintptr_t)p.sigma_calc, b = (uintptr_t)p.w;
+    const size_t fld = (size_t)s.n_nu * s.N * 16;
+    return a && b && a < b + 2 * s.n_om * fld && b < a + fld;
+}
+
+// The Schwinger-Dyson kernel writes sigma_calc (and mixes) itself: one chunk
+bool sigma_one_pass(const df_inst_t &p, const Shape &s) { return s.n_chunks == 1 && !sigma_over_w(p, s); }
+
+// norm partials of one iteration
+int norm_parts(const df_inst_t &p, const Shape &s, int accel) {
+    return accel > 0 || !sigma_one_pass(p, s) ? mix_blocks(s) : s.n_nu;
+}
 
 // Per-instance workspace regions (byte offsets from the instance base).
 struct Layout {
@@ -451,8 +463,9 @@ int stage_sigma(const df_inst_t &p, const Shape &s, void *ws, size_t base, const
     a.sigma_calc = sigma_calc;
     a.sigma = sigma;
     a.norm_part = norm;
+    a.one_pass = sigma_one_pass(p, s);
     HIPCHK(launch_sigma_part(a, st));
-    if (s.n_chunks == 1) return DF_OK;
+    if (a.one_pass) return DF_OK;
     ReduceMixArgs r{};
     r.count = (size_t)s.n_nu * s.N;
     r.n_chunks = s.n_chunks;
@@ -716,12 +729,19 @@ int queue_fused_iteration(const df_inst_t *inst, const Plan &P, const Fused &F,
         const Layout &L = P.lay[i];
         const size_t b = P.base[i];
         const double *w = inst[i].w ? inst[i].w : at<double>(ws, b + L.w);
+        bool sym = o.symmetry != 0;
+        if (sym && sigma_over_w(inst[i], s)) {
+            // sigma_calc lies over W: W is completed first, not after the loop
+            rc = stage_sym_expand(s, ws, b, L, inst[i].w, inst[i].logdet, inst[i].status, st);
+            if (rc != DF_OK) return rc;
+            sym = false;
+        }
         // (accelerated: F(x) only, the step follows outside this sequence)
         if (o.accel > 0)
-            rc = stage_sigma(inst[i], s, ws, b, L, w, o.symmetry != 0, at<double>(ws, b + L.fx), nullptr,
+            rc = stage_sigma(inst[i], s, ws, b, L, w, sym, at<double>(ws, b + L.fx), nullptr,
                              0.0, nullptr, st);
         else
-            rc = stage_sigma(inst[i], s, ws, b, L, w, o.symmetry != 0, inst[i].sigma_calc, inst[i].sigma,
+            rc = stage_sigma(inst[i], s, ws, b, L, w, sym, inst[i].sigma_calc, inst[i].sigma,
                              o.mix, norm_part(P, ws, i), st);
         if (rc != DF_OK) return rc;
     }
@@ -1263,7 +1283,7 @@ int df_iterate(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts, int
         std::vector<int> next;
         for (int i : act) {
             double diff = 0.0;
-            const bool finite = norm_diff(hnorms + P.norm0[i], norm_parts(P.shape[i], opts->accel), &diff);
+            const bool finite = norm_diff(hnorms + P.norm0[i], norm_parts(inst[i], P.shape[i], opts->accel), &diff);
             last[i] = diff;
             fell_back[i] = hints[kIntsInst + i] != 0;
             if (!finite || !isfinite(diff)) {
@@ -1297,6 +1317,7 @@ int df_iterate(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts, int
         bool any = false;
         for (int i = 0; i < n_inst; ++i) {
             if (!inst[i].w && !inst[i].logdet && !inst[i].status) continue;
+            if (sigma_over_w(inst[i], P.shape[i])) continue;   // (done in the loop)
             const Layout &L = P.lay[i];
             double *w = inst[i].w ? inst[i].w : at<double>(ws, P.base[i] + L.w);
             rc = stage_sym_expand(P.shape[i], ws, P.base[i], L, w, inst[i].logdet, inst[i].status, st);

@@ -354,7 +354,8 @@ hipError_t launch_bubble(const BubbleArgs &a, hipStream_t s) {
 
 template <typename P, typename Q> static hipError_t launch_sigma_grid(const SigmaArgs &a, hipStream_t s) {
     const dim3 grid(a.n_nu, a.n_chunks), block(P::T);
-    const bool all = a.n_chunks == 1;
+    const bool all = a.one_pass != 0;
+    if (all && a.n_chunks != 1) return hipErrorInvalidValue;
     if (a.qrep && all) hipLaunchKernelGGL((k_sigma_part<P, Q, true, true>), grid, block, 0, s, a);
     else if (a.qrep) hipLaunchKernelGGL((k_sigma_part<P, Q, true, false>), grid, block, 0, s, a);
     else if (all) hipLaunchKernelGGL((k_sigma_part<P, Q, false, true>), grid, block, 0, s, a);

@@ -45,11 +45,12 @@ struct SigmaArgs {
     double beta;
     const double *w;                 // [2][n_om][n_nu][N]
     const double *gr;                // [n_nu][N]
-    double *part;                    // [n_chunks][n_nu][N], n_chunks > 1
+    double *part;                    // [n_chunks][n_nu][N], unless one_pass
     // symmetry-reduced W: only m index >= im0 and q = qrep[q] are read (null: all)
     const int *qrep;
     int im0;
-    // n_chunks = 1: k_reduce_mix's outputs, norm_part [n_nu][2]
+    // one_pass (n_chunks = 1): k_reduce_mix's outputs, norm_part [n_nu][2]
+    int one_pass;
     double alpha;
     double *sigma_calc;
     double *sigma;

@@ -244,13 +244,35 @@ def kernel_symbol(variant: str, np_: int, full: bool = True) -> str:
 
 
 def fp64_launches(n_nu: int):
-    """Kernels of a certified FP64 ladder call, in order: certificate and second order;
-    items of symmetric vertices; the rest (none on the bench workloads)."""
+    """Kernels of a certified FP64 ladder call of the bench's sizes, in order: certificate and
+    second order; items of symmetric vertices; the rest (none on the bench workloads)."""
     nt = (n_nu + 15) // 16
     np_ = next(s for s in (16, 32, 48, 64, 96, 128) if n_nu <= s)
-    rest = "k_ladder_rest_o3" if np_ <= 64 else "k_ladder_rest"
-    return [f"k_ladder_screen<{nt}>", f"k_ladder_sym<{nt}, {'false' if n_nu % 16 else 'true'}>",
-            f"{rest}<{np_}>"]
+    full = "true" if n_nu == np_ else "false"
+    rest = "k_ladder_gjb_o3" if np_ <= 64 else "k_ladder_gjb_x2" if n_nu == 96 else "k_ladder_gjb"
+    out = [f"k_ladder_screen<{nt}>", f"k_ladder_sym<{nt}, {'false' if n_nu % 16 else 'true'}>",
+           f"{rest}<{np_}, {full}, true>"]
+    return out + (["k_ladder_fp64_queue<96, 16, 16>"] if np_ == 96 else [])
+
+
+def sym_products(nt: int) -> int:
+    """Complex 16 x 16 x 16 products of the symmetric block ladder with nt blocks: at step t
+    H = K S_tj for every other block, and the updates of the tiles with an unfinished
+    block (nt 4 / 6 / 8: 32 / 100 / 224)."""
+    return sum((nt - 1) + (nt - 1 - t) + (nt * (nt - 1) // 2 - t * (t + 1) // 2) for t in range(nt))
+
+
+def as_run(roof, n_nu: int):
+    """The roofline entry of a certified FP64 choice by what its kernels do: the symmetric
+    kernel by name, and the rate and fraction of the matrix operations it makes (three
+    real products per complex one) over the time of all its launches."""
+    if "launches" not in roof:
+        return roof
+    share = sym_products((n_nu + 15) // 16) * 3 * 2 * 16 ** 3 / ladder_flops(n_nu)
+    out = dict(roof, kernel=roof["launches"][1], achieved=roof["achieved"] * share, frac=roof["frac"] * share,
+               executed_flops_per_launch=roof["algorithmic_flops_per_launch"] * share,
+               algorithmic_achieved=roof["achieved"])
+    return out
 
 
 def roofline_of(prec, B, n_om, N, n_nu, lad_ms, n_inst=1):
@@ -272,12 +294,11 @@ def roofline_of(prec, B, n_om, N, n_nu, lad_ms, n_inst=1):
         t_unit = 2.0 / FP32_PEAK_TFLOPS + 1.0 / FP64_PEAK_TFLOPS
         peak = 3.0 / t_unit
     achieved = flops_launch / (lad_ms * 1e-3) / 1e12
-    # The unit of work stays the dense complex inverse (8 n^3 flops per solve), whatever
-    # the kernels do instead: the symmetric block ladder makes about half of it, so
-    # its fraction may pass 1.
+    # The unit of work here stays the dense complex inverse (8 n^3 flops per solve), whatever
+    # the kernels do instead; as_run() prices what they do.
     certified = {"launches": fp64_launches(n_nu),
-                 "unit_of_work": "8 n_nu^3 real flops per solve (dense complex inverse); the symmetric "
-                                 "block ladder makes about half of them"} if base.startswith("gjb") else {}
+                 "unit_of_work": "achieved and frac: matrix operations made; algorithmic_*: 8 n_nu^3 real "
+                                 "flops per solve (dense complex inverse)"} if base.startswith("gjb") else {}
     return {**certified, "bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
             "frac": achieved / peak,
             "traffic": measured_traffic(certified["launches"][1] if certified else kernel_name,
@@ -415,7 +436,7 @@ def cubic16_leg(B, args, log):
         if not args.no_tune:
             B.df_autotune(insts, ws, B.make_opts(prec=pr), stream=stream.cuda_stream)
         ms = ladder_launch_ms(B, insts, ws, pr, stream, 3)
-        roof = roofline_of(pr, B, p.n_om, p.N, p.n_nu, ms)
+        roof = as_run(roofline_of(pr, B, p.n_om, p.N, p.n_nu, ms), p.n_nu)
         out[name] = {"ladder_variant": B.df_ladder_variant(p.n_nu, pr), "ladder_launch_ms": ms,
                      "ladder_solves_per_s": 2 * p.n_om * p.N / (ms * 1e-3),
                      "roofline_frac": roof["frac"], "roofline_achieved": roof["achieved"],
@@ -599,7 +620,7 @@ def main():
     p0 = problems[0]
     reps = max(3, args.steps)
     lad_ms = ladder_launch_ms(B, insts, ws, prec, stream, reps)
-    roof = roofline_of(prec, B, p0.n_om, p0.N, p0.n_nu, lad_ms, len(insts))
+    roof = as_run(roofline_of(prec, B, p0.n_om, p0.N, p0.n_nu, lad_ms, len(insts)), p0.n_nu)
 
     if args.copy_calibration:
         # a plain copy kernel of known size: 256 MiB read + 256 MiB written
@@ -621,8 +642,8 @@ def main():
                 ms = lad_ms if pr == prec else ladder_launch_ms(B, insts, ws, pr, stream, reps)
                 entry = {"ladder_variant": B.df_ladder_variant(p0.n_nu, pr), "ladder_launch_ms": ms,
                          "ladder_solves_per_s": 2 * p0.n_om * p0.N / (ms * 1e-3),
-                         "roofline_frac": roofline_of(pr, B, p0.n_om, p0.N, p0.n_nu, ms,
-                                                     len(insts))["frac"]}
+                         "roofline_frac": as_run(roofline_of(pr, B, p0.n_om, p0.N, p0.n_nu, ms,
+                                                             len(insts)), p0.n_nu)["frac"]}
             if pr != B.DF_FP32:       # FP32 alone does not reach the FP64 fixed point
                 conv = converge_each(B, problems, insts, ws, pr, stream, args.graph)
                 entry.update({"s_per_converged_sigma": float(np.mean([c["seconds"] for c in conv])),

@@ -239,11 +239,11 @@ int df_autotune(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts, vo
  * "fp32_o4", "fp32_o5" for FP32 alone.  The "gjb" choices, with or without a launch
  * shape ("@p1", "@p2" after "gjb" or "gjb_o3"), run the same kernels and keep their
  * names for saved tables: screening (certificate), the symmetric block ladder for
- * vertices symmetric in their two frequencies, and one kernel for the rest
- * (certified elimination for other vertices, partial pivoting for uncertified
- * items).  Sizes: every class serves n_nu <= 128; "_o3" exists up to n_nu 64
- * (refined: 96), "_o4" and "_o5" up to 64.  A choice always belongs to the requested
- * precision class; the refined kernels hand their near-instability items to the
+ * vertices symmetric in their two frequencies, and certified elimination of other
+ * vertices' items beside partial pivoting of uncertified ones; small launches (n_nu <= 64)
+ * certify and eliminate every item in one kernel.  Sizes: every class serves
+ * n_nu <= 128; "_o3" exists up to n_nu 64 (refined: 96), "_o4" and "_o5" up to 64.  A
+ * choice always belongs to the requested precision class; the refined kernels hand their near-instability items to the
  * FP64 elimination, and every certified kernel its uncertified items to partial
  * pivoting, within the call. */
 int df_ladder_variant(int32_t n_nu, int32_t prec, char *name, size_t name_len);

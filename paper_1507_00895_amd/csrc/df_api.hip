@@ -638,7 +638,7 @@ LadderInst table_entry(const Plan &P, int i, void *ws, bool sym, const double *c
         d.im0 = s.im0;
     }
     *items += sym ? s.items_sym : s.items;
-    *sblocks += ladder_screen_blocks(s.n_nu, s.n_om - (sym ? s.im0 : 0), sym ? s.n_irr : s.N);
+    *sblocks += ladder_screen_blocks(s.n_om - (sym ? s.im0 : 0), sym ? s.n_irr : s.N);
     return d;
 }
 
@@ -1064,7 +1064,7 @@ int df_ladder_solve(const df_inst_t *inst, int32_t n_inst, const df_opts_t *opts
         a.gsym = at<double>(ws, b + L.gsym);
         a.gabs = at<float>(ws, b + L.gabs);
         a.symp = at<float>(ws, b + L.symp);
-        a.n_sblk = ladder_screen_blocks(s.n_nu, s.n_om - (sym ? s.im0 : 0), sym ? s.n_irr : s.N);
+        a.n_sblk = ladder_screen_blocks(s.n_om - (sym ? s.im0 : 0), sym ? s.n_irr : s.N);
         a.chi = inst[i].chi;
         a.w = inst[i].w;
         a.logdet = inst[i].logdet;
@@ -1563,7 +1563,7 @@ int df_lattice(const df_inst_t *inst, double mu, double *sigma_lat, double *g_la
     c.n_om = 1;
     c.N = s.N;
     c.n_items = 2 * s.N;
-    c.n_sblk = ladder_screen_blocks(s.n_nu, 1, s.N);
+    c.n_sblk = ladder_screen_blocks(1, s.N);
     c.queue = at<int>(ws, L.queue);
     c.queue_count = g.zero;
     double *lad = at<double>(ws, L.lad);

@@ -349,10 +349,9 @@ bool ladder_fp32_has_occ(int n_nu, int occ);
 hipError_t launch_ladder_mixed(const LadderArgs &a, int occ, int grid, hipStream_t s);
 hipError_t launch_ladder_fp32(const LadderArgs &a, int occ, int grid, hipStream_t s);
 // FP64 ladder of symmetric vertices (n_nu <= 128) behind its screening kernel,
-// which leaves t = (gamma chi gamma)_nn in W, marks the certified items of
-// symmetric vertices and queues the rest (near_queue: not symmetric; queue:
-// not certified)
-int ladder_screen_blocks(int n_nu, int n_m, int n_q);
+// which leaves t = (gamma chi gamma)_nn in W, marks the certified items by whether their
+// vertex is symmetric (cert) and queues the uncertified ones (queue)
+int ladder_screen_blocks(int n_m, int n_q);
 hipError_t launch_ladder_screen(const LadderArgs &a, hipStream_t s);
 hipError_t launch_ladder_sym(const LadderArgs &a, hipStream_t s);
 hipError_t launch_zero_ints(int *p, int n, hipStream_t s);

@@ -206,8 +206,7 @@ template <int NT> __global__ __launch_bounds__(256) void k_lattice_screen(Ladder
 
 // work-groups of one instance's screening: channels x bosonic indices x blocks of
 // 16 momenta
-int ladder_screen_blocks(int n_nu, int n_m, int n_q) {
-    (void)n_nu;
+int ladder_screen_blocks(int n_m, int n_q) {
     return 2 * n_m * ((n_q + 15) / 16);
 }
 

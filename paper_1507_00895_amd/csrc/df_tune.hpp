@@ -10,7 +10,8 @@
 namespace df {
 
 enum LadderVariant {
-    LV_GJB = 0,        // certified FP64 kernels (screening, symmetric ladder, the rest)
+    LV_GJB = 0,        // certified FP64 kernels (screening, symmetric ladder, elimination and
+                       // pivoting of the rest; small launches: one kernel)
     LV_GJB_O3 = 1,     // same kernels
     LV_VECTOR = 2,     // partial pivoting, FP64 vector FMAs
     LV_MFMA = 3,       // partial pivoting, FP64 MFMA trailing updates
